@@ -385,7 +385,8 @@ def run(s):
         tree = amr.build_tree(s["h"])
         scene = amr.pack(tree, s["h"], device=DEV)
         info = tree.info()
-        return dict(pool=scene.pool, nodes=info["nodes"], leaves=info["leaves"], depth=info["depth"])
+        # without the 256 spare bytes after the last brick, which hold no data and are not written
+        return dict(pool=scene.pool[:-256], nodes=info["nodes"], leaves=info["leaves"], depth=info["depth"])
     if kind == "fit":
         s["lut"].grad = s["shading"].grad = None
         rgba = amr.AMRRender.apply(s["lut"], s["shading"], s["scene"], s["cam_list"], s["params"], 4, 16, False, s["sched"])
