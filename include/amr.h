@@ -156,7 +156,10 @@ typedef struct {
     const void *face_taps;      /* per leaf, 6 records of 64 bytes for gradient taps beyond each
                                    face: the single owner's brick and the affine map from the
                                    leaf's patch-local cell coordinates into it, or the node to
-                                   descend from */
+                                   descend from.  Behind them (at the next multiple of 256 bytes
+                                   of the metadata): per leaf, 6 int32, the smallest node holding
+                                   the slab beyond each face, where a ray leaving through the face
+                                   resumes its descent */
     int64_t pool_bytes, meta_bytes;
     int32_t nnodes, nleaves, npatches, nlevels;
     int32_t lmax, refine, depth, brick_layout;

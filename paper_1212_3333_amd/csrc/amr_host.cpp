@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <cmath>
 #include <cstdarg>
@@ -646,6 +647,41 @@ uint32_t face_owners(const amr_tree *T, const Node &lf, const std::vector<int32_
     return mask;
 }
 
+// Ropes: for each leaf face 2a+side, the smallest node (breadth-first index) whose box holds the
+// whole slab of finest-level cells beyond the face, 0 (the root) where the slab leaves B.  Built top
+// down: a child inherits its parent's ropes, takes its sibling across the split, and each rope is
+// pushed down while one child still holds the face's slab.  order: nodes breadth first.
+void leaf_ropes(const amr_tree *T, const std::vector<int32_t> &order, const std::vector<int32_t> &bfs_index,
+                const std::vector<int32_t> &leaf_id, int32_t *out) {
+    std::vector<std::array<int32_t, 6>> rope(T->nodes.size());
+    rope[order[0]].fill(-1);
+    for (int32_t ni : order) {
+        const Node &n = T->nodes[ni];
+        std::array<int32_t, 6> &r = rope[ni];
+        for (int f = 0; f < 6; f++) {
+            const int a = f >> 1;
+            while (r[f] >= 0 && T->nodes[r[f]].axis >= 0) {
+                const Node &m = T->nodes[r[f]];
+                int64_t lo = n.lo[m.axis], hi = n.hi[m.axis];
+                if (m.axis == a) {
+                    lo = (f & 1) ? n.hi[a] : n.lo[a] - 1;
+                    hi = lo + 1;
+                }
+                if (hi <= m.split) r[f] = m.low;
+                else if (lo >= m.split) r[f] = m.high;
+                else break;
+            }
+        }
+        if (n.axis < 0) {
+            for (int f = 0; f < 6; f++) out[6 * (int64_t)leaf_id[ni] + f] = r[f] >= 0 ? bfs_index[r[f]] : 0;
+        } else {
+            rope[n.low] = rope[n.high] = r;
+            rope[n.low][2 * n.axis + 1] = n.high;
+            rope[n.high][2 * n.axis] = n.low;
+        }
+    }
+}
+
 double world_plane(const amr_tree *T, int a, int64_t G) {
     double g = (double)G;
     double hf = T->dom.h0[a] / (double)T->scale[0];
@@ -768,7 +804,8 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
     const int64_t o_patch = align_up(o_leaves + nl * (int64_t)sizeof(DLeaf), 256);
     const int64_t o_faces = align_up(o_patch + np * (int64_t)sizeof(DPatch), 256);
     const int64_t o_fxf = align_up(o_faces + nl * 6 * (int64_t)sizeof(int32_t), 256);
-    const int64_t mbytes = align_up(o_fxf + nl * 6 * (int64_t)sizeof(DFaceXf), 256);
+    const int64_t o_ropes = ropes_offset(o_fxf, nl);
+    const int64_t mbytes = align_up(o_ropes + nl0 * 6 * (int64_t)sizeof(int32_t), 256);
     const int64_t pbytes = std::max<int64_t>((nfl + 64) * 4, 256);   // trailing pad
     if (!d_pool && !d_meta) {
         *pool_bytes = pbytes;
@@ -835,6 +872,7 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
                 order.push_back(n.high);
             }
         }
+        leaf_ropes(T, order, bfs_index, leaf_id, (int32_t *)(meta.data() + o_ropes));
         DPatch *dp = (DPatch *)(meta.data() + o_patch);
         for (int p = 0; p < np; p++) {
             DPatch &h = dp[p];

@@ -63,6 +63,12 @@ static_assert(sizeof(DFaceXf) == 64, "DFaceXf layout");
 
 constexpr uint32_t kLeafAxis = 3u;
 
+// Ropes of the real leaves (int32[nleaves][6], node indices), behind the gradient-tap records of
+// all nrec leaf records: byte offset from the buffer's start, given the tap records' offset.
+constexpr int64_t ropes_offset(int64_t o_fxf, int64_t nrec) {
+    return (o_fxf + nrec * 6 * (int64_t)sizeof(DFaceXf) + 255) / 256 * 256;
+}
+
 // Offset (in floats) of padded-brick cell (i, j, k) (0 <= index <= n + 1) in each layout; for
 // the halo-row layout, the copy in the block column i / 4 (a cell also sits in the halo of the
 // neighbouring block row when i mod 4 is 0, 1, 2 or 3: see halo_row_fill).

@@ -579,9 +579,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LIT ? 3 : 4
         a.C2 = c0.C[2];
         int s = c0.sidx;
         double tcur = c0.t;
+        uint32_t start = 0;
         while (s < s_end && tcur < R.t1) {
             double tb = R.t1;
-            int leaf = descend(A, R, tcur, tb);
+            int leaf = descend(A, R, tcur, tb, start);
             if (leaf < 0) break;
             const DLeaf &L = A.leaves[leaf];
             if (L.patch >= 0) {
