@@ -1,7 +1,7 @@
 // Persistent multi-camera raycasting: one launch renders many cameras of different sizes.
 //
-// Work unit: a 64-pixel tile (tile_w x tile_h) rendered by one wave, one ray per lane, with
-// the per-ray code of the single-camera kernel.  Waves take tiles from one global atomic
+// Work unit: a quarter (16 pixels) of a 64-pixel tile (tile_w x tile_h), rendered by one wave with
+// four lanes per ray and the per-ray code of the single-camera kernel.  Waves take units from one global atomic
 // queue that lists the cameras largest first, so the short images of a batch fill the tail of
 // the long ones.  The wave that finishes an image's last tile writes the device clock into
 // stamps[camera]; the wave that takes tile 0 writes stamps[ncams] (launch start).  Everything
@@ -21,11 +21,11 @@ namespace amr {
 constexpr int kQueues = 8;
 
 struct QueueView {
-    unsigned int *next;          // [kQueues] next tile of each queue, 64 bytes apart
-    unsigned int *done;          // [ncams] tiles finished per camera
-    unsigned int *ntiles;        // [ncams] tiles of each camera over all queues
+    unsigned int *next;          // [kQueues] next unit of each queue, 64 bytes apart
+    unsigned int *done;          // [ncams] units finished per camera
+    unsigned int *ntiles;        // [ncams] units (quarter tiles) of each camera over all queues
     int *order;                  // [ncams] cameras in queue order
-    long long *tile0;            // [kQueues][ncams + 1] first tile of the k-th camera in `order`
+    long long *tile0;            // [kQueues][ncams + 1] first unit of the k-th camera in `order`
     long long *pix0;             // [ncams] first pixel of camera c in the rgba output
     int *tiles_x, *tiles_y;      // [ncams]
     int *sgrid;                  // [ncams] side of the power-of-two super-tile grid
@@ -79,7 +79,7 @@ __global__ void queue_setup(const amr_camera *cams, int ncams, void *qbase, int 
         int sg = 1;
         while (sg * 4 < q.tiles_x[c] || sg * 4 < q.tiles_y[c]) sg *= 2;
         q.sgrid[c] = sg;
-        q.ntiles[c] = xcd_tiles ? (unsigned int)(16 * sg * sg) : (unsigned int)(q.tiles_x[c] * q.tiles_y[c]);
+        q.ntiles[c] = 4u * (xcd_tiles ? (unsigned int)(16 * sg * sg) : (unsigned int)(q.tiles_x[c] * q.tiles_y[c]));
         if (stamps) stamps[c] = 0ull;
     }
     if (stamps) stamps[ncams] = 0ull;
@@ -102,7 +102,7 @@ __global__ void queue_setup(const amr_camera *cams, int ncams, void *qbase, int 
             const int c = q.order[k];
             if (xcd_tiles) {
                 const long long S = (long long)q.sgrid[c] * q.sgrid[c];      // super-tiles x, x + 8, ...
-                t += x < S ? 16 * ((S - x + kQueues - 1) / kQueues) : 0;
+                t += x < S ? 64 * ((S - x + kQueues - 1) / kQueues) : 0;
             } else if (x == 0) {
                 t += q.ntiles[c];
             }
@@ -169,7 +169,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
         const int c = q.order[k];
         const amr_camera C = B.cams[c];
         set_camera(A, C);
-        const long long local = (long long)tile - tile0[k];
+        const int quarter = (int)(((long long)tile - tile0[k]) & 3);
+        const long long local = ((long long)tile - tile0[k]) >> 2;
         int tx, ty;
         if (B.xcd_tiles) {
             // super-tile qx + 8 (local / 16) along the Morton curve, tile local % 16 in it
@@ -188,14 +189,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
             tx = (int)(local % txs);
             ty = (int)(local / txs);
         }
-        const int pi = tx * B.tw + lane % B.tw;
-        const int pj = ty * B.th + lane / B.tw;
+        // the unit's pixels: 4x4 where the tile has them, else 16 in a row of the tile's pixels
+        const int r = lane >> 2, sub = lane & 3;
+        int px, py;
+        if (B.tw == 8) {
+            px = (quarter & 1) * 4 + (r & 3);
+            py = (quarter >> 1) * 4 + (r >> 2);
+        } else {
+            px = (quarter * 16 + r) % B.tw;
+            py = (quarter * 16 + r) / B.tw;
+        }
+        const int pi = tx * B.tw + px;
+        const int pj = ty * B.th + py;
         const bool valid = pi < C.width && pj < C.height;
         float C0 = 0.f, C1 = 0.f, C2 = 0.f, T = 1.f;
         int nsamp_total = 0;
         Ray R;
         bool alive = valid && setup_ray(A, pi, pj, R);
-        if (REC) cnt.hit += alive ? 1 : 0;
+        if (REC) cnt.hit += alive && sub == 0 ? 1 : 0;
         if (LIT) tapq_init(*tq, lane);
         double tcur = R.t0;
         uint32_t start = 0;
@@ -203,77 +214,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
             double tb = R.t1;
             int leaf = descend(A, R, tcur, tb, start);
             if (leaf < 0) break;
-            if (REC) cnt.segments++;
+            if (REC && sub == 0) cnt.segments++;
             const DLeaf &L = A.leaves[leaf];
             if (L.patch >= 0) {
                 Segment S;
                 setup_segment<LIT, LAY>(A, R, L, leaf, tcur, tb, S);
-                if constexpr (!LIT && !REC) {
-                    float tseg = 1.f;
-                    bool stop;
-                    nsamp_total += composite_unlit<LAY>(A, s_lut, R, S, T, C0, C1, C2, tseg, stop, cnt);
-                    if (stop) alive = false;
-                } else if constexpr (LIT && !REC) {
-                    // as the single-camera kernel: the stencils of a lane's next two samples are
-                    // read together; after the first, the lanes still in this loop (each with a
-                    // second sample) take it when the queue has a slot for those of them whose
-                    // second sample defers, else they read it again in the next round
+                if constexpr (LIT) {
+                    // the steps of the single-camera kernel by the quads still in this segment,
+                    // which resolve the queue themselves when it lacks room for the step
                     TapQueue &Q = *tq;
-                    for (int k2 = 0; k2 < S.n;) {
-                        tapq_reserve<REC, LAY>(A, s_lut, Q, lane, cnt);
-                        const int kb = min(k2 + 1, S.n - 1);
-                        const float kka = (float)k2 + 0.5f, kkb = (float)kb + 0.5f;
-                        float qa[3], qb[3], Fa, Fpa[3], Fma[3], Fb, Fpb[3], Fmb[3];
-                        #pragma unroll
-                        for (int a = 0; a < 3; a++) {
-                            qa[a] = S.q0[a] + kka * S.dq[a];
-                            qb[a] = S.q0[a] + kkb * S.dq[a];
-                        }
-                        const uint32_t cla = lit_stencil<REC, LAY>(A, S, qa[0], qa[1], qa[2], Fa, Fpa, Fma);
-                        const uint32_t clb = lit_stencil<REC, LAY>(A, S, qb[0], qb[1], qb[2], Fb, Fpb, Fmb);
-                        float alpha = lit_consume<REC>(A, s_lut, Q, lane, R, S, k2, nullptr, qa[0], qa[1], qa[2], Fa,
-                                                       Fpa, Fma, cla, pending_taps(cla), T, C0, C1, C2, cnt, nullptr,
-                                                       nullptr);
-                        T *= 1.f - alpha;
-                        nsamp_total++;
-                        k2++;
-                        if (T < A.t_min) { alive = false; break; }
-                        if (k2 == S.n) break;
-                        const unsigned long long needb = __ballot(pending_taps(clb) != 0u);
-                        if (tapq_full(tq_count(Q), needb)) continue;
-                        alpha = lit_consume<REC>(A, s_lut, Q, lane, R, S, k2, nullptr, qb[0], qb[1], qb[2], Fb, Fpb,
-                                                 Fmb, clb, pending_taps(clb), T, C0, C1, C2, cnt, nullptr, nullptr);
-                        T *= 1.f - alpha;
-                        nsamp_total++;
-                        k2++;
-                        if (T < A.t_min) { alive = false; break; }
+                    uint32_t tpos = 0;
+                    for (int k = 0; k < S.n && alive; k += 4) {
+                        const LitPoint pt = lit_point<false>(A, R, S, min(k + sub, S.n - 1));
+                        if (tapq_full(tq_count(Q), __ballot(pt.pend != 0u && k + sub < S.n)))
+                            tapq_flush<REC, LAY>(A, s_lut, Q, lane, cnt);
+                        const QuadStep st = lit_step<REC, LAY, false>(A, s_lut, Q, lane, R, S, k, pt, T, C0, C1, C2, cnt,
+                                                                      nullptr, tpos);
+                        nsamp_total += st.n;
+                        if (st.stop) alive = false;
                     }
                 } else {
-                    for (int k2 = 0; k2 < S.n; k2++) {
-                        float alpha;
-                        if (LIT) {
-                            // as the single-camera kernel: taps that leave the brick are deferred
-                            TapQueue &Q = *tq;
-                            tapq_reserve<REC, LAY>(A, s_lut, Q, lane, cnt);
-                            alpha = lit_sample_deferred<REC, LAY>(A, s_lut, Q, lane, R, S, k2, T, C0, C1, C2, cnt);
-                        } else {
-                            SampleVals v;
-                            eval_sample<false, REC, false, LAY>(A, s_lut, R, S, k2, v, cnt);
-                            float wgt = T * v.alpha * v.shade;
-                            C0 += wgt * v.r;
-                            C1 += wgt * v.g;
-                            C2 += wgt * v.b;
-                            alpha = v.alpha;
-                        }
-                        T *= 1.f - alpha;
-                        nsamp_total++;
-                        if (T < A.t_min) { alive = false; break; }
-                    }
+                    bool stop;
+                    nsamp_total += composite_unlit_quad<REC, false, LAY>(A, s_lut, R, S, sub, T, C0, C1, C2, stop, cnt);
+                    if (stop) alive = false;
                 }
             }
             if (tb <= tcur) {
-                if (REC) cnt.guard++;
+                if (REC && sub == 0) cnt.guard++;
                 tb = nextafter(tcur, INFINITY);
+                start = 0;
             }
             tcur = tb;
         }
@@ -284,10 +253,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
             C1 += D1;
             C2 += D2;
         }
-        if (REC) cnt.samples += nsamp_total;
-        if (valid) reinterpret_cast<float4 *>(B.base.rgba)[q.pix0[c] + (long long)pj * C.width + pi] =
+        C0 = quad_sum(C0);
+        C1 = quad_sum(C1);
+        C2 = quad_sum(C2);
+        if (REC && sub == 0) cnt.samples += nsamp_total;
+        if (valid && sub == 0) reinterpret_cast<float4 *>(B.base.rgba)[q.pix0[c] + (long long)pj * C.width + pi] =
             make_float4(C0, C1, C2, 1.f - T);
-        // completion: the wave that finishes the image's last tile stamps it
+        // completion: the wave that finishes the image's last unit stamps it
         __threadfence();
         if (lane == 0) {
             unsigned int d = atomicAdd(&q.done[c], 1u) + 1u;

@@ -176,7 +176,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT ? 2 : (L
 
     Counters cnt;
     unsigned int c_skip = 0, c_coarse = 0, c_net = 0;
-    float C0 = 0.f, C1 = 0.f, C2 = 0.f, T = 1.f;
+    float C[3][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}}, T = 1.f;   // partial sums
     float budget = 0.f;                   // sum of T * alpha_hi over the segments skipped so far
     int nsamp_total = 0;
     Ray R;
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT ? 2 : (L
             }
             if constexpr (!LIT && !LOG) {
                 bool stop;
-                const int done = composite_unlit<LAY>(A, s_lut, R, S, T, C0, C1, C2, tseg, stop, cnt);
+                const int done = composite_unlit<LAY>(A, s_lut, R, S, T, C, tseg, stop, cnt);
                 nsamp_total += done;
                 if (stop) { alive = false; full = done == S.n; }
             } else {
@@ -307,9 +307,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT ? 2 : (L
                     SampleVals v;
                     eval_sample<LIT, false, false, LAY>(A, s_lut, R, S, k, v, cnt);
                     float wgt = T * v.alpha * v.shade;
-                    C0 += wgt * v.r;
-                    C1 += wgt * v.g;
-                    C2 += wgt * v.b;
+                    #pragma unroll
+                    for (int u = 0; u < 4; u++) {
+                        if ((k & 3) == u) {
+                            C[0][u] += wgt * v.r;
+                            C[1][u] += wgt * v.g;
+                            C[2][u] += wgt * v.b;
+                        }
+                    }
                     T *= 1.f - v.alpha;
                     tseg *= 1.f - v.alpha;
                     nsamp_total++;
@@ -350,7 +355,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT ? 2 : (L
             tcur = tb;
         }
     }
-    if (valid) reinterpret_cast<float4 *>(A.rgba)[ray] = make_float4(C0, C1, C2, 1.f - T);
+    if (valid) reinterpret_cast<float4 *>(A.rgba)[ray] = make_float4(sum4(C[0]), sum4(C[1]), sum4(C[2]), 1.f - T);
     if (A.nsamp && valid) A.nsamp[ray] = nsamp_total;
     if (A.stats) {
         cnt.samples = nsamp_total;

@@ -1,7 +1,7 @@
 // Device side of libamr: the single-pass raycaster (Section 5.3), its adjoint, and launchers.
 //
-// One lane owns one ray and a wave64 covers an 8x8 pixel tile; the forward kernel runs one wave
-// per block, the adjoint four.
+// In the forward kernel four lanes march one ray and a wave64 covers 4x4 pixels, one wave per block;
+// in the adjoint a lane owns one ray's interval, four waves per block.
 // The FP64 parts (ray generation, slab clip, kD-restart planes, sample positions of gradient
 // taps) are written with contraction disabled so that every operation is correctly rounded
 // exactly once; the per-sample arithmetic (trilinear, LUT, exp, compositing) is fp32 in
@@ -24,8 +24,8 @@ namespace amr {
 // Forward kernel
 // ------------------------------------------------------------------------------------------
 
-// At least 3 waves per SIMD: the timed lit kernel fits in 158 VGPRs without spilling and 12 KB
-// of LDS (its tap queue), so 12 waves share a CU; the unlit one needs 78 VGPRs and runs 6.
+// At least 3 waves per SIMD: the timed lit kernel takes 168 VGPRs (its queue resolution) and 9.8 KB of
+// LDS; forced to 4 (128 VGPRs) it spills and the 1024^2 view takes 20.3 ms instead of 12.8.
 // LAY: the brick layout fixed at compile time for the timed variants (-1: read at run time).
 // Lit variants defer the samples whose gradient taps leave the brick (trilinear) or need the
 // tree (nearest cell) to a per-wave queue (TapQueue).
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void re
     uint32_t sst = 0xffffffffu;
     constexpr uint32_t kSide = sched_side(LIT);
     if (G.sched) {
-        const uint32_t rank = (blockIdx.x / (8u * kSide * kSide)) * 8u + blockIdx.x % 8u;
+        const uint32_t rank = (blockIdx.x / (32u * kSide * kSide)) * 8u + blockIdx.x % 8u;
         if (rank >= G.nst) return;
         uint32_t e;
         if (A.sched_hdr[4 * G.cam0 + 1] == G.sig) {
@@ -65,22 +65,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void re
     for (int i = threadIdx.x; i < 256; i += 64) s_lut[i] = A.lut[i];
     __syncthreads();
 
-    // One wave per block, one 8x8 pixel tile per wave.  Tiles are grouped in 4x4 super-tiles
-    // (32x32 pixels) numbered along a Morton curve; blocks are dealt round-robin to the 8 XCDs
-    // and XCD x renders super-tiles x, x + 8, x + 16, ...  Every XCD thus gets a share of every
-    // part of the image (the work per tile varies by 10x and more across the screen), while
+    // One wave per block, 4x4 pixels per wave, four waves per 8x8 tile.  Tiles are grouped in 4x4
+    // super-tiles (32x32 pixels) numbered along a Morton curve; blocks are dealt round-robin to the
+    // 8 XCDs and XCD x renders super-tiles x, x + 8, x + 16, ...  Every XCD thus gets a share of
+    // every part of the image (the work per tile varies by 10x and more across the screen), while
     // the tiles in flight on one XCD stay grouped in a few compact 32x32 patches whose rays
     // share bricks in that XCD's L2.  With a tile schedule, the super-tiles of all the launch's
     // cameras (kSide x kSide tiles) are dealt the same way in the schedule's order (longest tile
     // of the last call first) instead.
+    const uint32_t quarter = (blockIdx.x / 8u) & 3u;
     int col, row;
     if (G.sched) {
         const uint32_t sgw = ((uint32_t)A.t8x + kSide - 1u) / kSide;
-        const uint32_t li = blockIdx.x / 8u;
+        const uint32_t li = blockIdx.x / 32u;
         col = (int)((sst % sgw) * kSide + (li % (kSide * kSide)) / kSide);
         row = (int)((sst / sgw) * kSide + li % kSide);
     } else {
-        const int xcd = (int)(blockIdx.x % 8), li = (int)(blockIdx.x / 8);
+        const int xcd = (int)(blockIdx.x % 8), li = (int)(blockIdx.x / 32);
         const int sidx = (li >> 4) * 8 + xcd;          // Morton index of the super-tile
         int sx = 0, sy = 0;
         #pragma unroll
@@ -91,12 +92,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void re
         col = sx * 4 + ((li & 15) >> 2);
         row = sy * 4 + (li & 3);
     }
-    if (col >= A.t8x || row >= A.t8y) return;
-    const unsigned long long tile_t0 = A.sched_time ? wall_clock64() : 0ull;
-    const int lane = threadIdx.x & 63;
-    const int pi = col * 8 + (lane & 7);
-    const int pj = row * 8 + (lane >> 3);
+    const int lane = threadIdx.x & 63, sub = lane & 3;
+    const int pi0 = col * 8 + (int)(quarter & 1u) * 4, pj0 = row * 8 + (int)(quarter >> 1) * 4;
+    if (pi0 >= A.width || pj0 >= A.height) return;
+    // a tile's time is that of its first quarter (the quarters' times lie close together)
+    const bool timed = A.sched_time && quarter == 0u;
+    const unsigned long long tile_t0 = timed ? wall_clock64() : 0ull;
+    const int pi = pi0 + ((lane >> 2) & 3);
+    const int pj = pj0 + (lane >> 4);
     const bool valid = pi < A.width && pj < A.height;
+    const bool lead = sub == 0;             // the quad's lane that writes the ray's outputs
     const int64_t ray = (int64_t)pj * A.width + pi;
 
     Counters cnt;
@@ -104,27 +109,67 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void re
     int nseg = 0, nsamp_total = 0;
     Ray R;
     bool alive = valid && setup_ray(A, pi, pj, R);
-    if (REC) cnt.hit = alive ? 1 : 0;
+    if (REC) cnt.hit = alive && lead ? 1 : 0;
     // checkpoints for the adjoint: (t, T, C) at the start of every `every`-th data segment
     CkptHeader *ckh = nullptr;
     Ckpt *ck = nullptr;
     int nck = 0, every = A.ckpt_every, dseg = 0;
     // the tape (lit, with checkpoints): the ray's row and its records so far; tape_base is the row
-    // of the tile's lane 0, which the queue resolution addresses owners from
+    // of the wave's first pixel, which the queue resolution addresses owners from
     uint32_t tpos = 0;
-    const int64_t tape_base = (kCk && LIT && A.tape) ? A.ckpt_ray0 + (int64_t)(row * 8) * A.width + col * 8 : -1;
+    const int64_t tape_base = (kCk && LIT && A.tape) ? A.ckpt_ray0 + (int64_t)pj0 * A.width + pi0 : -1;
     float4 *trow = (kCk && LIT && A.tape && valid) ? A.tape + (A.ckpt_ray0 + ray) * A.tape_cap : nullptr;
     if (kCk && A.ckpt && valid) {
         ckh = reinterpret_cast<CkptHeader *>(A.ckpt + (A.ckpt_ray0 + ray) * A.ckpt_stride);
         ck = reinterpret_cast<Ckpt *>(ckh + 1);
     }
+    // checkpoint before a data segment (its quad's lanes together); the colour (D: what the
+    // deferred samples added, all resolved) is the pixel's sum so far
+    auto checkpoint = [&](double t, float D0, float D1, float D2) {
+        if (dseg % every == 0) {
+            if (nck == A.ckpt_max) {             // full: keep every other, halve the rate
+                if (lead)
+                    for (int i = 0; i < A.ckpt_max / 2; i++) ck[i] = ck[2 * i];
+                nck = A.ckpt_max / 2;
+                every *= 2;
+                if (REC && lead) cnt.ckover++;
+            }
+            if (dseg % every == 0) {
+                Ckpt c;
+                c.t = t;
+                c.T = T;
+                c.C[0] = quad_sum(C0 + D0);
+                c.C[1] = quad_sum(C1 + D1);
+                c.C[2] = quad_sum(C2 + D2);
+                c.rec = (int32_t)tpos;
+                c.sidx = nsamp_total;
+                if (lead) ck[nck] = c;
+                nck++;
+            }
+        }
+        dseg++;
+    };
+    auto trace = [&](int leaf, int patch, int n, double ta, double tb) {
+        if (!lead) return;
+        if (nseg < A.trace_cap) {
+            amr_trace_rec rec;
+            rec.leaf = leaf;
+            rec.patch = patch;
+            rec.n = n;
+            rec.level = leaf_level(A.leaves[leaf]);
+            rec.ta = ta;
+            rec.tb = tb;
+            A.trace[ray * A.trace_cap + nseg] = rec;
+        } else {
+            cnt.tover++;
+        }
+    };
     if constexpr (kDefer) {
-        // Lit, deferred taps: the wave's lanes step together.  A step either fetches the next
-        // data segment of the lanes that have none (once half of the live lanes wait, or
-        // all do) or takes one sample on every lane that has a segment; the tap queue is
-        // resolved at the top of a step, where every lane of the wave works on it.  Segments,
-        // sample positions and traces are those of the per-segment loop of the unlit variants
-        // below.
+        // Lit, deferred taps: the wave's quads step together.  A step either fetches the next
+        // data segment of the quads that have none (once a quarter of the live ones wait) or
+        // takes four samples on every quad that has a segment; the tap queue is resolved before
+        // a step's stencils are read, where every lane of the wave works on it.  Segments, sample
+        // positions and traces are those of the per-segment loop of the unlit variants below.
         TapQueue &Q = *tq;
         tapq_init(Q, lane);
         double tcur = R.t0;
@@ -135,11 +180,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void re
         while (true) {
             const unsigned long long live = __ballot(alive);
             if (!live) break;
-            const unsigned long long samp = __ballot(has);
-            if (tapq_full(tq_count(Q), samp)) tapq_flush<REC, LAY, NEAR, kCk>(A, s_lut, Q, lane, cnt, tape_base);
             const bool waiting = alive && !has;
-            const unsigned long long wait = __ballot(waiting);
-            if (stepped_fetch(live, wait)) {
+            if (stepped_fetch(live, __ballot(waiting))) {
                 if (kCk && A.ckpt && tq_count(Q)) tapq_flush<REC, LAY, NEAR, kCk>(A, s_lut, Q, lane, cnt, tape_base);
                 if (waiting) {
                     while (true) {            // next segment with samples, or the end of the ray
@@ -147,59 +189,26 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void re
                         double tb = R.t1;
                         const int leaf = descend(A, R, tcur, tb, start);
                         if (leaf < 0) { alive = false; break; }
-                        if (REC) cnt.segments++;
+                        if (REC && lead) cnt.segments++;
                         if (REC && A.touch_meta) touch_segment_meta(A, R, tcur, leaf);
                         const DLeaf &L = A.leaves[leaf];
                         const int p = L.patch;
                         int n = 0;
                         if (p >= 0) {
-                            if (kCk && ck) {
-                                if (dseg % every == 0) {
-                                    if (nck == A.ckpt_max) {     // full: keep every other, halve the rate
-                                        for (int i = 0; i < A.ckpt_max / 2; i++) ck[i] = ck[2 * i];
-                                        nck = A.ckpt_max / 2;
-                                        every *= 2;
-                                        if (REC) cnt.ckover++;
-                                    }
-                                    if (dseg % every == 0) {     // colour: shaded at once + deferred, all resolved
-                                        Ckpt c;
-                                        c.t = tcur;
-                                        c.T = T;
-                                        c.C[0] = C0 + Q.cd[0][lane];
-                                        c.C[1] = C1 + Q.cd[1][lane];
-                                        c.C[2] = C2 + Q.cd[2][lane];
-                                        c.rec = (int32_t)tpos;
-                                        c.sidx = nsamp_total;
-                                        ck[nck++] = c;
-                                    }
-                                }
-                                dseg++;
-                            }
+                            if (kCk && ck) checkpoint(tcur, Q.cd[0][lane], Q.cd[1][lane], Q.cd[2][lane]);
                             setup_segment<LIT, LAY>(A, R, L, leaf, tcur, tb, S);
                             n = S.n;
                             if (kCk && trow && n > 0) {
-                                if (tpos < (uint32_t)A.tape_cap) trow[tpos] = tape_segment(S.delta, S.dl, n);
+                                if (lead && tpos < (uint32_t)A.tape_cap) trow[tpos] = tape_segment(S.delta, S.dl, n);
                                 tpos++;
                             }
                         }
-                        if (REC && A.trace) {
-                            if (nseg < A.trace_cap) {
-                                amr_trace_rec rec;
-                                rec.leaf = leaf;
-                                rec.patch = p;
-                                rec.n = n;
-                                rec.level = leaf_level(L);
-                                rec.ta = tcur;
-                                rec.tb = tb;
-                                A.trace[ray * A.trace_cap + nseg] = rec;
-                            } else {
-                                cnt.tover++;
-                            }
-                        }
+                        if (REC && A.trace) trace(leaf, p, n, tcur, tb);
                         nseg++;
                         if (tb <= tcur) {   // never expected: keep the walk moving forward
-                            if (REC) cnt.guard++;
+                            if (REC && lead) cnt.guard++;
                             tb = nextafter(tcur, INFINITY);
+                            start = 0;
                         }
                         tcur = tb;
                         if (n > 0) {
@@ -211,67 +220,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void re
                 }
                 continue;
             }
-            if constexpr (!REC && !NEAR) {
-                // Two samples per step: the stencils of a lane's next two samples are read
-                // together (one round of brick reads for both), the first is taken as above,
-                // and the second too when the queue has a slot for each lane whose second
-                // sample defers (tapq_full over those lanes); otherwise it is read again in the
-                // next step.  The samples are taken in order and each lane's queued samples
-                // stay in its sample order (one run per push), so results are those of one
-                // sample per step.
-                float qa[3], qb[3], Fa, Fpa[3], Fma[3], Fb, Fpb[3], Fmb[3];
-                uint32_t cla = 0u, clb = 0u;
-                if (has) {
-                    const int kb = min(k + 1, S.n - 1);
-                    const float kka = (float)k + 0.5f, kkb = (float)kb + 0.5f;
-                    #pragma unroll
-                    for (int a = 0; a < 3; a++) {
-                        qa[a] = S.q0[a] + kka * S.dq[a];
-                        qb[a] = S.q0[a] + kkb * S.dq[a];
-                    }
-                    cla = lit_stencil<REC, LAY>(A, S, qa[0], qa[1], qa[2], Fa, Fpa, Fma);
-                    clb = lit_stencil<REC, LAY>(A, S, qb[0], qb[1], qb[2], Fb, Fpb, Fmb);
-                    const float alpha = lit_consume<REC>(A, s_lut, Q, lane, R, S, k, nullptr, qa[0], qa[1], qa[2], Fa,
-                                                         Fpa, Fma, cla, pending_taps(cla), T, C0, C1, C2, cnt, trow,
-                                                         &tpos);
-                    T *= 1.f - alpha;
-                    nsamp_total++;
-                    k++;
-                    if (T < A.t_min) {
-                        alive = false;
-                        has = false;
-                    } else if (k == S.n) {
-                        has = false;
-                    }
-                }
-                const unsigned long long second = __ballot(has);
-                const unsigned long long needb = __ballot(has && pending_taps(clb) != 0u);
-                if (second && !tapq_full(tq_count(Q), needb) && has) {
-                    const float alpha = lit_consume<REC>(A, s_lut, Q, lane, R, S, k, nullptr, qb[0], qb[1], qb[2], Fb,
-                                                         Fpb, Fmb, clb, pending_taps(clb), T, C0, C1, C2, cnt, trow,
-                                                         &tpos);
-                    T *= 1.f - alpha;
-                    nsamp_total++;
-                    k++;
-                    if (T < A.t_min) {
-                        alive = false;
-                        has = false;
-                    } else if (k == S.n) {
-                        has = false;
-                    }
-                }
-            } else if (has) {
-                const float alpha = lit_sample_deferred<REC, LAY, NEAR>(A, s_lut, Q, lane, R, S, k, T, C0, C1, C2, cnt,
-                                                                       trow, &tpos);
-                T *= 1.f - alpha;
-                nsamp_total++;
-                k++;
-                if (T < A.t_min) {
-                    alive = false;
-                    has = false;
-                } else if (k == S.n) {
-                    has = false;
-                }
+            LitPoint pt;
+            pt.pend = 0u;
+            if (has) pt = lit_point<NEAR>(A, R, S, min(k + sub, S.n - 1));
+            if (tapq_full(tq_count(Q), __ballot(has && pt.pend != 0u && k + sub < S.n)))
+                tapq_flush<REC, LAY, NEAR, kCk>(A, s_lut, Q, lane, cnt, tape_base);
+            if (has) {
+                const QuadStep q = lit_step<REC, LAY, NEAR>(A, s_lut, Q, lane, R, S, k, pt, T, C0, C1, C2, cnt, trow, tpos);
+                nsamp_total += q.n;
+                k += 4;
+                if (q.stop) alive = false;
+                if (q.stop || k >= S.n) has = false;
             }
         }
         float D0, D1, D2;
@@ -286,83 +245,38 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void re
             double tb = R.t1;
             int leaf = descend(A, R, tcur, tb, start);
             if (leaf < 0) break;
-            if (REC) cnt.segments++;
+            if (REC && lead) cnt.segments++;
             if (REC && A.touch_meta) touch_segment_meta(A, R, tcur, leaf);
             const DLeaf &L = A.leaves[leaf];
             const int p = L.patch;
             int nsm = 0;
             if (p >= 0) {
-                if (kCk && ck) {
-                    if (dseg % every == 0) {
-                        if (nck == A.ckpt_max) {             // full: keep every other, halve the rate
-                            for (int i = 0; i < A.ckpt_max / 2; i++) ck[i] = ck[2 * i];
-                            nck = A.ckpt_max / 2;
-                            every *= 2;
-                            if (REC) cnt.ckover++;
-                        }
-                        if (dseg % every == 0) {
-                            Ckpt c;
-                            c.t = tcur;
-                            c.T = T;
-                            c.C[0] = C0;
-                            c.C[1] = C1;
-                            c.C[2] = C2;
-                            c.rec = 0;
-                            c.sidx = nsamp_total;
-                            ck[nck++] = c;
-                        }
-                    }
-                    dseg++;
-                }
+                if (kCk && ck) checkpoint(tcur, 0.f, 0.f, 0.f);
                 Segment S;
                 setup_segment<LIT, LAY>(A, R, L, leaf, tcur, tb, S);
                 nsm = S.n;
-                if constexpr (!REC && !kCk && !NEAR) {
-                    float tseg = 1.f;
-                    bool stop;
-                    nsamp_total += composite_unlit<LAY>(A, s_lut, R, S, T, C0, C1, C2, tseg, stop, cnt);
-                    if (stop) alive = false;
-                } else {
-                    for (int k = 0; k < nsm; k++) {
-                        SampleVals v;
-                        eval_sample<LIT, REC, NEAR, LAY>(A, s_lut, R, S, k, v, cnt);
-                        float wgt = T * v.alpha * v.shade;
-                        C0 += wgt * v.r;
-                        C1 += wgt * v.g;
-                        C2 += wgt * v.b;
-                        T *= 1.f - v.alpha;
-                        nsamp_total++;
-                        if (T < A.t_min) { alive = false; break; }
-                    }
-                }
+                bool stop;
+                nsamp_total += composite_unlit_quad<REC, NEAR, LAY>(A, s_lut, R, S, sub, T, C0, C1, C2, stop, cnt);
+                if (stop) alive = false;
             }
-            if (REC && A.trace) {
-                if (nseg < A.trace_cap) {
-                    amr_trace_rec rec;
-                    rec.leaf = leaf;
-                    rec.patch = p;
-                    rec.n = p >= 0 ? nsm : 0;
-                    rec.level = leaf_level(L);
-                    rec.ta = tcur;
-                    rec.tb = tb;
-                    A.trace[ray * A.trace_cap + nseg] = rec;
-                } else {
-                    cnt.tover++;
-                }
-            }
+            if (REC && A.trace) trace(leaf, p, nsm, tcur, tb);
             nseg++;
             if (tb <= tcur) {   // never expected: keep the walk moving forward
-                if (REC) cnt.guard++;
+                if (REC && lead) cnt.guard++;
                 tb = nextafter(tcur, INFINITY);
+                start = 0;
             }
             tcur = tb;
         }
     }
-    if (A.sched_time && lane == 0) {
+    C0 = quad_sum(C0);
+    C1 = quad_sum(C1);
+    C2 = quad_sum(C2);
+    if (timed && lane == 0) {
         const unsigned long long dt = wall_clock64() - tile_t0;
         A.sched_time[A.tile0 + (int64_t)row * A.t8x + col] = dt < 0xffffffffull ? (uint32_t)dt : 0xffffffffu;
     }
-    if (valid) {
+    if (valid && lead) {
         reinterpret_cast<float4 *>(A.rgba)[ray] = make_float4(C0, C1, C2, 1.f - T);
         if (REC && A.trace_n) A.trace_n[ray] = nseg;
         if (REC && A.nsamp) A.nsamp[ray] = nsamp_total;
@@ -380,7 +294,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void re
         }
     }
     if (REC) {
-        cnt.samples = nsamp_total;
+        cnt.samples = lead ? nsamp_total : 0;
         if (A.stats) flush_counters(A.stats, cnt, lane);
     }
 }
@@ -1110,7 +1024,7 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
             Ai.cam = c0 + i;
             if (i == 0) A = Ai;
             G.cam[i] = cam_args_of(Ai, rel);
-            gx = std::max(gx, 8 * ((Ai.sgrid * Ai.sgrid + 7) / 8) * 16);
+            gx = std::max(gx, 32 * ((Ai.sgrid * Ai.sgrid + 7) / 8) * 16);
             SG.tile0[i] = tile_off;
             SG.t8x[i] = Ai.t8x;
             SG.t8y[i] = Ai.t8y;
@@ -1149,8 +1063,8 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
         A.touch = P->d_touch;
         A.ckpt_ray0 = pix_off;
         const bool rec = A.trace || A.trace_n || A.nsamp || A.stats || A.touch || A.touch_meta || A.ckpt;
-        // scheduled: one-dimensional, 16 blocks per super-tile, ranks dealt to the 8 XCDs in turn
-        const dim3 g(sched ? 8 * side * side * ((nst + 7) / 8) : gx, sched ? 1 : n), b(64);
+        // scheduled: one-dimensional, four blocks per tile, ranks dealt to the 8 XCDs in turn
+        const dim3 g(sched ? 32 * side * side * ((nst + 7) / 8) : gx, sched ? 1 : n), b(64);
         if (A.nearest) {
             if (A.lighting) {
                 if (rec) hipLaunchKernelGGL((render_fwd<true, true, true, -1>), g, b, 0, s, A, G);

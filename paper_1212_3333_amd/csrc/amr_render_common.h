@@ -103,8 +103,9 @@ struct CamGroup {
     CamArgs cam[kCamGroup];
     int32_t n;                       // cameras in the group; 0: one camera, RenderArgs as given
     // with a tile schedule: the launch is one-dimensional over the group's super-tiles of
-    // s x s tiles (s = sched_side), block b taking rank (b / (8 s^2)) * 8 + b % 8 of the order
-    // and tile (b / 8) % s^2 of that super-tile; an order entry is camera << 24 | super-tile
+    // s x s tiles (s = sched_side), block b taking rank (b / (32 s^2)) * 8 + b % 8 of the order,
+    // tile (b / 32) % s^2 of that super-tile and quarter (b / 8) % 4 of the tile; an order entry is
+    // camera << 24 | super-tile
     int32_t sched;                   // 1: a scheduled launch
     uint32_t nst;                    // super-tiles of the group
     uint32_t sig;                    // signature of the group's camera sizes, the order's key
@@ -1141,7 +1142,7 @@ __device__ __forceinline__ void eval_sample(const RenderArgs &A, const float4 *s
     const float qx = S.q0[0] + kk * S.dq[0], qy = S.q0[1] + kk * S.dq[1], qz = S.q0[2] + kk * S.dq[2];
     float F;
     if constexpr (NEAR) {
-        static_assert(!LIT, "lit nearest-cell samples take the tap queue (lit_sample_deferred)");
+        static_assert(!LIT, "lit nearest-cell samples take the tap queue (lit_step)");
         F = nearest_value<LAY>(A, R, S, k, qx, qy, qz);
     } else if (LIT) {
         // value and the six taps x +- h^l e_a from this brick in one fused stencil; a tap that
@@ -1163,33 +1164,37 @@ __device__ __forceinline__ void eval_sample(const RenderArgs &A, const float4 *s
     v.shade = LIT ? lit_shade(A, v.gv, v.dot, v.den) : 1.f;
 }
 
-// Unlit samples of one data segment, composited front to back (emission-absorption with early
-// termination, Section 5.3).  A ray's samples depend on each other only through T, so the
-// values of kUnlitBatch samples are evaluated (their brick loads in flight together) before
-// they are composited one by one in sample order; the ray's dependent memory round trips fall
-// by that factor.  A batch that runs past the segment's end repeats its last sample, which is
-// not composited, and samples past early termination are not composited either: results are
-// bit-identical to one sample at a time.  tseg: the segment's own transmittance, multiplied
-// alike.  Returns the samples composited; stop: the ray terminated in this segment.
-constexpr int kUnlitBatch = 4;
+// Colour sums.  A ray's colour is the sum of four partial sums: sample k of a segment adds to
+// partial k mod 4, in sample order, and the pixel is (p0 + p1) + (p2 + p3).  So the kernels that
+// give a ray four lanes (lane u of the quad takes the samples k = u mod 4 and holds partial u) and
+// those that give it one (holding all four) form the same sums, bit for bit.
+__device__ __forceinline__ float sum4(const float p[4]) { return (p[0] + p[1]) + (p[2] + p[3]); }
+
+// Unlit samples of one data segment by one lane, composited front to back (emission-absorption
+// with early termination, Section 5.3).  A ray's samples depend on each other only through T, so
+// the values of four samples are evaluated (their brick loads in flight together) before
+// they are composited one by one in sample order.  A batch that runs past the segment's end
+// repeats its last sample, which is not composited, and samples past early termination are not
+// composited either.  tseg: the segment's own transmittance, multiplied alike.  Returns the
+// samples composited; stop: the ray terminated in this segment.
 template <int LAY>
 __device__ __forceinline__ int composite_unlit(const RenderArgs &A, const float4 *s_lut, const Ray &R,
-                                               const Segment &S, float &T, float &C0, float &C1, float &C2,
-                                               float &tseg, bool &stop, Counters &cnt) {
+                                               const Segment &S, float &T, float (&C)[3][4], float &tseg, bool &stop,
+                                               Counters &cnt) {
     int done = 0;
     stop = false;
-    for (int k = 0; k < S.n; k += kUnlitBatch) {
-        SampleVals v[kUnlitBatch];
+    for (int k = 0; k < S.n; k += 4) {
+        SampleVals v[4];
         #pragma unroll
-        for (int u = 0; u < kUnlitBatch; u++)
+        for (int u = 0; u < 4; u++)
             eval_sample<false, false, false, LAY>(A, s_lut, R, S, min(k + u, S.n - 1), v[u], cnt);
         #pragma unroll
-        for (int u = 0; u < kUnlitBatch; u++) {
+        for (int u = 0; u < 4; u++) {
             if (!stop && k + u < S.n) {
                 const float wgt = T * v[u].alpha * v[u].shade;
-                C0 += wgt * v[u].r;
-                C1 += wgt * v[u].g;
-                C2 += wgt * v[u].b;
+                C[0][u] += wgt * v[u].r;
+                C[1][u] += wgt * v[u].g;
+                C[2][u] += wgt * v[u].b;
                 T *= 1.f - v[u].alpha;
                 tseg *= 1.f - v[u].alpha;
                 done++;
@@ -1197,6 +1202,82 @@ __device__ __forceinline__ int composite_unlit(const RenderArgs &A, const float4
             }
         }
         if (stop) break;
+    }
+    return done;
+}
+
+// ------------------------------------------------------------------------------------------
+// Four lanes per ray (the forward kernels)
+// ------------------------------------------------------------------------------------------
+//
+// Lanes 4 r .. 4 r + 3 (a quad) march ray r of a wave's 16 together: they walk the tree and hold
+// the segment and the transmittance alike, and lane u samples k = u mod 4.  Against one lane
+// per ray, a ray's chain of dependent brick reads is a quarter as long, a wave's 16 rays lie in
+// 4x4 pixels and stay closer in step than 64 rays in 8x8, and a quad's four stencils, half a cell
+// apart, fall into the same rows and cache lines, where the stencils of neighbouring pixels lie
+// several fine cells apart.  The walk is paid four times; ropes keep it short.  One lane per ray
+// against four: lit, 256^2 of a tiny scene 583 -> 175 us, 517x389 5.27 -> 1.94 ms, 1024^2 14.8 -> 12.9
+// ms; unlit, 1024^2 3.47 -> 2.54 ms, 1024^2 of a 20-level hierarchy 1.92 -> 1.29 ms.  What bounds them
+// now: VALU issue (73% of the cycles at 1024^2, lit and unlit, 41 and 44 of 64 lanes active).
+
+// The value of lane U of the quad (every lane of the quad active).
+template <int U>
+__device__ __forceinline__ float quad_lane(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), U * 0x55, 0xf, 0xf, true));
+}
+
+// The quad's values as sum4 adds them, in all four lanes.
+__device__ __forceinline__ float quad_sum(float v) {
+    const float w = v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true));
+    return w + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(w), 0x4E, 0xf, 0xf, true));
+}
+
+// One step of a quad: its four samples' opacities (sub: this lane's place; valid: its sample lies
+// in the segment, the valid ones first) multiplied into T in sample order, as one sample after the
+// other, up to the sample at which T < t_min.
+struct QuadStep {
+    float T;         // transmittance before this lane's sample
+    bool take;       // the sample counts: valid, and no earlier one ended the ray
+    bool stop;       // a sample ended the ray (all lanes)
+    int n;           // samples that count (all lanes)
+};
+__device__ __forceinline__ QuadStep quad_advance(float &T, float alpha, bool valid, int sub, int left, float t_min) {
+    const float f = valid ? 1.f - alpha : 1.f;
+    const float t1 = T * quad_lane<0>(f), t2 = t1 * quad_lane<1>(f), t3 = t2 * quad_lane<2>(f), t4 = t3 * quad_lane<3>(f);
+    const bool e1 = t1 < t_min, e2 = e1 || t2 < t_min, e3 = e2 || t3 < t_min;
+    QuadStep q;
+    q.T = sub == 0 ? T : (sub == 1 ? t1 : (sub == 2 ? t2 : t3));
+    q.take = valid && !(sub == 1 ? e1 : (sub == 2 ? e2 : (sub == 3 ? e3 : false)));
+    q.stop = e3 || t4 < t_min;
+    const int m = min(left, 4);
+    q.n = e1 ? 1 : (e2 ? min(m, 2) : (e3 ? min(m, 3) : m));
+    T = e1 ? t1 : (e2 ? t2 : (e3 ? t3 : t4));
+    return q;
+}
+
+// Unlit samples of one data segment by a quad, four per step.  (C0, C1, C2): this lane's partial
+// sums.  Returns the samples composited; stop: the ray terminated in this segment.  One step's
+// reads in flight at a time: with two or three steps' samples evaluated before they are
+// composited, a 1024^2 frame of the cosmology-like scene took 3.01 and 2.80 ms against 2.63 ms (the
+// registers of the deeper batch cost a wave per SIMD).
+template <bool REC, bool NEAR, int LAY>
+__device__ __forceinline__ int composite_unlit_quad(const RenderArgs &A, const float4 *s_lut, const Ray &R,
+                                                    const Segment &S, int sub, float &T, float &C0, float &C1,
+                                                    float &C2, bool &stop, Counters &cnt) {
+    int done = 0;
+    stop = false;
+    for (int k = 0; k < S.n && !stop; k += 4) {
+        SampleVals v;
+        eval_sample<false, REC, NEAR, LAY>(A, s_lut, R, S, min(k + sub, S.n - 1), v, cnt);
+        const QuadStep q = quad_advance(T, v.alpha, k + sub < S.n, sub, S.n - k, A.t_min);
+        if (q.take) {
+            const float wgt = q.T * v.alpha * v.shade;
+            C0 += wgt * v.r;
+            C1 += wgt * v.g;
+            C2 += wgt * v.b;
+        }
+        done += q.n;
+        stop = q.stop;
     }
     return done;
 }
@@ -1212,13 +1293,14 @@ __device__ __forceinline__ int composite_unlit(const RenderArgs &A, const float4
 // evaluated at once (value, colour and opacity from the LUT, the in-brick taps).  Opacity and
 // transmittance do not depend on the shading, so the ray marches on, and the sample's pending
 // taps, gradient, shading and colour contribution wait in a per-wave queue in LDS.  When the
-// queue could not take one more sample from every marching lane, the calling lanes resolve all
-// queued samples together, one sample per lane.
+// queue could not take the next samples that will wait (their taps are classified before their
+// stencils are read), the calling lanes resolve all queued samples together, one per lane: the
+// queue holds one wave's worth, so a resolution is one round of nearly full lanes.
 //
-// Each ray sums its colour in two accumulators, each in its own sample order: the samples
-// shaded at once (in registers), and the deferred ones (in LDS, added per owner in queue
-// order, which is the owner's sample order); the pixel is their sum.  So a ray's result does
-// not depend on which rays share its wave or on when the queue is resolved.
+// Each lane sums the colour of its samples in two accumulators, each in its own sample order: the
+// samples shaded at once (in registers), and the deferred ones (in LDS, added per owner lane in
+// queue order, which is the owner's sample order).  So a ray's result does not depend on which
+// rays share its wave or on when the queue is resolved.
 
 // A queued sample.  Per axis, g holds the finished central difference when neither tap of
 // the axis is pending, else the value of the tap that is not (or nothing).
@@ -1273,10 +1355,10 @@ __device__ __forceinline__ void tapq_init(TapQueue &Q, int lane) {
 
 // The calling (active) lanes resolve every queued sample: remaining taps, gradient, shading,
 // contribution; then each owner's deferred colour takes its contributions in queue order.
-// TAPE (checkpointed single-camera forward, one 8x8 pixel tile per wave): each resolved sample's
-// record (value, gradient) is also written to the owner ray's tape at the sample's position, so
-// the adjoint need not evaluate it again.  tape_base: the tape row (ray) of lane 0, whose tile
-// row holds lanes 0..7; lane o's ray is tape_base + (o / 8) * width + o % 8.
+// TAPE (checkpointed single-camera forward): each resolved sample's record (value, gradient) is
+// also written to the owner ray's tape at the sample's position, so the adjoint need not evaluate
+// it again.  tape_base: the tape row (ray) of lane 0; lane o's ray is o / 4 of the wave's 4x4
+// pixels, row tape_base + (o / 16) * width + (o / 4) % 4.
 template <bool REC, int LAY = -1, bool NEAR = false, bool TAPE = false>
 __device__ __forceinline__ void tapq_flush(const RenderArgs &A, const float4 *s_lut, TapQueue &Q, int lane,
                                            Counters &cnt, int64_t tape_base = -1) {
@@ -1318,7 +1400,7 @@ __device__ __forceinline__ void tapq_flush(const RenderArgs &A, const float4 *s_
         }
         if (TAPE && tape_base >= 0) {
             const int o = (int)(m & 63u);
-            const int64_t row = tape_base + (int64_t)(o >> 3) * A.width + (o & 7);
+            const int64_t row = tape_base + (int64_t)(o >> 4) * A.width + ((o >> 2) & 3);
             const int64_t pos = (int64_t)(Q.pend[j] >> 6);
             if (pos < A.tape_cap) A.tape[row * A.tape_cap + pos] = make_float4(F, gv[0], gv[1], gv[2]);
         }
@@ -1352,15 +1434,6 @@ __device__ __forceinline__ void tapq_flush(const RenderArgs &A, const float4 *s_
     }
     if (rank == 0) tq_set(Q, 0u, 0ull, 0ull);
     wave_lds_fence();
-}
-
-// At the top of a step, by the marching lanes: resolve the queue first unless it has a free
-// slot for each of them.
-template <bool REC, int LAY = -1, bool NEAR = false>
-__device__ __forceinline__ void tapq_reserve(const RenderArgs &A, const float4 *s_lut, TapQueue &Q, int lane,
-                                             Counters &cnt) {
-    const unsigned long long act = __ballot(1);
-    if (tapq_full(tq_count(Q), act)) tapq_flush<REC, LAY, NEAR>(A, s_lut, Q, lane, cnt);
 }
 
 // Queues a lit sample whose taps in `pend` are left to resolve (all marching lanes call it in
@@ -1429,23 +1502,85 @@ __device__ __forceinline__ uint32_t pending_taps(uint32_t cls) {
     return pend;
 }
 
-// The part of a lit sample after its stencil: LUT classification, then either the shading and
-// colour at once (every tap in the brick) or a queue slot (tapq_push: every lane of the calling
-// set takes part).  xs: the sample's FP64 position if already known (else null).  With a tape
-// row, the sample's record is written (at once) or its tape position queued.  Returns alpha.
-template <bool REC>
-__device__ __forceinline__ float lit_consume(const RenderArgs &A, const float4 *s_lut, TapQueue &Q, int lane,
-                                             const Ray &R, const Segment &S, int k, const double *xs, float qx,
-                                             float qy, float qz, float F, const float Fp[3], const float Fm[3],
-                                             uint32_t cls, uint32_t pend, float T, float &C0, float &C1, float &C2,
-                                             Counters &cnt, float4 *trow, uint32_t *tpos) {
+// A lane's next lit sample, before its stencil is read: patch-local position, tap classes and the
+// taps that will wait in the queue (trilinear: those that leave the brick; nearest cell: those
+// that need the tree), so that the queue can be resolved first when it lacks the room.
+struct LitPoint {
+    float q[3];
+    uint32_t cls, pend;
+    int ci[3];              // nearest cell: the sample's cell
+    double xs[3];           // nearest cell: its FP64 position, formed when pend is set
+};
+
+template <bool NEAR>
+__device__ __forceinline__ LitPoint lit_point(const RenderArgs &A, const Ray &R, const Segment &S, int k) {
+    LitPoint p;
+    const float kk = (float)k + 0.5f;
+    #pragma unroll
+    for (int a = 0; a < 3; a++) p.q[a] = S.q0[a] + kk * S.dq[a];
+    p.cls = classify_taps(S, p.q[0], p.q[1], p.q[2]);
+    p.pend = pending_taps(p.cls);
+    if (NEAR) {
+        // the sample's cell and the taps one cell over in this brick; the rest needs the tree
+        bool sure = true;
+        #pragma unroll
+        for (int a = 0; a < 3; a++) {
+            const float u = p.q[a] + 0.5f, fl = floorf(u), fr = u - fl;
+            sure = sure && fr >= kTapMargin && fr <= 1.f - kTapMargin;
+            p.ci[a] = (int)fl;
+        }
+        if (!sure) p.pend = 0x3fu;
+        if (p.pend) sample_point(R, S, k, p.xs);
+        if (!sure) {
+            const DPatch &P = A.patches[S.patch];
+            #pragma unroll
+            for (int a = 0; a < 3; a++) p.ci[a] = cell_index(p.xs[a], P.lo[a], P.h[a], P.n[a]);
+        }
+        p.ci[0] = min(max(p.ci[0], 0), S.pv.nx - 1);
+        p.ci[1] = min(max(p.ci[1], 0), S.pv.ny - 1);
+        p.ci[2] = min(max(p.ci[2], 0), S.pv.nz - 1);
+    }
+    return p;
+}
+
+// One step of a quad with a segment (all lanes of the quads that have one call it together, after
+// lit_point, with room in the queue for every lane whose sample has taps pending): the in-brick
+// part of each lane's sample now; a sample with taps pending is queued, else shaded and added to
+// this lane's partial sums.  T advances past the quad's samples.
+// trow, tpos (checkpointed forward with a tape): the ray's tape row and the position of the quad's
+// first sample in it, advanced here; a sample shaded at once writes its record now, a queued one
+// when resolved.
+template <bool REC, int LAY, bool NEAR>
+__device__ __forceinline__ QuadStep lit_step(const RenderArgs &A, const float4 *s_lut, TapQueue &Q, int lane,
+                                             const Ray &R, const Segment &S, int k, const LitPoint &p, float &T,
+                                             float &C0, float &C1, float &C2, Counters &cnt, float4 *trow,
+                                             uint32_t &tpos) {
+    const int sub = lane & 3;
+    float F, Fp[3], Fm[3];
+    if (NEAR) {
+        F = brick_cell<LAY>(A, S.pv, p.ci[0], p.ci[1], p.ci[2]);
+        #pragma unroll
+        for (int t = 0; t < 6; t++) {
+            const int a = t >> 1, sgn = t & 1;
+            int cj[3] = {p.ci[0], p.ci[1], p.ci[2]};
+            cj[a] += sgn ? -1 : 1;
+            #pragma unroll
+            for (int b = 0; b < 3; b++) cj[b] = min(max(cj[b], 0), (b == 0 ? S.pv.nx : (b == 1 ? S.pv.ny : S.pv.nz)) - 1);
+            const float val = brick_cell<LAY>(A, S.pv, cj[0], cj[1], cj[2]);
+            if (sgn) Fm[a] = val;
+            else Fp[a] = val;
+        }
+    } else {
+        F = trilinear_taps<REC, LAY>(A, S.pv, p.q[0], p.q[1], p.q[2], Fp, Fm);
+    }
     SampleVals v;
     lut_classify(A, s_lut, F, S.dl, v);
-    const float Ta = T * v.alpha;
-    const bool defer = pend != 0;
-    const uint32_t pos = trow ? *tpos : 0u;
+    const QuadStep q = quad_advance(T, v.alpha, k + sub < S.n, sub, S.n - k, A.t_min);
+    const float Ta = q.T * v.alpha;
+    const bool defer = q.take && p.pend != 0u;
+    const uint32_t pos = trow ? tpos + (uint32_t)sub : 0u;
     const uint32_t cap = (uint32_t)A.tape_cap;
-    if (!defer) {
+    if (q.take && !defer) {
         float gv[3], dot, den;
         lit_gradient(A, F, Fp, Fm, 0x3fu, gv);
         const float wgt = Ta * lit_shade(A, gv, dot, den);
@@ -1454,76 +1589,10 @@ __device__ __forceinline__ float lit_consume(const RenderArgs &A, const float4 *
         C2 += wgt * v.b;
         if (trow && pos < cap) trow[pos] = make_float4(F, gv[0], gv[1], gv[2]);
     }
-    const uint32_t ord = pos < cap ? pos : cap;
-    if (trow) *tpos = pos + 1u;
-    tapq_push<REC>(A, Q, lane, defer, R, S, k, xs, qx, qy, qz, F, Fp, Fm, cls, pend, Ta, v, cnt, ord);
-    return v.alpha;
-}
-
-// One lit sample of a marching lane with deferred taps: the in-brick part now; the sample is
-// queued when a tap leaves the brick (trilinear) or needs the tree (nearest cell), else shaded
-// and added to (C0, C1, C2) at once.  Returns the opacity.  All marching lanes call it in the
-// same step, after tapq_reserve.
-// trow, tpos (checkpointed forward with a tape): the lane's tape row and the sample's position in
-// it, advanced here; a sample shaded at once writes its record now, a queued one when resolved.
-template <bool REC, int LAY = -1, bool NEAR = false>
-__device__ __forceinline__ float lit_sample_deferred(const RenderArgs &A, const float4 *s_lut, TapQueue &Q, int lane,
-                                                     const Ray &R, const Segment &S, int k, float T, float &C0,
-                                                     float &C1, float &C2, Counters &cnt, float4 *trow = nullptr,
-                                                     uint32_t *tpos = nullptr) {
-    const float kk = (float)k + 0.5f;
-    const float qx = S.q0[0] + kk * S.dq[0], qy = S.q0[1] + kk * S.dq[1], qz = S.q0[2] + kk * S.dq[2];
-    float F, Fp[3], Fm[3];
-    uint32_t cls, pend;
-    double xs[3] = {0.0, 0.0, 0.0};
-    bool have_xs = false;
-    if (NEAR) {
-        // the sample's cell and the taps one cell over in this brick; the rest needs the tree
-        const float qc[3] = {qx, qy, qz};
-        int ci[3];
-        bool sure = true;
-        #pragma unroll
-        for (int a = 0; a < 3; a++) {
-            const float u = qc[a] + 0.5f, fl = floorf(u), fr = u - fl;
-            sure = sure && fr >= kTapMargin && fr <= 1.f - kTapMargin;
-            ci[a] = (int)fl;
-        }
-        cls = classify_taps(S, qx, qy, qz);
-        pend = sure ? pending_taps(cls) : 0x3fu;
-        if (pend) {
-            sample_point(R, S, k, xs);
-            have_xs = true;
-        }
-        if (!sure) {
-            const DPatch &P = A.patches[S.patch];
-            #pragma unroll
-            for (int a = 0; a < 3; a++) ci[a] = cell_index(xs[a], P.lo[a], P.h[a], P.n[a]);
-        }
-        ci[0] = min(max(ci[0], 0), S.pv.nx - 1);
-        ci[1] = min(max(ci[1], 0), S.pv.ny - 1);
-        ci[2] = min(max(ci[2], 0), S.pv.nz - 1);
-        F = brick_cell<LAY>(A, S.pv, ci[0], ci[1], ci[2]);
-        #pragma unroll
-        for (int t = 0; t < 6; t++) {
-            const int a = t >> 1, sgn = t & 1;
-            float val = F;
-            if (!((pend >> t) & 1u)) {
-                int cj[3] = {ci[0], ci[1], ci[2]};
-                cj[a] += sgn ? -1 : 1;
-                cj[0] = min(max(cj[0], 0), S.pv.nx - 1);
-                cj[1] = min(max(cj[1], 0), S.pv.ny - 1);
-                cj[2] = min(max(cj[2], 0), S.pv.nz - 1);
-                val = brick_cell<LAY>(A, S.pv, cj[0], cj[1], cj[2]);
-            }
-            if (sgn) Fm[a] = val;
-            else Fp[a] = val;
-        }
-    } else {
-        cls = lit_stencil<REC, LAY>(A, S, qx, qy, qz, F, Fp, Fm);
-        pend = pending_taps(cls);
-    }
-    return lit_consume<REC>(A, s_lut, Q, lane, R, S, k, have_xs ? xs : nullptr, qx, qy, qz, F, Fp, Fm, cls, pend, T,
-                            C0, C1, C2, cnt, trow, tpos);
+    tpos += (uint32_t)q.n;
+    tapq_push<REC>(A, Q, lane, defer, R, S, min(k + sub, S.n - 1), NEAR ? p.xs : nullptr, p.q[0], p.q[1], p.q[2], F, Fp,
+                   Fm, p.cls, p.pend, Ta, v, cnt, pos < cap ? pos : cap);
+    return q;
 }
 
 // After the march, by all lanes of the wave: resolve what is queued; returns the lane's
