@@ -1066,12 +1066,17 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
         // scheduled: one-dimensional, four blocks per tile, ranks dealt to the 8 XCDs in turn
         const dim3 g(sched ? 32 * side * side * ((nst + 7) / 8) : gx, sched ? 1 : n), b(64);
         if (A.nearest) {
-            if (A.lighting) {
-                if (rec) hipLaunchKernelGGL((render_fwd<true, true, true, -1>), g, b, 0, s, A, G);
-                else hipLaunchKernelGGL((render_fwd<true, false, true, -1>), g, b, 0, s, A, G);
+            if (rec) {
+                if (A.lighting) hipLaunchKernelGGL((render_fwd<true, true, true, -1>), g, b, 0, s, A, G);
+                else hipLaunchKernelGGL((render_fwd<false, true, true, -1>), g, b, 0, s, A, G);
+            } else if (A.lighting) {
+                if (A.layout == 0) hipLaunchKernelGGL((render_fwd<true, false, true, 0>), g, b, 0, s, A, G);
+                else if (A.layout == 1) hipLaunchKernelGGL((render_fwd<true, false, true, 1>), g, b, 0, s, A, G);
+                else hipLaunchKernelGGL((render_fwd<true, false, true, 2>), g, b, 0, s, A, G);
             } else {
-                if (rec) hipLaunchKernelGGL((render_fwd<false, true, true, -1>), g, b, 0, s, A, G);
-                else hipLaunchKernelGGL((render_fwd<false, false, true, -1>), g, b, 0, s, A, G);
+                if (A.layout == 0) hipLaunchKernelGGL((render_fwd<false, false, true, 0>), g, b, 0, s, A, G);
+                else if (A.layout == 1) hipLaunchKernelGGL((render_fwd<false, false, true, 1>), g, b, 0, s, A, G);
+                else hipLaunchKernelGGL((render_fwd<false, false, true, 2>), g, b, 0, s, A, G);
             }
         } else if (rec && !(A.ckpt && !A.trace && !A.trace_n && !A.nsamp && !A.stats && !A.touch && !A.touch_meta)) {
             if (A.lighting) hipLaunchKernelGGL((render_fwd<true, true, false, -1>), g, b, 0, s, A, G);
