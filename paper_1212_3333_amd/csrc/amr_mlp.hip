@@ -3,7 +3,7 @@
 //
 // GEMMs run on the matrix cores, fp16 operands and fp32 accumulation: the 16x16x16 shape for
 // layer 1 (K = 16, the 12 inputs padded), gfx950's 16x16x32 shape for every K = 64 product
-// (operand layouts in amr_mlp.h).  A wave handles a 64-row tile.
+// (operand layouts in amr_mlp.h).
 // Parameters are fp32 masters packed as W1 [12][64], b1 [64], W2 [64][64], b2 [64],
 // W3 [64][2], b3 [2] (input-major); the fp16 operands are rounded from them.
 #include <hip/hip_runtime.h>
@@ -35,212 +35,395 @@ __device__ inline void stage_weights(const float *W, MlpLds &s) {
     if (threadIdx.x < 2) s.b3[threadIdx.x] = W[kOffB3 + threadIdx.x];
 }
 
-// Forward of one 64-row tile whose fp16 inputs sit in x16 ([64][16], row-major, zero padded).
-// Writes post-ReLU activations to h1/h2 (fp16, [64][64]) and returns the pre-sigmoid logits of
-// rows 4 (l/16) + j of row tile rt in z3[rt][j] for column l % 16 (columns 0, 1 are valid).
-__device__ inline void mlp_tile_forward(const MlpLds &s, const _Float16 *x16, _Float16 *h1, _Float16 *h2,
-                                        float z3[4][4], float *h1f, float *h2f) {
-    const int lane = threadIdx.x & 63;
-    const int lr = lane & 15, lq = lane >> 4;
-    // layer 1: [64 x 16] . [16 x 64]
-    for (int rt = 0; rt < 4; rt++) {
-        half4 a = *reinterpret_cast<const half4 *>(x16 + (rt * 16 + lr) * 16 + 4 * lq);
-        for (int ct = 0; ct < 4; ct++) {
-            half4 b = *reinterpret_cast<const half4 *>(s.w1t + (ct * 16 + lr) * 16 + 4 * lq);
-            float4v acc = {0.f, 0.f, 0.f, 0.f};
-            acc = mfma_k16(a, b, acc);
-            for (int j = 0; j < 4; j++) {
-                int row = rt * 16 + 4 * lq + j, col = ct * 16 + lr;
-                float hv = fmaxf(acc[j] + s.b1[col], 0.f);
-                h1[row * 64 + col] = (_Float16)hv;
-                if (h1f) h1f[row * 64 + col] = hv;
-            }
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-    // layer 2: [64 x 64] . [64 x 64]
-    for (int rt = 0; rt < 4; rt++)
-        for (int ct = 0; ct < 4; ct++) {
-            float4v acc = {0.f, 0.f, 0.f, 0.f};
-            for (int ks = 0; ks < 2; ks++) {
-                half8 a = *reinterpret_cast<const half8 *>(h1 + (rt * 16 + lr) * 64 + ks * 32 + 8 * lq);
-                half8 b = *reinterpret_cast<const half8 *>(s.w2t + (ct * 16 + lr) * 64 + ks * 32 + 8 * lq);
-                acc = mfma_k32(a, b, acc);
-            }
-            for (int j = 0; j < 4; j++) {
-                int row = rt * 16 + 4 * lq + j, col = ct * 16 + lr;
-                float hv = fmaxf(acc[j] + s.b2[col], 0.f);
-                h2[row * 64 + col] = (_Float16)hv;
-                if (h2f) h2f[row * 64 + col] = hv;
-            }
-        }
-    __builtin_amdgcn_wave_barrier();
-    // layer 3: [64 x 64] . [64 x 16] (two valid columns)
-    for (int rt = 0; rt < 4; rt++) {
-        float4v acc = {0.f, 0.f, 0.f, 0.f};
-        for (int ks = 0; ks < 2; ks++) {
-            half8 a = *reinterpret_cast<const half8 *>(h2 + (rt * 16 + lr) * 64 + ks * 32 + 8 * lq);
-            half8 b = *reinterpret_cast<const half8 *>(s.w3t + lr * 64 + ks * 32 + 8 * lq);
-            acc = mfma_k32(a, b, acc);
-        }
-        for (int j = 0; j < 4; j++) z3[rt][j] = acc[j] + (lr < kOut ? s.b3[lr] : 0.f);
-    }
-}
-
 __device__ inline float sigmoidf_(float z) { return 1.f / (1.f + __expf(-z)); }
 
-__global__ __launch_bounds__(256) void mlp_forward_kernel(const float *X, const float *W, float *Y, float *H,
-                                                         int64_t n) {
-    __shared__ MlpLds s;
-    __shared__ __attribute__((aligned(16))) _Float16 xs[4][64 * 16];
-    __shared__ __attribute__((aligned(16))) _Float16 hs1[4][64 * 64], hs2[4][64 * 64];
-    stage_weights(W, s);
+// The training kernels: 512 threads, eight waves, each taking tiles of 32 rows.  At 65536 rows that
+// is one tile per wave on 256 blocks, one block per CU: both kernels are chains (weights, inputs,
+// layers, results), so a tile is small and a CU holds eight of them to overlap.
+constexpr int kTile = 32;
+constexpr int kWaves = 8;
+// LDS rows are padded to a multiple of 16 bytes that is not one of 128: the matrix-core operand
+// reads take 16 bytes from each of 16 rows, which at 128 bytes all fall into the same banks.
+constexpr int kRow = 72;              // rows of 64 units
+constexpr int kCol = 40;              // rows of kTile tile rows
+
+struct FwdLds {
+    _Float16 w1t[64 * 16];           // [u][i], i >= 12 zero
+    _Float16 w2t[64 * kRow];         // [v][u]
+    _Float16 w3t[16 * kRow];         // [j][u], j >= 2 zero
+    float b1[64], b2[64], b3[4];
+    _Float16 x[kWaves][kTile * 16];  // per wave: the tile's inputs, zero padded
+    _Float16 h[kWaves][kTile * kRow];  // per wave: layer 1's activations, then layer 2's
+};
+
+// Forward.  Its floor is the activations it writes for the backward pass (512 bytes a row, 33.5 MB at
+// 65536 rows, 6.5 us at the copy rate); they leave as whole rows, 16 bytes per lane.  The layers
+// share one activation buffer per wave: a layer's operand rows are in registers before its
+// results overwrite them.  65536 rows: 14 us (four waves a block on 64-row tiles: 22 us).
+__global__ __launch_bounds__(64 * kWaves) void mlp_forward_kernel(const float *X, const float *W, float *Y, float *H,
+                                                                 int64_t n) {
+    __shared__ __attribute__((aligned(16))) FwdLds s;
+    const int tid = threadIdx.x;
+    {   // every load of the weights in flight before the first is used
+        float w1[2], w2[8], w3[2], bias = 0.f;
+        #pragma unroll
+        for (int i = 0; i < 2; i++) {
+            const int e = tid + 512 * i;
+            w1[i] = (e >> 6) < kIn ? W[kOffW1 + e] : 0.f;                   // W1[k][u], k >= 12 zero
+            w3[i] = (e & 15) < kOut ? W[kOffW3 + (e >> 4) * kOut + (e & 15)] : 0.f;
+        }
+        #pragma unroll
+        for (int i = 0; i < 8; i++) w2[i] = W[kOffW2 + tid + 512 * i];
+        if (tid < 64) bias = W[kOffB1 + tid];
+        else if (tid < 128) bias = W[kOffB2 + tid - 64];
+        else if (tid < 128 + kOut) bias = W[kOffB3 + tid - 128];
+        #pragma unroll
+        for (int i = 0; i < 2; i++) {
+            const int e = tid + 512 * i;
+            s.w1t[(e & 63) * 16 + (e >> 6)] = (_Float16)w1[i];
+            s.w3t[(e & 15) * kRow + (e >> 4)] = (_Float16)w3[i];
+        }
+        #pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const int e = tid + 512 * i;
+            s.w2t[(e & 63) * kRow + (e >> 6)] = (_Float16)w2[i];
+        }
+        if (tid < 64) s.b1[tid] = bias;
+        else if (tid < 128) s.b2[tid - 64] = bias;
+        else if (tid < 128 + kOut) s.b3[tid - 128] = bias;
+    }
     __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = tid >> 6, lane = tid & 63;
     const int lr = lane & 15, lq = lane >> 4;
-    const int64_t ntiles = (n + 63) / 64;
-    for (int64_t t = (int64_t)blockIdx.x * 4 + wave; t < ntiles; t += (int64_t)gridDim.x * 4) {
-        const int64_t row0 = t * 64;
-        for (int i = lane; i < 64 * 16; i += 64) {
-            int r = i / 16, k = i % 16;
-            int64_t g = row0 + r;
-            xs[wave][i] = (_Float16)(g < n && k < kIn ? X[g * kIn + k] : 0.f);
+    _Float16 *x = s.x[wave], *h = s.h[wave];
+    const bool wide = (reinterpret_cast<uintptr_t>(H) & 15u) == 0;
+    const int64_t ntiles = (n + kTile - 1) / kTile;
+    for (int64_t t = (int64_t)blockIdx.x * kWaves + wave; t < ntiles; t += (int64_t)gridDim.x * kWaves) {
+        const int64_t row0 = t * kTile;
+        #pragma unroll
+        for (int i = 0; i < kTile * kIn / 64; i++) {     // rows of 12 values, contiguous
+            const int e = i * 64 + lane;
+            const int64_t g = row0 * kIn + e;
+            x[(e / kIn) * 16 + e % kIn] = (_Float16)(g < n * kIn ? X[g] : 0.f);
+        }
+        if (lane < kTile) *reinterpret_cast<half4 *>(x + lane * 16 + 12) = half4{0, 0, 0, 0};
+        __builtin_amdgcn_wave_barrier();
+        // activations of one layer to H (part 0: layer 1, 1: layer 2), whole rows
+        auto keep = [&](int part) {
+            if (!H) return;
+            #pragma unroll
+            for (int i = 0; i < kTile / 4; i++) {
+                const int row = i * 4 + lq;
+                const half4 v = *reinterpret_cast<const half4 *>(h + row * kRow + 4 * lr);
+                float *out = H + (row0 + row) * 128 + part * 64 + 4 * lr;
+                if (row0 + row >= n) continue;
+                if (wide) {
+                    *reinterpret_cast<float4 *>(out) = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+                } else {
+                    #pragma unroll
+                    for (int j = 0; j < 4; j++) out[j] = (float)v[j];
+                }
+            }
+        };
+        // layer 1: [32 x 16] . [16 x 64]
+        #pragma unroll
+        for (int rt = 0; rt < kTile / 16; rt++) {
+            const half4 a = *reinterpret_cast<const half4 *>(x + (rt * 16 + lr) * 16 + 4 * lq);
+            #pragma unroll
+            for (int ct = 0; ct < 4; ct++) {
+                const half4 b = *reinterpret_cast<const half4 *>(s.w1t + (ct * 16 + lr) * 16 + 4 * lq);
+                float4v acc = {0.f, 0.f, 0.f, 0.f};
+                acc = mfma_k16(a, b, acc);
+                #pragma unroll
+                for (int j = 0; j < 4; j++)
+                    h[(rt * 16 + 4 * lq + j) * kRow + ct * 16 + lr] = (_Float16)fmaxf(acc[j] + s.b1[ct * 16 + lr], 0.f);
+            }
         }
         __builtin_amdgcn_wave_barrier();
-        float z3[4][4];
-        float *h1f = nullptr, *h2f = nullptr;
-        mlp_tile_forward(s, xs[wave], hs1[wave], hs2[wave], z3, h1f, h2f);
-        for (int rt = 0; rt < 4; rt++)
-            for (int j = 0; j < 4; j++) {
-                int64_t g = row0 + rt * 16 + 4 * lq + j;
-                if (lr < kOut && g < n) Y[g * 2 + lr] = sigmoidf_(z3[rt][j]);
+        keep(0);
+        // layer 2: [32 x 64] . [64 x 64]
+        half8 a2[kTile / 16][2];
+        #pragma unroll
+        for (int rt = 0; rt < kTile / 16; rt++)
+            #pragma unroll
+            for (int ks = 0; ks < 2; ks++)
+                a2[rt][ks] = *reinterpret_cast<const half8 *>(h + (rt * 16 + lr) * kRow + ks * 32 + 8 * lq);
+        __builtin_amdgcn_wave_barrier();
+        #pragma unroll
+        for (int ct = 0; ct < 4; ct++) {
+            half8 b[2];
+            #pragma unroll
+            for (int ks = 0; ks < 2; ks++)
+                b[ks] = *reinterpret_cast<const half8 *>(s.w2t + (ct * 16 + lr) * kRow + ks * 32 + 8 * lq);
+            #pragma unroll
+            for (int rt = 0; rt < kTile / 16; rt++) {
+                float4v acc = {0.f, 0.f, 0.f, 0.f};
+                acc = mfma_k32(a2[rt][0], b[0], acc);
+                acc = mfma_k32(a2[rt][1], b[1], acc);
+                #pragma unroll
+                for (int j = 0; j < 4; j++)
+                    h[(rt * 16 + 4 * lq + j) * kRow + ct * 16 + lr] = (_Float16)fmaxf(acc[j] + s.b2[ct * 16 + lr], 0.f);
             }
-        if (H) {   // activations for the backward pass: [n][128] = h1 (64) then h2 (64), fp32
-            __builtin_amdgcn_wave_barrier();
-            for (int i = lane; i < 64 * 64; i += 64) {
-                int r = i / 64, c = i % 64;
-                int64_t g = row0 + r;
-                if (g < n) {
-                    H[g * 128 + c] = (float)hs1[wave][i];
-                    H[g * 128 + 64 + c] = (float)hs2[wave][i];
-                }
+        }
+        __builtin_amdgcn_wave_barrier();
+        keep(1);
+        // layer 3: [32 x 64] . [64 x 16] (two valid columns)
+        half8 b3[2];
+        #pragma unroll
+        for (int ks = 0; ks < 2; ks++) b3[ks] = *reinterpret_cast<const half8 *>(s.w3t + lr * kRow + ks * 32 + 8 * lq);
+        #pragma unroll
+        for (int rt = 0; rt < kTile / 16; rt++) {
+            float4v acc = {0.f, 0.f, 0.f, 0.f};
+            #pragma unroll
+            for (int ks = 0; ks < 2; ks++)
+                acc = mfma_k32(*reinterpret_cast<const half8 *>(h + (rt * 16 + lr) * kRow + ks * 32 + 8 * lq), b3[ks], acc);
+            #pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const int64_t g = row0 + rt * 16 + 4 * lq + j;
+                if (lr < kOut && g < n) Y[g * 2 + lr] = sigmoidf_(acc[j] + s.b3[lr]);
             }
         }
         __builtin_amdgcn_wave_barrier();
     }
 }
+
+constexpr int kSums = 88;            // sums that a lane holds: dW2 64, dW1 16, db2, dW3 2, db3 2, loss, 2 unused
+
+struct BwdTile {                     // per wave
+    _Float16 h1t[64 * kCol];         // [u][row]: layer 1's activations
+    _Float16 dzt[64 * kCol];         // [v][row]: dZ2, then [u][row]: dZ1
+    _Float16 dz2[kTile * kRow];      // [row][v]: dZ2
+    float2 dz3[kTile];               // the rows' output derivatives
+};
+struct BwdLds {
+    _Float16 w2[64 * kRow];          // [u][v]
+    union {
+        BwdTile tile[kWaves];
+        float4 sums[kWaves / 2][kSums / 4][64];   // after the last tile: the upper waves' sums, per lane
+    };
+};
 
 // Backward of the mean pinball loss.  dZ values are kept unscaled (no 1/n) through the fp16
 // products and scaled at the end, so they stay in fp16's normal range.
-__global__ __launch_bounds__(256) void mlp_backward_kernel(const float *X, const float *W, const float *H,
-                                                          const float *Y, const float *Tg, int64_t n, float q_lo,
-                                                          float q_hi, float *dW, float *loss) {
-    __shared__ MlpLds s;
-    __shared__ __attribute__((aligned(16))) _Float16 hs1[4][64 * 64], dz2s[4][64 * 64];
-    __shared__ float acc_s[kParams];
-    stage_weights(W, s);
-    for (int i = threadIdx.x; i < kParams; i += blockDim.x) acc_s[i] = 0.f;
-    __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+// Of a tile: the rows' output derivatives, one per lane; then, lane = hidden unit, dZ2 of the rows,
+// H read as whole rows, all of them in flight together; the products on the matrix cores from
+// operands laid out so that each is read as 16 bytes per lane (dZ2 by row and by unit, H1 by unit).
+// dW1 and db1 are one product too: the inputs, which are fp32, enter as two fp16 terms (their sum
+// holds 22 bits), a row of ones gives db1.  65536 rows: 20 us, of which a tile takes 3.5 and the blocks'
+// 5058 atomic sums 0.06 each, hence the grid of 128 (256 blocks 25 us, 64 blocks 25 us); with
+// serial row loops, operands gathered by halves and sums in LDS by atomics it took 94 us.
+constexpr int kBwdBlocks = 128;
+
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void mlp_backward_kernel(const float *X, const float *W, const float *H,
+                                                                  const float *Y, const float *Tg, int64_t n,
+                                                                  float q_lo, float q_hi, float *dW, float *loss) {
+    __shared__ __attribute__((aligned(16))) BwdLds s;
+    const int tid = threadIdx.x;
+    const int wave = tid >> 6, lane = tid & 63;
     const int lr = lane & 15, lq = lane >> 4;
-    const int64_t ntiles = (n + 63) / 64;
-    // per-lane fp32 accumulators: dW2 tiles (MFMA D layout) and the VALU parts
-    float4v dw2[4][4];
-    for (int a = 0; a < 4; a++)
-        for (int b = 0; b < 4; b++) dw2[a][b] = float4v{0.f, 0.f, 0.f, 0.f};
-    float dw1[kIn], db1 = 0.f, db2 = 0.f, dw3[2] = {0.f, 0.f}, db3[2] = {0.f, 0.f}, lsum = 0.f;
-    for (int k = 0; k < kIn; k++) dw1[k] = 0.f;
-    const float *W3 = W + kOffW3;
-    const float w3u0 = W3[lane * 2], w3u1 = W3[lane * 2 + 1];   // lane = hidden unit u
-    for (int64_t t = (int64_t)blockIdx.x * 4 + wave; t < ntiles; t += (int64_t)gridDim.x * 4) {
-        const int64_t row0 = t * 64;
-        // lane = hidden unit: dZ2 column for all 64 rows; dW3 and db3 on the VALU
-        for (int r = 0; r < 64; r++) {
-            int64_t g = row0 + r;
-            float dz2 = 0.f;
+    {
+        float w2[8];
+        #pragma unroll
+        for (int i = 0; i < 8; i++) w2[i] = W[kOffW2 + tid + 512 * i];
+        #pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const int e = tid + 512 * i;
+            s.w2[(e >> 6) * kRow + (e & 63)] = (_Float16)w2[i];
+        }
+    }
+    const float w3u0 = W[kOffW3 + lane * 2], w3u1 = W[kOffW3 + lane * 2 + 1];   // lane = hidden unit u
+    __syncthreads();
+    BwdTile &b = s.tile[wave];
+    const int64_t ntiles = (n + kTile - 1) / kTile;
+    // per-lane fp32 accumulators: dW2 and dW1 tiles (MFMA D layout) and the VALU parts
+    float4v dw2[4][4], dw1[4];
+    #pragma unroll
+    for (int i = 0; i < 4; i++) {
+        dw1[i] = float4v{0.f, 0.f, 0.f, 0.f};
+        #pragma unroll
+        for (int j = 0; j < 4; j++) dw2[i][j] = float4v{0.f, 0.f, 0.f, 0.f};
+    }
+    float db2 = 0.f, dw3[2] = {0.f, 0.f}, db3[2] = {0.f, 0.f}, lsum = 0.f;
+    for (int64_t t = (int64_t)blockIdx.x * kWaves + wave; t < ntiles; t += (int64_t)gridDim.x * kWaves) {
+        const int64_t row0 = t * kTile;
+        float h1[kTile], h2[kTile], x[8];
+        #pragma unroll
+        for (int r = 0; r < kTile; r++) {
+            const int64_t g = row0 + r < n ? row0 + r : n - 1;
+            h1[r] = H[g * 128 + lane];
+            h2[r] = H[g * 128 + 64 + lane];
+        }
+        // dW1's operand rows: input lr (row 12: ones) of tile rows 8 lq .. 8 lq + 7
+        #pragma unroll
+        for (int j = 0; j < 8; j++) {
+            const int64_t g = row0 + 8 * lq + j;
+            x[j] = lr < kIn && g < n ? X[g * kIn + lr] : (lr == kIn ? 1.f : 0.f);
+        }
+        // lane = row: the output derivatives (zero past the last row, which keeps such a row out of
+        // every product below) and the loss
+        if (lane < kTile) {
+            const int64_t g = row0 + lane;
+            float2 d = make_float2(0.f, 0.f);
             if (g < n) {
-                float y0 = Y[g * 2], y1 = Y[g * 2 + 1], tg = Tg[g];
-                float d0 = tg > y0 ? -q_lo : 1.f - q_lo;
-                float d1 = tg > y1 ? -q_hi : 1.f - q_hi;
-                if (lane == 0) {
-                    float r0 = tg - y0, r1 = tg - y1;
-                    lsum += fmaxf(q_lo * r0, (q_lo - 1.f) * r0) + fmaxf(q_hi * r1, (q_hi - 1.f) * r1);
-                }
-                float dz30 = d0 * y0 * (1.f - y0), dz31 = d1 * y1 * (1.f - y1);
-                float h2 = H[g * 128 + 64 + lane], h1 = H[g * 128 + lane];
-                dw3[0] += h2 * dz30;
-                dw3[1] += h2 * dz31;
-                if (lane < 2) db3[lane] += lane == 0 ? dz30 : dz31;
-                dz2 = h2 > 0.f ? dz30 * w3u0 + dz31 * w3u1 : 0.f;
-                db2 += dz2;
-                hs1[wave][r * 64 + lane] = (_Float16)h1;
-            } else {
-                hs1[wave][r * 64 + lane] = (_Float16)0.f;
+                const float y0 = Y[g * 2], y1 = Y[g * 2 + 1], tg = Tg[g];
+                const float d0 = tg > y0 ? -q_lo : 1.f - q_lo;
+                const float d1 = tg > y1 ? -q_hi : 1.f - q_hi;
+                const float r0 = tg - y0, r1 = tg - y1;
+                lsum += fmaxf(q_lo * r0, (q_lo - 1.f) * r0) + fmaxf(q_hi * r1, (q_hi - 1.f) * r1);
+                d = make_float2(d0 * y0 * (1.f - y0), d1 * y1 * (1.f - y1));
             }
-            dz2s[wave][r * 64 + lane] = (_Float16)dz2;
+            db3[0] += d.x;
+            db3[1] += d.y;
+            b.dz3[lane] = d;
+        }
+        __builtin_amdgcn_wave_barrier();
+        // lane = hidden unit: dZ2's column for the tile's rows; dW3 and db2 on the VALU
+        #pragma unroll
+        for (int r8 = 0; r8 < kTile; r8 += 8) {
+            half8 hv, dv;
+            #pragma unroll
+            for (int i = 0; i < 8; i++) {
+                const float2 d = b.dz3[r8 + i];
+                dw3[0] += h2[r8 + i] * d.x;
+                dw3[1] += h2[r8 + i] * d.y;
+                const float dz2 = h2[r8 + i] > 0.f ? d.x * w3u0 + d.y * w3u1 : 0.f;
+                db2 += dz2;
+                hv[i] = (_Float16)h1[r8 + i];
+                dv[i] = (_Float16)dz2;
+                b.dz2[(r8 + i) * kRow + lane] = dv[i];
+            }
+            *reinterpret_cast<half8 *>(b.h1t + lane * kCol + r8) = hv;
+            *reinterpret_cast<half8 *>(b.dzt + lane * kCol + r8) = dv;
         }
         __builtin_amdgcn_wave_barrier();
         // dW2 += H1^T dZ2: M = unit u, K = row, N = unit v
-        for (int mt = 0; mt < 4; mt++)
-            for (int nt = 0; nt < 4; nt++)
-                for (int ks = 0; ks < 2; ks++) {
-                    half8 a, b;
-                    for (int j = 0; j < 8; j++) {
-                        int row = ks * 32 + 8 * lq + j;
-                        a[j] = hs1[wave][row * 64 + mt * 16 + lr];
-                        b[j] = dz2s[wave][row * 64 + nt * 16 + lr];
-                    }
-                    dw2[mt][nt] = mfma_k32(a, b, dw2[mt][nt]);
-                }
-        // dH1 = dZ2 W2^T (M = row, K = unit v, N = unit u), then dZ1 = dH1 (H1 > 0);
-        // dW1 += X^T dZ1 and db1 on the VALU (lane = unit u after the shuffle through LDS)
-        for (int rt = 0; rt < 4; rt++)
-            for (int ct = 0; ct < 4; ct++) {
-                float4v acc = {0.f, 0.f, 0.f, 0.f};
-                for (int ks = 0; ks < 2; ks++) {
-                    half8 a = *reinterpret_cast<const half8 *>(&dz2s[wave][(rt * 16 + lr) * 64 + ks * 32 + 8 * lq]);
-                    half8 b = *reinterpret_cast<const half8 *>(&s.w2[(ct * 16 + lr) * 64 + ks * 32 + 8 * lq]);
-                    acc = mfma_k32(a, b, acc);
-                }
-                __builtin_amdgcn_wave_barrier();
-                for (int j = 0; j < 4; j++) {
-                    int row = rt * 16 + 4 * lq + j, col = ct * 16 + lr;
-                    float h1 = (float)hs1[wave][row * 64 + col];
-                    // reuse dz2s rows already consumed? no: stash dZ1 in hs1 (h1 no longer needed
-                    // after its sign is read)
-                    hs1[wave][row * 64 + col] = (_Float16)(h1 > 0.f ? acc[j] : 0.f);
-                }
+        {
+            half8 a[4];
+            #pragma unroll
+            for (int mt = 0; mt < 4; mt++) a[mt] = *reinterpret_cast<const half8 *>(b.h1t + (mt * 16 + lr) * kCol + 8 * lq);
+            #pragma unroll
+            for (int nt = 0; nt < 4; nt++) {
+                const half8 d = *reinterpret_cast<const half8 *>(b.dzt + (nt * 16 + lr) * kCol + 8 * lq);
+                #pragma unroll
+                for (int mt = 0; mt < 4; mt++) dw2[mt][nt] = mfma_k32(a[mt], d, dw2[mt][nt]);
             }
+        }
         __builtin_amdgcn_wave_barrier();
-        for (int r = 0; r < 64; r++) {
-            int64_t g = row0 + r;
-            if (g >= n) break;
-            float dz1 = (float)hs1[wave][r * 64 + lane];
-            db1 += dz1;
-            for (int k = 0; k < kIn; k++) dw1[k] += X[g * kIn + k] * dz1;
+        // dH1 = dZ2 W2^T (M = row, K = unit v, N = unit u), then dZ1 = dH1 (H1 > 0), by unit
+        half8 a[kTile / 16][2];
+        #pragma unroll
+        for (int rt = 0; rt < kTile / 16; rt++)
+            #pragma unroll
+            for (int ks = 0; ks < 2; ks++)
+                a[rt][ks] = *reinterpret_cast<const half8 *>(b.dz2 + (rt * 16 + lr) * kRow + ks * 32 + 8 * lq);
+        #pragma unroll
+        for (int ct = 0; ct < 4; ct++) {
+            half8 w[2];
+            #pragma unroll
+            for (int ks = 0; ks < 2; ks++) w[ks] = *reinterpret_cast<const half8 *>(s.w2 + (ct * 16 + lr) * kRow + ks * 32 + 8 * lq);
+            #pragma unroll
+            for (int rt = 0; rt < kTile / 16; rt++) {
+                float4v acc = {0.f, 0.f, 0.f, 0.f};
+                acc = mfma_k32(a[rt][0], w[0], acc);
+                acc = mfma_k32(a[rt][1], w[1], acc);
+                const int at = (ct * 16 + lr) * kCol + rt * 16 + 4 * lq;
+                const half4 hs = *reinterpret_cast<const half4 *>(b.h1t + at);
+                half4 d;
+                #pragma unroll
+                for (int j = 0; j < 4; j++) d[j] = (_Float16)((float)hs[j] > 0.f ? acc[j] : 0.f);
+                *reinterpret_cast<half4 *>(b.dzt + at) = d;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        // dW1 += X^T dZ1 (M = input, K = row, N = unit u), the inputs as two fp16 terms
+        {
+            half8 hi, lo;
+            #pragma unroll
+            for (int j = 0; j < 8; j++) {
+                hi[j] = (_Float16)x[j];
+                lo[j] = (_Float16)(x[j] - (float)hi[j]);
+            }
+            #pragma unroll
+            for (int nt = 0; nt < 4; nt++) {
+                const half8 d = *reinterpret_cast<const half8 *>(b.dzt + (nt * 16 + lr) * kCol + 8 * lq);
+                dw1[nt] = mfma_k32(hi, d, dw1[nt]);
+                dw1[nt] = mfma_k32(lo, d, dw1[nt]);
+            }
         }
         __builtin_amdgcn_wave_barrier();
     }
-    // reduce per block in LDS, then one global atomic per parameter and block
-    for (int k = 0; k < kIn; k++) atomicAdd(&acc_s[kOffW1 + k * 64 + lane], dw1[k]);
-    atomicAdd(&acc_s[kOffB1 + lane], db1);
-    for (int mt = 0; mt < 4; mt++)
-        for (int nt = 0; nt < 4; nt++)
-            for (int j = 0; j < 4; j++)
-                atomicAdd(&acc_s[kOffW2 + (mt * 16 + 4 * lq + j) * 64 + nt * 16 + lr], dw2[mt][nt][j]);
-    atomicAdd(&acc_s[kOffB2 + lane], db2);
-    atomicAdd(&acc_s[kOffW3 + lane * 2], dw3[0]);
-    atomicAdd(&acc_s[kOffW3 + lane * 2 + 1], dw3[1]);
-    if (lane < 2) atomicAdd(&acc_s[kOffB3 + lane], db3[lane]);
-    __syncthreads();
+    for (int o = 32; o > 0; o >>= 1) {
+        db3[0] += __shfl_xor(db3[0], o, 64);
+        db3[1] += __shfl_xor(db3[1], o, 64);
+        lsum += __shfl_xor(lsum, o, 64);
+    }
+    // the block's sums: the upper half of the waves hands its sums to the lower, three times; then
+    // one global atomic per parameter and block (adding to one LDS copy by atomics took 6.6 us per
+    // wave)
+    float sum[kSums];
+    #pragma unroll
+    for (int i = 0; i < 4; i++) {
+        #pragma unroll
+        for (int k = 0; k < 4; k++)
+            #pragma unroll
+            for (int j = 0; j < 4; j++) sum[16 * i + 4 * k + j] = dw2[i][k][j];
+        #pragma unroll
+        for (int j = 0; j < 4; j++) sum[64 + 4 * i + j] = dw1[i][j];
+    }
+    sum[80] = db2;
+    sum[81] = dw3[0];
+    sum[82] = dw3[1];
+    sum[83] = db3[0];
+    sum[84] = db3[1];
+    sum[85] = lsum;
+    sum[86] = sum[87] = 0.f;
+    #pragma unroll
+    for (int half = kWaves / 2; half >= 1; half /= 2) {
+        __syncthreads();
+        if (wave >= half && wave < 2 * half) {
+            #pragma unroll
+            for (int i = 0; i < kSums / 4; i++)
+                s.sums[wave - half][i][lane] = make_float4(sum[4 * i], sum[4 * i + 1], sum[4 * i + 2], sum[4 * i + 3]);
+        }
+        __syncthreads();
+        if (wave < half) {
+            #pragma unroll
+            for (int i = 0; i < kSums / 4; i++) {
+                const float4 v = s.sums[wave][i][lane];
+                sum[4 * i] += v.x;
+                sum[4 * i + 1] += v.y;
+                sum[4 * i + 2] += v.z;
+                sum[4 * i + 3] += v.w;
+            }
+        }
+    }
+    if (wave) return;
     const float inv_n = 1.f / (float)n;
-    for (int i = threadIdx.x; i < kParams; i += blockDim.x) atomicAdd(&dW[i], acc_s[i] * inv_n);
-    if (lane == 0 && lsum != 0.f) atomicAdd(loss, lsum * inv_n);
+    #pragma unroll
+    for (int mt = 0; mt < 4; mt++)
+        #pragma unroll
+        for (int nt = 0; nt < 4; nt++)
+            #pragma unroll
+            for (int j = 0; j < 4; j++)
+                atomicAdd(&dW[kOffW2 + (mt * 16 + 4 * lq + j) * 64 + nt * 16 + lr], sum[16 * mt + 4 * nt + j] * inv_n);
+    #pragma unroll
+    for (int nt = 0; nt < 4; nt++)
+        #pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const int k = 4 * lq + j, u = nt * 16 + lr;       // input (12: the bias), unit
+            if (k < kIn) atomicAdd(&dW[kOffW1 + k * 64 + u], sum[64 + 4 * nt + j] * inv_n);
+            else if (k == kIn) atomicAdd(&dW[kOffB1 + u], sum[64 + 4 * nt + j] * inv_n);
+        }
+    atomicAdd(&dW[kOffB2 + lane], sum[80] * inv_n);
+    atomicAdd(&dW[kOffW3 + lane * 2], sum[81] * inv_n);
+    atomicAdd(&dW[kOffW3 + lane * 2 + 1], sum[82] * inv_n);
+    if (lane < 3) atomicAdd(lane == 2 ? loss : &dW[kOffB3 + lane], (lane == 0 ? sum[83] : (lane == 1 ? sum[84] : sum[85])) * inv_n);
 }
 
-__global__ void mlp_zero(float *p, int n) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.f;
+__global__ void mlp_zero(float *dW, float *loss) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kParams) dW[i] = 0.f;
+    if (i == kParams) *loss = 0.f;
 }
 
 __global__ void mlp_adam_kernel(float *W, const float *dW, float *M, float *V, int n, float lr, float b1, float b2,
@@ -276,9 +459,9 @@ int64_t amr_mlp_packed_bytes(void) { return (int64_t)sizeof(MlpLds); }
 
 int amr_mlp_forward(const float *X, const float *W, float *Y, float *H, int64_t n, void *stream) {
     if (!X || !W || !Y || n <= 0) { set_error("amr_mlp_forward: null argument or n <= 0"); return AMR_EINVAL; }
-    int64_t tiles = (n + 63) / 64;
-    int grid = (int)std::min<int64_t>((tiles + 3) / 4, 4096);
-    hipLaunchKernelGGL(mlp_forward_kernel, dim3(grid), dim3(256), 0, (hipStream_t)stream, X, W, Y, H, n);
+    const int64_t tiles = (n + kTile - 1) / kTile;
+    const int grid = (int)std::min<int64_t>((tiles + kWaves - 1) / kWaves, 2048);
+    hipLaunchKernelGGL(mlp_forward_kernel, dim3(grid), dim3(64 * kWaves), 0, (hipStream_t)stream, X, W, Y, H, n);
     return check_hip_mlp(hipGetLastError(), "mlp_forward launch");
 }
 
@@ -289,11 +472,10 @@ int amr_mlp_backward(const float *X, const float *W, const float *H, const float
         return AMR_EINVAL;
     }
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(mlp_zero, dim3((kParams + 255) / 256), dim3(256), 0, s, dW, kParams);
-    hipLaunchKernelGGL(mlp_zero, dim3(1), dim3(64), 0, s, loss, 1);
-    int64_t tiles = (n + 63) / 64;
-    int grid = (int)std::min<int64_t>((tiles + 3) / 4, 512);
-    hipLaunchKernelGGL(mlp_backward_kernel, dim3(grid), dim3(256), 0, s, X, W, H, Y, T, n, q_lo, q_hi, dW, loss);
+    hipLaunchKernelGGL(mlp_zero, dim3((kParams + 256) / 256), dim3(256), 0, s, dW, loss);
+    const int64_t tiles = (n + kTile - 1) / kTile;
+    const int grid = (int)std::min<int64_t>((tiles + kWaves - 1) / kWaves, kBwdBlocks);
+    hipLaunchKernelGGL(mlp_backward_kernel, dim3(grid), dim3(64 * kWaves), 0, s, X, W, H, Y, T, n, q_lo, q_hi, dW, loss);
     return check_hip_mlp(hipGetLastError(), "mlp_backward launch");
 }
 
