@@ -330,19 +330,16 @@ int launch_persistent(const amr_scene *S, const amr_camera *cams, int32_t ncams,
     int bpc = P->blocks_per_cu > 0 ? P->blocks_per_cu : 4;
     dim3 grid(device_cus() * bpc);
     const bool rec = d_stats != nullptr;
-    if (B.base.lighting) {
-        if (rec) hipLaunchKernelGGL((render_batched<true, true, -1>), grid, dim3(256), 0, s, B);
-        else if (B.base.layout == 0 && two) hipLaunchKernelGGL((render_batched<true, false, 0, 2>), grid, dim3(256), 0, s, B);
-        else if (B.base.layout == 0) hipLaunchKernelGGL((render_batched<true, false, 0>), grid, dim3(256), 0, s, B);
-        else if (B.base.layout == 1 && two) hipLaunchKernelGGL((render_batched<true, false, 1, 2>), grid, dim3(256), 0, s, B);
-        else if (B.base.layout == 1) hipLaunchKernelGGL((render_batched<true, false, 1>), grid, dim3(256), 0, s, B);
-        else if (two) hipLaunchKernelGGL((render_batched<true, false, 2, 2>), grid, dim3(256), 0, s, B);
-        else hipLaunchKernelGGL((render_batched<true, false, 2>), grid, dim3(256), 0, s, B);
+    if (rec) {
+        if (B.base.lighting) hipLaunchKernelGGL((render_batched<true, true, -1>), grid, dim3(256), 0, s, B);
+        else hipLaunchKernelGGL((render_batched<false, true, -1>), grid, dim3(256), 0, s, B);
     } else {
-        if (rec) hipLaunchKernelGGL((render_batched<false, true, -1>), grid, dim3(256), 0, s, B);
-        else if (B.base.layout == 0) hipLaunchKernelGGL((render_batched<false, false, 0>), grid, dim3(256), 0, s, B);
-        else if (B.base.layout == 1) hipLaunchKernelGGL((render_batched<false, false, 1>), grid, dim3(256), 0, s, B);
-        else hipLaunchKernelGGL((render_batched<false, false, 2>), grid, dim3(256), 0, s, B);
+        with_layout(B.base, [&](auto lay) {
+            constexpr int L = decltype(lay)::value;
+            if (B.base.lighting && two) hipLaunchKernelGGL((render_batched<true, false, L, 2>), grid, dim3(256), 0, s, B);
+            else if (B.base.lighting) hipLaunchKernelGGL((render_batched<true, false, L>), grid, dim3(256), 0, s, B);
+            else hipLaunchKernelGGL((render_batched<false, false, L>), grid, dim3(256), 0, s, B);
+        });
     }
     return check_hip(hipGetLastError(), "render_batched launch");
 }

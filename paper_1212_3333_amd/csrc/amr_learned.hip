@@ -131,7 +131,7 @@ constexpr int kNetMinSamples = 32;
 // analytic bound alone, 2 the bound and then the network (G.mlp set).  LOG: segments are logged
 // for training (G.seglog set).  LAY: the brick layout (-1: read at run time).
 template <bool LIT, int DEC, bool LOG, int LAY>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT ? 2 : (LOG ? 4 : 5)))) void render_learned(RenderArgs A, LearnArgs G) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT ? 2 : (LOG ? 4 : (DEC == 2 ? 3 : 5))))) void render_learned(RenderArgs A, LearnArgs G) {
     __shared__ LearnLds s;
     NetLds *sn = nullptr;
     for (int i = threadIdx.x; i < 256; i += 64) s.lut[i] = A.lut[i];
@@ -392,9 +392,9 @@ int launch_learned(const RenderArgs &A, const amr_render_params *P, int lmax, vo
     auto timed = [&](auto lit, auto decc) {
         constexpr bool L = decltype(lit)::value;
         constexpr int D = decltype(decc)::value;
-        if (A.layout == 0) hipLaunchKernelGGL((render_learned<L, D, false, 0>), g, b, 0, s, A, G);
-        else if (A.layout == 1) hipLaunchKernelGGL((render_learned<L, D, false, 1>), g, b, 0, s, A, G);
-        else hipLaunchKernelGGL((render_learned<L, D, false, 2>), g, b, 0, s, A, G);
+        with_layout(A, [&](auto lay) {
+            hipLaunchKernelGGL((render_learned<L, D, false, decltype(lay)::value>), g, b, 0, s, A, G);
+        });
     };
     using T_ = std::true_type;
     using F_ = std::false_type;

@@ -35,7 +35,7 @@ namespace amr {
 // CK: checkpoints (and the tape) without the other recording outputs, for the adjoint's forward
 // pass at the layout's compiled addressing.
 template <bool LIT, bool REC, bool NEAR, int LAY, bool CK = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void render_fwd(RenderArgs A, CamGroup G) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC || NEAR ? 3 : 5))) void render_fwd(RenderArgs A, CamGroup G) {
     // scheduled launches: this block's camera and super-tile from the order (or, before a call
     // has recorded it, camera by camera, super-tiles row by row)
     int gc = (int)blockIdx.y;
@@ -779,15 +779,11 @@ int backward_launch(const amr_scene *S, const amr_camera *cams, int32_t ncams, c
         B.nrays = (int64_t)A.width * A.height;     // one camera's (taken per block)
         B.ray_major = taped;
         const dim3 gg(kBwdGrid / n, n);
-        if (A.lighting) {
-            if (A.layout == 0) hipLaunchKernelGGL((render_bwd<true, 0>), gg, b, 0, s, A, B, G);
-            else if (A.layout == 1) hipLaunchKernelGGL((render_bwd<true, 1>), gg, b, 0, s, A, B, G);
-            else hipLaunchKernelGGL((render_bwd<true, 2>), gg, b, 0, s, A, B, G);
-        } else {
-            if (A.layout == 0) hipLaunchKernelGGL((render_bwd<false, 0>), gg, b, 0, s, A, B, G);
-            else if (A.layout == 1) hipLaunchKernelGGL((render_bwd<false, 1>), gg, b, 0, s, A, B, G);
-            else hipLaunchKernelGGL((render_bwd<false, 2>), gg, b, 0, s, A, B, G);
-        }
+        with_layout(A, [&](auto lay) {
+            constexpr int L = decltype(lay)::value;
+            if (A.lighting) hipLaunchKernelGGL((render_bwd<true, L>), gg, b, 0, s, A, B, G);
+            else hipLaunchKernelGGL((render_bwd<false, L>), gg, b, 0, s, A, B, G);
+        });
         rc = check_hip(hipGetLastError(), "render_bwd launch");
         if (rc == AMR_OK && deterministic)
             hipLaunchKernelGGL(reduce_partials, dim3((kGradLen + 255) / 256), dim3(256), 0, s, partials,
@@ -1065,40 +1061,26 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
         const bool rec = A.trace || A.trace_n || A.nsamp || A.stats || A.touch || A.touch_meta || A.ckpt;
         // scheduled: one-dimensional, four blocks per tile, ranks dealt to the 8 XCDs in turn
         const dim3 g(sched ? 32 * side * side * ((nst + 7) / 8) : gx, sched ? 1 : n), b(64);
-        if (A.nearest) {
-            if (rec) {
-                if (A.lighting) hipLaunchKernelGGL((render_fwd<true, true, true, -1>), g, b, 0, s, A, G);
-                else hipLaunchKernelGGL((render_fwd<false, true, true, -1>), g, b, 0, s, A, G);
-            } else if (A.lighting) {
-                if (A.layout == 0) hipLaunchKernelGGL((render_fwd<true, false, true, 0>), g, b, 0, s, A, G);
-                else if (A.layout == 1) hipLaunchKernelGGL((render_fwd<true, false, true, 1>), g, b, 0, s, A, G);
-                else hipLaunchKernelGGL((render_fwd<true, false, true, 2>), g, b, 0, s, A, G);
-            } else {
-                if (A.layout == 0) hipLaunchKernelGGL((render_fwd<false, false, true, 0>), g, b, 0, s, A, G);
-                else if (A.layout == 1) hipLaunchKernelGGL((render_fwd<false, false, true, 1>), g, b, 0, s, A, G);
-                else hipLaunchKernelGGL((render_fwd<false, false, true, 2>), g, b, 0, s, A, G);
-            }
-        } else if (rec && !(A.ckpt && !A.trace && !A.trace_n && !A.nsamp && !A.stats && !A.touch && !A.touch_meta)) {
-            if (A.lighting) hipLaunchKernelGGL((render_fwd<true, true, false, -1>), g, b, 0, s, A, G);
+        if (rec && !(A.ckpt && !A.nearest && !A.trace && !A.trace_n && !A.nsamp && !A.stats && !A.touch && !A.touch_meta)) {
+            if (A.nearest && A.lighting) hipLaunchKernelGGL((render_fwd<true, true, true, -1>), g, b, 0, s, A, G);
+            else if (A.nearest) hipLaunchKernelGGL((render_fwd<false, true, true, -1>), g, b, 0, s, A, G);
+            else if (A.lighting) hipLaunchKernelGGL((render_fwd<true, true, false, -1>), g, b, 0, s, A, G);
             else hipLaunchKernelGGL((render_fwd<false, true, false, -1>), g, b, 0, s, A, G);
-        } else if (A.ckpt) {       // checkpoints (and the tape) only: the adjoint's forward pass
-            if (A.lighting) {
-                if (A.layout == 0) hipLaunchKernelGGL((render_fwd<true, false, false, 0, true>), g, b, 0, s, A, G);
-                else if (A.layout == 1) hipLaunchKernelGGL((render_fwd<true, false, false, 1, true>), g, b, 0, s, A, G);
-                else hipLaunchKernelGGL((render_fwd<true, false, false, 2, true>), g, b, 0, s, A, G);
-            } else {
-                if (A.layout == 0) hipLaunchKernelGGL((render_fwd<false, false, false, 0, true>), g, b, 0, s, A, G);
-                else if (A.layout == 1) hipLaunchKernelGGL((render_fwd<false, false, false, 1, true>), g, b, 0, s, A, G);
-                else hipLaunchKernelGGL((render_fwd<false, false, false, 2, true>), g, b, 0, s, A, G);
-            }
-        } else if (A.lighting) {   // the timed variants, one per brick layout
-            if (A.layout == 0) hipLaunchKernelGGL((render_fwd<true, false, false, 0>), g, b, 0, s, A, G);
-            else if (A.layout == 1) hipLaunchKernelGGL((render_fwd<true, false, false, 1>), g, b, 0, s, A, G);
-            else hipLaunchKernelGGL((render_fwd<true, false, false, 2>), g, b, 0, s, A, G);
-        } else {
-            if (A.layout == 0) hipLaunchKernelGGL((render_fwd<false, false, false, 0>), g, b, 0, s, A, G);
-            else if (A.layout == 1) hipLaunchKernelGGL((render_fwd<false, false, false, 1>), g, b, 0, s, A, G);
-            else hipLaunchKernelGGL((render_fwd<false, false, false, 2>), g, b, 0, s, A, G);
+        } else {   // the timed variants, one per brick layout
+            with_layout(A, [&](auto lay) {
+                constexpr int L = decltype(lay)::value;
+                if (A.nearest) {
+                    if (A.lighting) hipLaunchKernelGGL((render_fwd<true, false, true, L>), g, b, 0, s, A, G);
+                    else hipLaunchKernelGGL((render_fwd<false, false, true, L>), g, b, 0, s, A, G);
+                } else if (A.ckpt) {       // checkpoints (and the tape) only: the adjoint's forward pass
+                    if (A.lighting) hipLaunchKernelGGL((render_fwd<true, false, false, L, true>), g, b, 0, s, A, G);
+                    else hipLaunchKernelGGL((render_fwd<false, false, false, L, true>), g, b, 0, s, A, G);
+                } else if (A.lighting) {
+                    hipLaunchKernelGGL((render_fwd<true, false, false, L>), g, b, 0, s, A, G);
+                } else {
+                    hipLaunchKernelGGL((render_fwd<false, false, false, L>), g, b, 0, s, A, G);
+                }
+            });
         }
         int rc = check_hip(hipGetLastError(), "render_fwd launch");
         if (rc) return rc;

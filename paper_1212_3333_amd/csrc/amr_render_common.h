@@ -5,6 +5,7 @@
 
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "amr_internal.h"
 #include "amr_tapq_index.h"
@@ -58,6 +59,7 @@ struct RenderArgs {
     float v_lo, inv_range, step_frac, t_min;
     float lhat[3], inv_lnorm, k_a, k_d, eps2;
     int32_t uniform_step, lighting, layout;   // layout: 0 linear, 1 micro-bricks, 2 halo rows
+    int32_t compiled;                // the LAY of the kernels compiled for it
     float *rgba;
     amr_trace_rec *trace;
     int32_t *trace_n;
@@ -308,6 +310,29 @@ __device__ __forceinline__ int descend_walk(const RenderArgs &A, const Ray &R, d
     return -1;
 }
 
+// The exit of a ray from leaf `leaf`, entered at tmin (tmax shrunk to it), and the node its next walk
+// starts at.
+__device__ __forceinline__ void leaf_exit(const RenderArgs &A, const Ray &R, int leaf, double tmin, double &tmax,
+                                          uint32_t &start) {
+#pragma clang fp contract(off)
+    const DLeaf &L = A.leaves[leaf];
+    int face = -1;
+    bool tie = false;
+    #pragma unroll
+    for (int a = 0; a < 3; a++) {
+        const bool up = R.d[a] > 0.0;
+        const double ts = ((up ? L.hi[a] : L.lo[a]) - R.o[a]) * R.invd[a];
+        const bool ahead = R.d[a] != 0.0 && ts > tmin;
+        if (ahead && ts == tmax) tie = true;
+        if (ahead && ts < tmax) {
+            tmax = ts;
+            face = 2 * a + (up ? 1 : 0);
+            tie = false;
+        }
+    }
+    start = (face >= 0 && !tie) ? (uint32_t)A.ropes[6 * leaf + face] : 0u;
+}
+
 // The next leaf of a ray by ropes: the leaves and exits of a restart from the root, found by a
 // shorter walk.  `start` is the node to descend from: the root before the ray's first call, then
 // the rope of the face the last leaf was left through (the smallest node holding the slab beyond
@@ -343,23 +368,7 @@ __device__ __forceinline__ int descend_rope(const RenderArgs &A, const Ray &R, d
         const bool far = da != 0.0 && ts > 0.0 && ts <= tmin;
         ni = n.child + (near_low != far ? 0u : 1u);
     }
-    if (leaf < 0) return leaf;
-    const DLeaf &L = A.leaves[leaf];
-    int face = -1;
-    bool tie = false;
-    #pragma unroll
-    for (int a = 0; a < 3; a++) {
-        const bool up = R.d[a] > 0.0;
-        const double ts = ((up ? L.hi[a] : L.lo[a]) - R.o[a]) * R.invd[a];
-        const bool ahead = R.d[a] != 0.0 && ts > tmin;
-        if (ahead && ts == tmax) tie = true;
-        if (ahead && ts < tmax) {
-            tmax = ts;
-            face = 2 * a + (up ? 1 : 0);
-            tie = false;
-        }
-    }
-    start = (face >= 0 && !tie) ? (uint32_t)A.ropes[6 * leaf + face] : 0u;
+    if (leaf >= 0) leaf_exit(A, R, leaf, tmin, tmax, start);
     return leaf;
 }
 
@@ -405,8 +414,9 @@ __device__ __forceinline__ float lerpf(float a, float b, float f) { return a + f
 
 struct PatchView {
     const float *brick;
-    int px, pxy, nx, ny, nz;          // linear: row and slab strides; micro-bricks: 64 nbx, 64 nbx nby;
-                                      // halo rows: 128 nbx, 128 nbx nby
+    int px, pxy;                      // linear: row and slab strides; micro-bricks: 64 nbx, 64 nbx nby;
+                                      // halo rows: nbx, nbx nby
+    float mx, my, mz;                 // n - 1 per axis, the highest cell index
 };
 
 // Halo-row layout (2): the padded brick is cut into 4x4x4-cell blocks; a block stores its 16
@@ -414,39 +424,105 @@ struct PatchView {
 // the four x cells a stencil row needs lie in one row of the block chosen by the stencil's first
 // core cell, and load as one vector.  Offset of padded x index x in the block column bx:
 __device__ __forceinline__ int halo_x(int x, int bx) { return x + 1 + 124 * bx; }
-// The block row and slab products in 24 bits (one full-rate instruction where the 32-bit product
-// takes four issue slots, eight of them per lit sample): px = 128 nbx and nbx nby stay below 2^24 up
-// to 524288 cells a row and 16384^2 cells a slab.
+// The block row and slab products in 24 bits: one full-rate instruction where the 32-bit product
+// takes four issue slots (block counts of a row and of a slab are below 2^24).
 __device__ __forceinline__ int halo_y(const PatchView &pv, int j) {
-    return (int)__umul24((uint32_t)(j >> 2), (uint32_t)pv.px) + (j & 3) * 8;
+    return (int)(__umul24((uint32_t)(j >> 2), (uint32_t)pv.px) << 7) + (j & 3) * 8;
 }
 __device__ __forceinline__ int halo_z(const PatchView &pv, int k) {
-    return (int)(__umul24((uint32_t)(k >> 2), (uint32_t)pv.pxy >> 7) << 7) + (k & 3) * 32;
+    return (int)(__umul24((uint32_t)(k >> 2), (uint32_t)pv.pxy) << 7) + (k & 3) * 32;
 }
 
-// LAY: the brick layout when known at compile time (0, 1, 2), else -1 (read from A.layout).
+// LAY: the brick layout when known at compile time (0, 1, 2; kHalo32: halo rows in a pool below
+// 4 GB), else -1 (read from A.layout).
+constexpr int kHalo32 = 3;
 template <int LAY = -1>
-__device__ __forceinline__ int layout_of(const RenderArgs &A) { return LAY >= 0 ? LAY : A.layout; }
+__device__ __forceinline__ int layout_of(const RenderArgs &A) {
+    return LAY == kHalo32 ? 2 : (LAY >= 0 ? LAY : A.layout);
+}
 
 template <int LAY = -1>
 __device__ __forceinline__ PatchView patch_view(const RenderArgs &A, const DPatch &P) {
     const int lay = layout_of<LAY>(A);
     PatchView v;
     v.brick = A.pool + P.off;
-    v.nx = P.n[0];
-    v.ny = P.n[1];
-    v.nz = P.n[2];
+    v.mx = (float)(P.n[0] - 1);
+    v.my = (float)(P.n[1] - 1);
+    v.mz = (float)(P.n[2] - 1);
     if (lay == 1) {
         v.px = 64 * P.nb[0];
         v.pxy = v.px * P.nb[1];
     } else if (lay == 2) {
-        v.px = 128 * P.nb[0];
+        v.px = P.nb[0];
         v.pxy = v.px * P.nb[1];
     } else {
-        v.px = v.nx + 2;
-        v.pxy = v.px * (v.ny + 2);
+        v.px = P.n[0] + 2;
+        v.pxy = v.px * (P.n[1] + 2);
     }
     return v;
+}
+
+// The same from a face record: the brick of the slab's single owner.
+template <int LAY = -1>
+__device__ __forceinline__ PatchView patch_view(const RenderArgs &A, const DFaceXf &X) {
+    PatchView v;
+    v.brick = A.pool + X.off;
+    v.mx = (float)(X.n[0] - 1);
+    v.my = (float)(X.n[1] - 1);
+    v.mz = (float)(X.n[2] - 1);
+    const int sh = layout_of<LAY>(A) == 2 ? 7 : 0;       // the record's strides are in floats
+    v.px = X.px >> sh;
+    v.pxy = X.pxy >> sh;
+    return v;
+}
+
+typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// The cell of a patch-local position: lower cell indices, clamped into the brick (-1 and n - 1 + 1
+// are ghost cells), and the position's fractions above them.
+struct Cell3 {
+    float fx, fy, fz;
+    int ix, iy, iz;
+};
+__device__ __forceinline__ Cell3 cell_of(const PatchView &pv, float qx, float qy, float qz) {
+    const float bx = __builtin_amdgcn_fmed3f(floorf(qx), -1.f, pv.mx);
+    const float by = __builtin_amdgcn_fmed3f(floorf(qy), -1.f, pv.my);
+    const float bz = __builtin_amdgcn_fmed3f(floorf(qz), -1.f, pv.mz);
+    return Cell3{qx - bx, qy - by, qz - bz, (int)bx, (int)by, (int)bz};
+}
+
+// Halo rows in a pool below 4 GB (kHalo32): row addresses as 32-bit byte offsets from the pool,
+// which is uniform, so a row costs one add instead of 64-bit pointer arithmetic.  r: the row of core
+// cell (iy, iz) at padded x index ix + 1 (the core's first cell is 4 bytes on); dy, dz: to the next
+// row along y and z.  The address part of an unlit sample takes 26 instructions this way and took
+// 60: 1024^2 unlit 2.64 -> 2.53 ms (5 waves per SIMD with either), a 20-level scene 1.30 -> 1.25 ms; lit
+// frames, which wait on occupancy, stay as they were.  A kernel that holds both forms and chooses at
+// run time needs 10 more registers: 2.60 ms, and the learned kernel 1.54 -> 1.89 ms.
+struct RowBase {
+    uint32_t r, dy, dz;
+    uint32_t py, pz;                 // the step along y or z out of a block
+    int ty, tz;                      // row and slab in the block
+};
+__device__ __forceinline__ RowBase row_base(const RenderArgs &A, const PatchView &pv, const Cell3 &c) {
+    RowBase b;
+    const uint32_t brick = (uint32_t)(uintptr_t)pv.brick - (uint32_t)(uintptr_t)A.pool;
+    const int j = c.iy + 1, k = c.iz + 1;
+    b.ty = j & 3;
+    b.tz = k & 3;
+    b.py = ((uint32_t)pv.px << 9) - 96u;
+    b.pz = ((uint32_t)pv.pxy << 9) - 384u;
+    const uint32_t x = brick + __umul24((uint32_t)(c.ix + 1) >> 2, 496u) + 4u * (uint32_t)c.ix;
+    const uint32_t y = (__umul24((uint32_t)j >> 2, (uint32_t)pv.px) << 9) | ((uint32_t)b.ty << 5);
+    const uint32_t z = (__umul24((uint32_t)k >> 2, (uint32_t)pv.pxy) << 9) | ((uint32_t)b.tz << 7);
+    b.dy = b.ty == 3 ? b.py : 32u;
+    b.dz = b.tz == 3 ? b.pz : 128u;
+    b.r = x + y + z;
+    return b;
+}
+template <typename V>
+__device__ __forceinline__ V pool_row(const RenderArgs &A, uint32_t off, int plus) {
+    return *reinterpret_cast<const V *>(reinterpret_cast<const char *>(A.pool) + (size_t)off + plus);
 }
 
 // Trilinear value of a padded brick at patch-local continuous index q (cell centres at
@@ -454,16 +530,18 @@ __device__ __forceinline__ PatchView patch_view(const RenderArgs &A, const DPatc
 template <bool REC, int LAY = -1>
 __device__ __forceinline__ float trilinear(const RenderArgs &A, const PatchView &pv, float qx, float qy, float qz) {
     const int lay = layout_of<LAY>(A);
-    float fx = floorf(qx), fy = floorf(qy), fz = floorf(qz);
-    int ix = min(max((int)fx, -1), pv.nx - 1);
-    int iy = min(max((int)fy, -1), pv.ny - 1);
-    int iz = min(max((int)fz, -1), pv.nz - 1);
-    fx = qx - (float)ix;
-    fy = qy - (float)iy;
-    fz = qz - (float)iz;
-    typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+    const Cell3 c = cell_of(pv, qx, qy, qz);
+    const float fx = c.fx, fy = c.fy, fz = c.fz;
+    const int ix = c.ix, iy = c.iy, iz = c.iz;
     float v000, v100, v010, v110, v001, v101, v011, v111;
-    if (lay == 1) {
+    if constexpr (LAY == kHalo32) {
+        static_assert(!REC, "recording kernels read the layout at run time");
+        const RowBase b = row_base(A, pv, c);
+        const uint32_t r01 = b.r + b.dz;
+        const f2u a00 = pool_row<f2u>(A, b.r, 8), a10 = pool_row<f2u>(A, b.r + b.dy, 8), a01 = pool_row<f2u>(A, r01, 8),
+                  a11 = pool_row<f2u>(A, r01 + b.dy, 8);
+        v000 = a00.x; v100 = a00.y; v010 = a10.x; v110 = a10.y; v001 = a01.x; v101 = a01.y; v011 = a11.x; v111 = a11.y;
+    } else if (lay == 1) {
         // 4^3 micro-bricks: the +1 neighbour is in the same block unless the index is 3 mod 4
         const int i = ix + 1, j = iy + 1, k = iz + 1;
         const float *b = pv.brick + ((k >> 2) * pv.pxy + (j >> 2) * pv.px + (i >> 2) * 64 + (k & 3) * 16 + (j & 3) * 4 + (i & 3));
@@ -517,21 +595,42 @@ template <bool REC, int LAY = -1>
 __device__ __forceinline__ float trilinear_taps(const RenderArgs &A, const PatchView &pv, float qx, float qy,
                                                 float qz, float Fp[3], float Fm[3]) {
     const int lay = layout_of<LAY>(A);
-    float fx = floorf(qx), fy = floorf(qy), fz = floorf(qz);
-    const int ix = min(max((int)fx, -1), pv.nx - 1);
-    const int iy = min(max((int)fy, -1), pv.ny - 1);
-    const int iz = min(max((int)fz, -1), pv.nz - 1);
-    fx = qx - (float)ix;
-    fy = qy - (float)iy;
-    fz = qz - (float)iz;
+    const Cell3 c = cell_of(pv, qx, qy, qz);
+    const float fx = c.fx, fy = c.fy, fz = c.fz;
+    const int ix = c.ix, iy = c.iy, iz = c.iz;
+    // c[x][y][z] for the core (indices 1, 2 on every axis) and the arms (0 or 3 on one axis)
+    float core[2][2][2], ax[2][2][2], ay[2][2][2], az[2][2][2];
+    if constexpr (LAY == kHalo32) {
+        static_assert(!REC, "recording kernels read the layout at run time");
+        // as below, by 32-bit row offsets; an arm's row beyond the brick is the core's
+        const RowBase b = row_base(A, pv, c);
+        const uint32_t r[2][2] = {{b.r, b.r + b.dz}, {b.r + b.dy, b.r + b.dy + b.dz}};
+        const uint32_t y0 = iy < 0 ? 0u : (b.ty == 0 ? b.py : 32u), z0 = iz < 0 ? 0u : (b.tz == 0 ? b.pz : 128u);
+        const uint32_t y3 = (float)iy == pv.my ? 0u : (b.ty == 2 ? b.py : 32u);
+        const uint32_t z3 = (float)iz == pv.mz ? 0u : (b.tz == 2 ? b.pz : 128u);
+        #pragma unroll
+        for (int v = 0; v < 2; v++)
+            #pragma unroll
+            for (int w = 0; w < 2; w++) {
+                const f4u q = pool_row<f4u>(A, r[v][w], 4);
+                ax[0][v][w] = q.x; core[0][v][w] = q.y; core[1][v][w] = q.z; ax[1][v][w] = q.w;
+            }
+        #pragma unroll
+        for (int w = 0; w < 2; w++) {
+            const f2u a0 = pool_row<f2u>(A, r[0][w] - y0, 8), a1 = pool_row<f2u>(A, r[1][w] + y3, 8);
+            ay[0][0][w] = a0.x; ay[0][1][w] = a0.y; ay[1][0][w] = a1.x; ay[1][1][w] = a1.y;
+            const f2u b0 = pool_row<f2u>(A, r[w][0] - z0, 8), b1 = pool_row<f2u>(A, r[w][1] + z3, 8);
+            az[0][0][w] = b0.x; az[0][1][w] = b0.y; az[1][0][w] = b1.x; az[1][1][w] = b1.y;
+        }
+    } else {
     // padded index ix + d holds cell ix - 1 + d; the arms (d = 0, 3) are clamped to [0, n + 1]
     int xo[4], yo[4], zo[4];
     const int hbx = (ix + 1) >> 2;        // halo rows: the block column of the first core cell
     #pragma unroll
     for (int d = 0; d < 4; d++) {
-        const int i = d == 0 ? max(ix, 0) : (d == 3 ? min(ix + 3, pv.nx + 1) : ix + d);
-        const int j = d == 0 ? max(iy, 0) : (d == 3 ? min(iy + 3, pv.ny + 1) : iy + d);
-        const int k = d == 0 ? max(iz, 0) : (d == 3 ? min(iz + 3, pv.nz + 1) : iz + d);
+        const int i = d == 0 ? max(ix, 0) : (d == 3 ? min(ix + 3, (int)pv.mx + 2) : ix + d);
+        const int j = d == 0 ? max(iy, 0) : (d == 3 ? min(iy + 3, (int)pv.my + 2) : iy + d);
+        const int k = d == 0 ? max(iz, 0) : (d == 3 ? min(iz + 3, (int)pv.mz + 2) : iz + d);
         if (lay == 1) {
             xo[d] = (i >> 2) * 64 + (i & 3);
             yo[d] = (j >> 2) * pv.px + (j & 3) * 4;
@@ -547,16 +646,12 @@ __device__ __forceinline__ float trilinear_taps(const RenderArgs &A, const Patch
         }
     }
     const float *b = pv.brick;
-    // c[x][y][z] for the core (indices 1, 2 on every axis) and the arms (0 or 3 on one axis)
-    float core[2][2][2], ax[2][2][2], ay[2][2][2], az[2][2][2];
     if (lay != 1) {
         // linear and halo-row layouts: the four x cells of a core row are one 16-byte load and
         // each arm row pair one 8-byte load (12 loads instead of 32).  In the linear layout a
         // row load may touch the float before or after the brick row (the arms of a tap that
         // leaves the brick, replaced later); the packer pads the pool by 64 floats on both ends
         // so such reads stay in the allocation.  A halo row holds all four.
-        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-        typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
         // padded x index ix (holding cell ix - 1), unclamped
         const float *row0 = b + (lay == 2 ? halo_x(ix, hbx) : ix);
         #pragma unroll
@@ -600,8 +695,9 @@ __device__ __forceinline__ float trilinear_taps(const RenderArgs &A, const Patch
                                            base + (uint64_t)(xo[1 + v] + yo[3 * u] + zo[1 + w]),
                                            base + (uint64_t)(xo[1 + v] + yo[1 + w] + zo[3 * u])};
                     #pragma unroll
-                    for (int c = 0; c < 4; c++) atomicOr(&A.touch[e[c] >> 5], 1u << (e[c] & 31));
+                    for (int t = 0; t < 4; t++) atomicOr(&A.touch[e[t] >> 5], 1u << (e[t] & 31));
                 }
+    }
     }
     // Interpolate along x, then y, then z, as trilinear does: the twelve rows at the centre's x serve
     // the value and the y and z taps, and the value's two slabs the z taps (39 lerps instead of the
@@ -871,12 +967,7 @@ __device__ __forceinline__ uint32_t resolve_taps(const RenderArgs &A, int leaf, 
             if (c == kTapFace && X.n[0] > 0) {
                 // the slab's single owner: its brick at the mapped position
                 if (REC) cnt.face++;
-                pv.brick = A.pool + X.off;
-                pv.px = X.px;
-                pv.pxy = X.pxy;
-                pv.nx = X.n[0];
-                pv.ny = X.n[1];
-                pv.nz = X.n[2];
+                pv = patch_view<LAY>(A, X);
                 q0 = qt0 * X.r + X.t[0];
                 q1 = qt1 * X.r + X.t[1];
                 q2 = qt2 * X.r + X.t[2];
@@ -953,13 +1044,7 @@ __device__ __forceinline__ uint32_t resolve_taps_nearest(const RenderArgs &A, in
                     co[b] = min(max((int)fl, 0), X.n[b] - 1);
                 }
                 if (clear) {
-                    PatchView pv;
-                    pv.brick = A.pool + X.off;
-                    pv.px = X.px;
-                    pv.pxy = X.pxy;
-                    pv.nx = X.n[0];
-                    pv.ny = X.n[1];
-                    pv.nz = X.n[2];
+                    const PatchView pv = patch_view<LAY>(A, X);
                     val = brick_cell<LAY>(A, pv, co[0], co[1], co[2]);
                     if (REC) cnt.face++;
                     done = true;
@@ -1050,9 +1135,9 @@ __device__ __forceinline__ float nearest_value(const RenderArgs &A, const Ray &R
         #pragma unroll
         for (int a = 0; a < 3; a++) ci[a] = cell_index(x[a], P.lo[a], P.h[a], P.n[a]);
     }
-    ci[0] = min(max(ci[0], 0), S.pv.nx - 1);
-    ci[1] = min(max(ci[1], 0), S.pv.ny - 1);
-    ci[2] = min(max(ci[2], 0), S.pv.nz - 1);
+    ci[0] = min(max(ci[0], 0), (int)S.pv.mx);
+    ci[1] = min(max(ci[1], 0), (int)S.pv.my);
+    ci[2] = min(max(ci[2], 0), (int)S.pv.mz);
     return brick_cell<LAY>(A, S.pv, ci[0], ci[1], ci[2]);
 }
 
@@ -1456,9 +1541,9 @@ __device__ __forceinline__ LitPoint lit_point(const RenderArgs &A, const Ray &R,
             #pragma unroll
             for (int a = 0; a < 3; a++) p.ci[a] = cell_index(p.xs[a], P.lo[a], P.h[a], P.n[a]);
         }
-        p.ci[0] = min(max(p.ci[0], 0), S.pv.nx - 1);
-        p.ci[1] = min(max(p.ci[1], 0), S.pv.ny - 1);
-        p.ci[2] = min(max(p.ci[2], 0), S.pv.nz - 1);
+        p.ci[0] = min(max(p.ci[0], 0), (int)S.pv.mx);
+        p.ci[1] = min(max(p.ci[1], 0), (int)S.pv.my);
+        p.ci[2] = min(max(p.ci[2], 0), (int)S.pv.mz);
     }
     return p;
 }
@@ -1485,7 +1570,7 @@ __device__ __forceinline__ QuadStep lit_step(const RenderArgs &A, const float4 *
             int cj[3] = {p.ci[0], p.ci[1], p.ci[2]};
             cj[a] += sgn ? -1 : 1;
             #pragma unroll
-            for (int b = 0; b < 3; b++) cj[b] = min(max(cj[b], 0), (b == 0 ? S.pv.nx : (b == 1 ? S.pv.ny : S.pv.nz)) - 1);
+            for (int b = 0; b < 3; b++) cj[b] = min(max(cj[b], 0), (int)(b == 0 ? S.pv.mx : (b == 1 ? S.pv.my : S.pv.mz)));
             const float val = brick_cell<LAY>(A, S.pv, cj[0], cj[1], cj[2]);
             if (sgn) Fm[a] = val;
             else Fp[a] = val;
@@ -1567,6 +1652,15 @@ __device__ __forceinline__ void flush_counters(amr_render_stats *st, Counters c,
 // Host helpers
 // ------------------------------------------------------------------------------------------
 
+// f(LAY) for the kernels compiled for the scene's layout (A.compiled).
+template <typename F>
+inline void with_layout(const RenderArgs &A, F f) {
+    if (A.compiled == 0) f(std::integral_constant<int, 0>{});
+    else if (A.compiled == 1) f(std::integral_constant<int, 1>{});
+    else if (A.compiled == 2) f(std::integral_constant<int, 2>{});
+    else f(std::integral_constant<int, kHalo32>{});
+}
+
 inline int check_hip(hipError_t e, const char *what) {
     if (e != hipSuccess) {
         set_error("%s: %s", what, hipGetErrorString(e));
@@ -1582,6 +1676,8 @@ inline int fill_args(const amr_scene *S, const amr_camera *C, const amr_render_p
     if (!(P->step_frac > 0.f) || !std::isfinite(P->step_frac)) { set_error("step_frac must be positive"); return AMR_EINVAL; }
     if (C->width <= 0 || C->height <= 0) { set_error("camera size must be positive"); return AMR_EINVAL; }
     A->pool = S->pool;
+    if (S->brick_layout == 2 && S->pool_bytes < ((int64_t)1 << 32)) A->compiled = kHalo32;
+    else A->compiled = S->brick_layout;
     A->nodes = (const DNode *)S->nodes;
     A->leaves = (const DLeaf *)S->leaves;
     A->patches = (const DPatch *)S->patches;
