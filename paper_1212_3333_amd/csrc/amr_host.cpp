@@ -14,10 +14,12 @@
 #include <cstring>
 #include <memory>
 #include <new>
+#include <string>
 #include <thread>
 #include <vector>
 
 #include "amr_internal.h"
+#include "amr_pack.h"
 
 namespace amr {
 
@@ -691,6 +693,54 @@ double world_plane(const amr_tree *T, int a, int64_t G) {
 
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
+// `work` on n threads, the calling one among them.
+template <typename F>
+void run_threads(int n, F &work) {
+    std::vector<std::thread> th;
+    for (int t = 1; t < n; t++) th.emplace_back([&]() { work(); });
+    work();
+    for (auto &x : th) x.join();
+}
+
+// What the packing kernels need to know of the patches: where cells, shells and bricks lie, the boxes
+// and the neighbours (pk.nbr) that the ghost layers draw from.
+void plan_device(const amr_tree *T, const amr_patch *patches, int np, int layout, const std::vector<int64_t> &off,
+                 int64_t nfl, const Packer &pk, PackPlan &plan) {
+    plan.layout = layout;
+    plan.pool_floats = nfl + 64;
+    for (int a = 0; a < 3; a++) {
+        plan.B_lo[a] = T->B_lo[a];
+        plan.B_hi[a] = T->B_hi[a];
+    }
+    plan.levels.resize((size_t)T->lmax + 1);
+    plan.patches.resize((size_t)np);
+    plan.cells.resize((size_t)np);
+    for (int p = 0; p < np; p++) {
+        PackPatch &P = plan.patches[p];
+        memset(&P, 0, sizeof(P));
+        P.level = T->plevel[p];
+        P.scale = T->scale[P.level];
+        for (int a = 0; a < 3; a++) {
+            P.n[a] = (int32_t)patches[p].dims[a];
+            P.nb[a] = (P.n[a] + 5) / 4;
+            P.lo[a] = patches[p].lo[a];
+            P.blo[a] = T->pbox[p].lo[a];
+            P.bhi[a] = T->pbox[p].hi[a];
+        }
+        P.cells = plan.cell_floats;
+        P.shell = plan.shell_doubles;
+        P.pool = off[p];
+        P.floats = (p + 1 < np ? off[p + 1] : nfl) - off[p];
+        plan.cell_floats += (int64_t)P.n[0] * P.n[1] * P.n[2];
+        plan.shell_doubles += shell_count(P.n);
+        P.nbr0 = (int32_t)plan.nbr.size();
+        plan.nbr.insert(plan.nbr.end(), pk.nbr[p].begin(), pk.nbr[p].end());
+        P.nbr1 = (int32_t)plan.nbr.size();
+        plan.cells[p] = patches[p].cells;
+        plan.levels[P.level].push_back(p);
+    }
+}
+
 }  // namespace
 }  // namespace amr
 
@@ -823,31 +873,68 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
     int nthreads = opts && opts->nthreads > 0 ? opts->nthreads : (int)std::max(1u, std::thread::hardware_concurrency());
     bool host_dst = opts && opts->host_dst;
 
+    // Cell-centred patches bound for the GPU are packed there (amr_pack.hip) from the cells as they
+    // are; the host packs for host memory, vertex-centred data, an unaligned pool, and where the GPU
+    // has no room to stage the cells.  Both form the same bytes.
+    PackPlan plan;
+    PackStage stage;
+    bool device = !host_dst && !vertex && ((uintptr_t)d_pool & 15u) == 0;
+    struct StageGuard {
+        PackStage *st;
+        ~StageGuard() { pack_stage_free(st); }
+    } guard{&stage};
+    float vmin = INFINITY, vmax = -INFINITY;
     std::vector<float> pool;
     std::vector<uint8_t> meta;
+    int upload_rc = AMR_OK;
+    std::string upload_err;
     try {
-        pool.assign((size_t)nfl, 0.0f);
         meta.assign((size_t)mbytes, 0);
         Packer pk{T, patches, np, vertex, {}, {}};
-        pk.run(nthreads);
-        float vmin = INFINITY, vmax = -INFINITY;
-        for (int p = 0; p < np; p++) {
-            const std::vector<double> &b = pk.brick[p];
-            int32_t n32[3], nb[3];
-            for (int a = 0; a < 3; a++) {
-                n32[a] = (int32_t)patches[p].dims[a] + vertex;
-                nb[a] = (n32[a] + 5) / 4;
-            }
-            const int64_t px = n32[0] + 2, py = n32[1] + 2, pz = n32[2] + 2;
-            if (layout == 2) {
-                halo_row_fill(n32, nb, pool.data() + off[p],
-                              [&](int64_t i, int64_t j, int64_t k) { return (float)b[(size_t)(i + px * (j + py * k))]; });
-                continue;
-            }
-            for (int64_t k = 0; k < pz; k++)
-                for (int64_t j = 0; j < py; j++)
-                    for (int64_t i = 0; i < px; i++)
-                        pool[(size_t)(off[p] + brick_index(layout, n32, nb, i, j, k))] = (float)b[(size_t)(i + px * (j + py * k))];
+        std::thread uploader;
+        struct Join {
+            std::thread *t;
+            ~Join() { if (t->joinable()) t->join(); }
+        } join{&uploader};
+        if (device) {
+            pk.neighbours(nthreads);
+            plan_device(T, patches, np, layout, off, nfl, pk, plan);
+            device = pack_stage_alloc(plan, nl, &stage);
+        }
+        if (device) {
+            // the cells travel while the tree and the records below are written
+            int dev = 0;
+            (void)hipGetDevice(&dev);
+            uploader = std::thread([&, dev]() {
+                (void)hipSetDevice(dev);
+                upload_rc = pack_upload_cells(plan, stage, stream);
+                if (upload_rc) upload_err = g_err;
+            });
+        } else {
+            pool.assign((size_t)nfl, 0.0f);
+            pk.run(nthreads);
+            std::atomic<int> next{0};
+            auto work = [&]() {
+                for (int p; (p = next.fetch_add(1)) < np;) {
+                    const std::vector<double> &b = pk.brick[p];
+                    int32_t n32[3], nb[3];
+                    for (int a = 0; a < 3; a++) {
+                        n32[a] = (int32_t)patches[p].dims[a] + vertex;
+                        nb[a] = (n32[a] + 5) / 4;
+                    }
+                    const int64_t px = n32[0] + 2, py = n32[1] + 2, pz = n32[2] + 2;
+                    if (layout == 2) {
+                        halo_row_fill(n32, nb, pool.data() + off[p],
+                                      [&](int64_t i, int64_t j, int64_t k) { return (float)b[(size_t)(i + px * (j + py * k))]; });
+                        continue;
+                    }
+                    for (int64_t k = 0; k < pz; k++)
+                        for (int64_t j = 0; j < py; j++)
+                            for (int64_t i = 0; i < px; i++)
+                                pool[(size_t)(off[p] + brick_index(layout, n32, nb, i, j, k))] = (float)b[(size_t)(i + px * (j + py * k))];
+                }
+            };
+            run_threads(nthreads, work);
         }
         // device tree, breadth first with adjacent children
         DNode *dn = (DNode *)(meta.data() + o_nodes);
@@ -879,14 +966,16 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
             int l = T->plevel[p];
             h.off = (uint64_t)off[p];
             h.level = l;
-            float pmin = INFINITY, pmax = -INFINITY;
-            for (double v : pk.brick[p]) { pmin = std::min(pmin, (float)v); pmax = std::max(pmax, (float)v); }
-            h.vmin = pmin;
-            h.vmax = pmax;
+            if (!device) {
+                float pmin = INFINITY, pmax = -INFINITY;
+                for (double v : pk.brick[p]) { pmin = std::min(pmin, (float)v); pmax = std::max(pmax, (float)v); }
+                h.vmin = pmin;
+                h.vmax = pmax;
+                vmin = std::min(vmin, pmin);
+                vmax = std::max(vmax, pmax);
+            }
             for (int a = 0; a < 3; a++) h.nb[a] = ((int32_t)patches[p].dims[a] + vertex + 5) / 4;
             h.layout = layout;
-            vmin = std::min(vmin, pmin);
-            vmax = std::max(vmax, pmax);
             double hmin = INFINITY;
             for (int a = 0; a < 3; a++) {
                 h.n[a] = (int32_t)patches[p].dims[a] + vertex;
@@ -903,7 +992,8 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
             h.step = hmin / rl;
         }
         DLeaf *dl = (DLeaf *)(meta.data() + o_leaves);
-        for (int64_t k = 0; k < nl; k++) {
+        if (device) plan.leaves.resize((size_t)nl);
+        auto leaf_record = [&](int64_t k) {
             const bool virt = k >= nl0;           // a kind-(a) node, rendered from its cover patch
             const Node &n = virt ? T->nodes[anodes[k - nl0]] : T->nodes[T->leaves[k]];
             const int32_t np_k = virt ? n.cover : n.patch;
@@ -920,6 +1010,7 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
             }
             L.vmin = 0.0f;
             L.vmax = 0.0f;
+            if (device) plan.leaves[(size_t)k] = PackLeaf{-1, {0, 0, 0}, {0, 0, 0}};
             if (np_k >= 0) {
                 // value range over what a sample in the leaf can read: cell-centred, the leaf's
                 // cells plus one halo cell; vertex-centred, the vertices of the leaf's cells
@@ -933,6 +1024,15 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
                 const int64_t d[3] = {patches[p].dims[0] + vertex, patches[p].dims[1] + vertex,
                                       patches[p].dims[2] + vertex};
                 const int64_t first = vertex ? 0 : 1;
+                if (device) {
+                    PackLeaf &pl = plan.leaves[(size_t)k];
+                    pl.patch = p;
+                    for (int a = 0; a < 3; a++) {
+                        pl.lo[a] = (int32_t)(i0[a] - first);
+                        pl.hi[a] = (int32_t)i1[a];
+                    }
+                    return;
+                }
                 const std::vector<double> &bk = pk.brick[p];
                 float mn = INFINITY, mx = -INFINITY;
                 for (int64_t z = i0[2] - first; z <= i1[2]; z++)
@@ -945,6 +1045,14 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
                 L.vmin = mn;
                 L.vmax = mx;
             }
+        };
+        {
+            std::atomic<int64_t> next{0};
+            auto work = [&]() {
+                for (int64_t k0; (k0 = next.fetch_add(64)) < nl;)
+                    for (int64_t k = k0; k < std::min(k0 + 64, nl); k++) leaf_record(k);
+            };
+            run_threads((int)std::min<int64_t>(nthreads, (nl + 63) / 64), work);
         }
         // gradient-tap records per leaf face (after the patch headers, which they read)
         DFaceXf *fx = (DFaceXf *)(meta.data() + o_fxf);
@@ -1007,12 +1115,22 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
             out->h0[a] = T->dom.h0[a];
             out->hfine[a] = T->dom.h0[a] / (double)T->scale[0];
         }
+        if (device) {
+            uploader.join();
+            if (upload_rc) {
+                set_error("%s", upload_err.c_str());
+                return upload_rc;
+            }
+            const int rc = pack_run(plan, stage, d_pool, d_meta, meta.data(), mbytes, o_leaves, o_patch, &vmin, &vmax, stream);
+            if (rc) return rc;
+        }
         out->v_min = vmin;
         out->v_max = vmax;
     } catch (const std::bad_alloc &) {
         set_error("out of host memory");
         return AMR_ENOMEM;
     }
+    if (device) return AMR_OK;
     if (host_dst) {
         memcpy(d_pool, pool.data(), pool.size() * 4);
         memcpy(d_meta, meta.data(), meta.size());
