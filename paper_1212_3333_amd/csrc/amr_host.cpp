@@ -12,6 +12,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <memory>
 #include <new>
 #include <string>
@@ -906,9 +907,13 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
             int dev = 0;
             (void)hipGetDevice(&dev);
             uploader = std::thread([&, dev]() {
-                (void)hipSetDevice(dev);
-                upload_rc = pack_upload_cells(plan, stage, stream);
-                if (upload_rc) upload_err = g_err;
+                try {
+                    upload_rc = pack_upload_cells(plan, stage, dev);
+                    if (upload_rc) upload_err = g_err;
+                } catch (const std::exception &e) {      // no thread or memory to copy with
+                    upload_rc = AMR_ENOMEM;
+                    upload_err = e.what();
+                }
             });
         } else {
             pool.assign((size_t)nfl, 0.0f);

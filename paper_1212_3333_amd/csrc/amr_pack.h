@@ -67,8 +67,8 @@ struct PackStage {
 // False when the device has no room (nothing allocated then).  nbr, leaves: upper bounds.
 bool pack_stage_alloc(const PackPlan &plan, int64_t nleaves, PackStage *st);
 void pack_stage_free(PackStage *st);
-// Enqueues the copies of the patches' cells.
-int pack_upload_cells(const PackPlan &plan, const PackStage &st, void *stream);
+// Copies the patches' cells to the stage on device `device`, and waits.
+int pack_upload_cells(const PackPlan &plan, const PackStage &st, int device);
 // Uploads tables and metadata, fills the pool and the value ranges of the metadata's patch headers and
 // leaf records, and waits; the range of all cells in *vmin, *vmax.
 int pack_run(const PackPlan &plan, const PackStage &st, void *d_pool, void *d_meta, const void *meta, int64_t meta_bytes,

@@ -8,7 +8,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <thread>
 
 #include "amr_pack.h"
 
@@ -249,6 +251,11 @@ __global__ __launch_bounds__(256) void leaf_range_kernel(const PackPatch *patche
 
 int64_t up256(int64_t b) { return (b + 255) / 256 * 256; }
 
+// Threads that copy, each on its own stream: the copy of pageable memory is bound by the host's pass
+// through pinned buffers (250 patches, 60 M cells, pack: 18.3 ms with one thread, 15.4 with two, 14.7 with
+// four, 16.3 with eight).
+constexpr int kUploaders = 4;
+
 int hip_failed(hipError_t e, const char *what) {
     if (e == hipSuccess) return AMR_OK;
     set_error("%s: %s", what, hipGetErrorString(e));
@@ -288,15 +295,32 @@ void pack_stage_free(PackStage *st) {
     st->mem = nullptr;
 }
 
-int pack_upload_cells(const PackPlan &plan, const PackStage &st, void *stream) {
-    for (size_t p = 0; p < plan.patches.size(); p++) {
-        const PackPatch &P = plan.patches[p];
-        const size_t bytes = 4 * (size_t)P.n[0] * P.n[1] * P.n[2];
-        const int rc = hip_failed(hipMemcpyAsync(st.cells + P.cells, plan.cells[p], bytes, hipMemcpyHostToDevice,
-                                                 (hipStream_t)stream), "copy of the cells");
-        if (rc) return rc;
+int pack_upload_cells(const PackPlan &plan, const PackStage &st, int device) {
+    const int nt = (int)std::min<size_t>(kUploaders, plan.patches.size());
+    std::atomic<size_t> next{0};
+    std::atomic<int> failed{(int)hipSuccess};
+    auto work = [&]() {
+        hipError_t e = hipSetDevice(device);
+        for (size_t p; e == hipSuccess && failed == (int)hipSuccess && (p = next.fetch_add(1)) < plan.patches.size();) {
+            const PackPatch &P = plan.patches[p];
+            e = hipMemcpyAsync(st.cells + P.cells, plan.cells[p], 4 * (size_t)P.n[0] * P.n[1] * P.n[2], hipMemcpyHostToDevice,
+                               hipStreamPerThread);
+        }
+        const hipError_t w = hipStreamSynchronize(hipStreamPerThread);
+        if (e == hipSuccess) e = w;
+        if (e != hipSuccess) failed = (int)e;
+    };
+    struct Pool {
+        std::vector<std::thread> th;
+        ~Pool() {
+            for (auto &x : th) x.join();
+        }
+    };
+    {
+        Pool pool;
+        for (int t = 0; t < nt; t++) pool.th.emplace_back(work);
     }
-    return AMR_OK;
+    return hip_failed((hipError_t)failed.load(), "copy of the cells");
 }
 
 int pack_run(const PackPlan &plan, const PackStage &st, void *d_pool, void *d_meta, const void *meta, int64_t meta_bytes,
