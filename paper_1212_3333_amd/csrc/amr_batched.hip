@@ -142,7 +142,7 @@ template <bool LIT, bool REC, int LAY, int WPS = 3>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void render_batched(BatchArgs B) {
     __shared__ float4 s_lut[256];
     TapQueue *tq = nullptr;                        // lit: one deferred-tap queue per wave
-    if constexpr (LIT) tq = tap_queues<4>() + (threadIdx.x >> 6);
+    if constexpr (LIT) tq = tap_queues<4, TapQueue>() + (threadIdx.x >> 6);
     s_lut[threadIdx.x] = B.base.lut[threadIdx.x];
     __syncthreads();
     const int lane = threadIdx.x & 63;
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
                     uint32_t tpos = 0;
                     for (int k = 0; k < S.n && alive; k += 4) {
                         const LitPoint pt = lit_point<false>(A, R, S, min(k + sub, S.n - 1));
-                        if (tapq_full(tq_count(Q), __ballot(pt.pend != 0u && k + sub < S.n)))
+                        if (tq_due(Q, k + sub < S.n ? pt.pend : 0u, lane))
                             tapq_flush<REC, LAY>(A, s_lut, Q, lane, cnt);
                         const QuadStep st = lit_step<REC, LAY, false>(A, s_lut, Q, lane, R, S, k, pt, T, C0, C1, C2, cnt,
                                                                       nullptr, tpos);

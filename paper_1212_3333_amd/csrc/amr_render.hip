@@ -60,8 +60,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
     constexpr bool kDefer = LIT;
     constexpr bool kCk = REC || CK;             // checkpoints (and the tape) may be recorded
     __shared__ float4 s_lut[256];
-    TapQueue *tq = nullptr;
-    if constexpr (kDefer) tq = tap_queues<1>();
+    using TQ = std::conditional_t<NEAR || kCk, TapQueueList, TapQueue>;
+    TQ *tq = nullptr;
+    if constexpr (kDefer) tq = tap_queues<1, TQ>();
     for (int i = threadIdx.x; i < 256; i += 64) s_lut[i] = A.lut[i];
     __syncthreads();
 
@@ -170,7 +171,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
         // takes four samples on every quad that has a segment; the tap queue is resolved before
         // a step's stencils are read, where every lane of the wave works on it.  Segments, sample
         // positions and traces are those of the per-segment loop of the unlit variants below.
-        TapQueue &Q = *tq;
+        TQ &Q = *tq;
         tapq_init(Q, lane);
         double tcur = R.t0;
         uint32_t start = 0;
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
             LitPoint pt;
             pt.pend = 0u;
             if (has) pt = lit_point<NEAR>(A, R, S, min(k + sub, S.n - 1));
-            if (tapq_full(tq_count(Q), __ballot(has && pt.pend != 0u && k + sub < S.n)))
+            if (tq_due(Q, has && k + sub < S.n ? pt.pend : 0u, lane))
                 tapq_flush<REC, LAY, NEAR, kCk>(A, s_lut, Q, lane, cnt, tape_base);
             if (has) {
                 const QuadStep q = lit_step<REC, LAY, NEAR>(A, s_lut, Q, lane, R, S, k, pt, T, C0, C1, C2, cnt, trow, tpos);

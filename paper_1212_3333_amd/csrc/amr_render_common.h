@@ -927,14 +927,61 @@ __device__ __forceinline__ void tap_point(const RenderArgs &A, int patch, const 
     for (int b = 0; b < 3; b++) xt[b] = b == a ? xn : xs[b];
 }
 
-// The taps of a lit sample that may leave its brick (out and face as classify_taps returns
-// them), one at a time: each chooses a brick and a position in it, then one trilinear read
-// replaces Fp or Fm.  A tap beyond a face whose one-cell slab has a single owner patch is
-// mapped into that patch's brick (the face record of the leaf); otherwise the exact FP64 tap
-// point xs +- h^l e_a is located by a descent from the rope node holding the slab, else from
-// the root.  leaf, patch and safe describe the sample's segment, own its brick (null: read
-// from the patch header when a tap needs it); xs is the sample's FP64 position, (qx, qy, qz)
-// its patch-local position.  Returns bit t set where tap t holds data.
+// The brick that holds tap t of a lit sample which may leave its own (face: it surely lies in the slab
+// beyond the leaf's face), and the tap's position in it.  A tap beyond a face whose one-cell slab
+// has a single owner patch is mapped into that patch's brick (the face record of the leaf);
+// otherwise the exact FP64 tap point xs +- h^l e_a is located by a descent from the rope node
+// holding the slab, else from the root.  leaf, patch and safe describe the sample's segment, own its
+// brick (null: read from the patch header when the tap needs it); xs is the sample's FP64 position,
+// (qx, qy, qz) its patch-local position.  False where the tap holds no data.
+template <bool REC, int LAY = -1>
+__device__ __forceinline__ bool tap_brick(const RenderArgs &A, int leaf, int patch, uint32_t safe, const PatchView *own,
+                                          const double xs[3], float qx, float qy, float qz, int t, bool face,
+                                          PatchView &pv, float &q0, float &q1, float &q2, Counters &cnt) {
+    const int a = t >> 1, sgn = t & 1;
+    int c = face ? kTapFace : kTapUnsure;
+    const float step = sgn ? -1.f : 1.f;
+    const float qt0 = qx + (a == 0 ? step : 0.f), qt1 = qy + (a == 1 ? step : 0.f),
+                qt2 = qz + (a == 2 ? step : 0.f);
+    // the exact FP64 tap point, formed near a face and for descents only
+    double xt[3] = {0.0, 0.0, 0.0};
+    const bool exact = c != kTapFace;
+    if (exact) tap_point(A, patch, xs, a, sgn, xt);
+    if (REC && c == kTapUnsure) cnt.unsure++;
+    if (c == kTapUnsure) c = classify_tap_fp64(A, leaf, patch, safe, xt, a, sgn);
+    q0 = qt0;
+    q1 = qt1;
+    q2 = qt2;
+    bool ok = true;
+    if (c == kTapSame) {
+        pv = own ? *own : patch_view<LAY>(A, A.patches[patch]);
+    } else {
+        const DFaceXf X = c == kTapFace ? A.face_xf[6 * leaf + 2 * a + (sgn ? 0 : 1)] : DFaceXf{};
+        if (REC && A.touch_meta && c == kTapFace)
+            touch_meta(A, &A.face_xf[6 * leaf + 2 * a + (sgn ? 0 : 1)], (int)sizeof(DFaceXf));
+        if (c == kTapFace && X.n[0] > 0) {
+            // the slab's single owner: its brick at the mapped position
+            if (REC) cnt.face++;
+            pv = patch_view<LAY>(A, X);
+            q0 = qt0 * X.r + X.t[0];
+            q1 = qt1 * X.r + X.t[1];
+            q2 = qt2 * X.r + X.t[2];
+        } else {
+            // descend from the rope node holding the slab, else from the root (a slab beyond
+            // B fails the box test there, except on B's closed upper faces)
+            if (!exact) tap_point(A, patch, xs, a, sgn, xt);
+            float qq[3];
+            ok = locate_brick<REC, LAY>(A, xt, pv, qq, cnt, c == kTapFace && X.rope > 0 ? (uint32_t)X.rope : 0u);
+            q0 = qq[0];
+            q1 = qq[1];
+            q2 = qq[2];
+        }
+    }
+    return ok;
+}
+
+// The taps in `out` of one sample (face: classify_taps), one after the other: a trilinear read
+// replaces Fp or Fm.  Returns bit t set where tap t holds data.
 template <bool REC, int LAY = -1>
 __device__ __forceinline__ uint32_t resolve_taps(const RenderArgs &A, int leaf, int patch, uint32_t safe,
                                                  const PatchView *own, const double xs[3], float qx, float qy,
@@ -944,44 +991,10 @@ __device__ __forceinline__ uint32_t resolve_taps(const RenderArgs &A, int leaf, 
     while (out) {
         const int t = __builtin_ctz(out);
         out &= out - 1u;
-        const int a = t >> 1, sgn = t & 1;
-        int c = ((face >> t) & 1u) ? kTapFace : kTapUnsure;
-        const float step = sgn ? -1.f : 1.f;
-        const float qt0 = qx + (a == 0 ? step : 0.f), qt1 = qy + (a == 1 ? step : 0.f),
-                    qt2 = qz + (a == 2 ? step : 0.f);
-        // the exact FP64 tap point, formed near a face and for descents only
-        double xt[3] = {0.0, 0.0, 0.0};
-        const bool exact = c != kTapFace;
-        if (exact) tap_point(A, patch, xs, a, sgn, xt);
-        if (REC && c == kTapUnsure) cnt.unsure++;
-        if (c == kTapUnsure) c = classify_tap_fp64(A, leaf, patch, safe, xt, a, sgn);
         PatchView pv;
-        float q0 = qt0, q1 = qt1, q2 = qt2;
-        bool ok = true;
-        if (c == kTapSame) {
-            pv = own ? *own : patch_view<LAY>(A, A.patches[patch]);
-        } else {
-            const DFaceXf X = c == kTapFace ? A.face_xf[6 * leaf + 2 * a + (sgn ? 0 : 1)] : DFaceXf{};
-            if (REC && A.touch_meta && c == kTapFace)
-                touch_meta(A, &A.face_xf[6 * leaf + 2 * a + (sgn ? 0 : 1)], (int)sizeof(DFaceXf));
-            if (c == kTapFace && X.n[0] > 0) {
-                // the slab's single owner: its brick at the mapped position
-                if (REC) cnt.face++;
-                pv = patch_view<LAY>(A, X);
-                q0 = qt0 * X.r + X.t[0];
-                q1 = qt1 * X.r + X.t[1];
-                q2 = qt2 * X.r + X.t[2];
-            } else {
-                // descend from the rope node holding the slab, else from the root (a slab beyond
-                // B fails the box test there, except on B's closed upper faces)
-                if (!exact) tap_point(A, patch, xs, a, sgn, xt);
-                float qq[3];
-                ok = locate_brick<REC, LAY>(A, xt, pv, qq, cnt, c == kTapFace && X.rope > 0 ? (uint32_t)X.rope : 0u);
-                q0 = qq[0];
-                q1 = qq[1];
-                q2 = qq[2];
-            }
-        }
+        float q0, q1, q2;
+        const bool ok = tap_brick<REC, LAY>(A, leaf, patch, safe, own, xs, qx, qy, qz, t, (face >> t) & 1u, pv, q0, q1,
+                                            q2, cnt);
         const float Fs = ok ? trilinear<REC, LAY>(A, pv, q0, q1, q2) : 0.f;
         if (!ok) okbits &= ~(1u << t);
         // write the tap back (selects keep the arrays in registers)
@@ -994,74 +1007,54 @@ __device__ __forceinline__ uint32_t resolve_taps(const RenderArgs &A, int leaf, 
     return okbits;
 }
 
-// The pending taps (bit t of pend) of a nearest-cell lit sample, one at a time: each reads the
-// cell of the finest patch holding the exact FP64 tap point xs +- h^l e_a.  A tap classified
-// in the sample's own patch takes its cell from the FP64 position; beyond a face whose slab has
-// a single owner, the cell under the mapped position when that is clear of the owner's cell
-// faces; otherwise a descent from the slab's rope node, else from the root.  leaf, patch and
-// safe describe the sample's segment, q its patch-local position, out and face its taps' classes.
-// Returns bit t set where tap t holds data.
+// Pending tap t of a nearest-cell lit sample: the cell of the finest patch holding the exact FP64 tap
+// point xs +- h^l e_a.  A tap classified in the sample's own patch (not in `out`) takes its cell
+// from the FP64 position; beyond a face whose slab has a single owner (in `face`), the cell under
+// the mapped position when that is clear of the owner's cell faces; otherwise a descent from the
+// slab's rope node, else from the root.  False where the tap holds no data.
 template <bool REC, int LAY = -1>
-__device__ __forceinline__ uint32_t resolve_taps_nearest(const RenderArgs &A, int leaf, int patch, uint32_t safe,
-                                                         const double xs[3], const float q[3], uint32_t out,
-                                                         uint32_t face, uint32_t pend, float Fp[3], float Fm[3],
-                                                         Counters &cnt) {
+__device__ __forceinline__ bool resolve_tap_nearest(const RenderArgs &A, int leaf, int patch, uint32_t safe,
+                                                    const double xs[3], const float q[3], int t, bool out, bool face,
+                                                    float &val, Counters &cnt) {
     const DPatch &P = A.patches[patch];
-    uint32_t okbits = 0x3fu;
-    while (pend) {
-        const int t = __builtin_ctz(pend);
-        pend &= pend - 1u;
-        const int a = t >> 1, sgn = t & 1;
-        float qt[3] = {q[0], q[1], q[2]};
-        qt[a] += sgn ? -1.f : 1.f;
-        const int c = !((out >> t) & 1u) ? kTapSame : (((face >> t) & 1u) ? kTapFace : kTapUnsure);
-        double xt[3] = {xs[0], xs[1], xs[2]};
-        {
-#pragma clang fp contract(off)
-            xt[a] = sgn ? xs[a] - P.h[a] : xs[a] + P.h[a];
-        }
-        float val = 0.f;
-        bool ok = true, done = false;
-        if (REC && c == kTapUnsure) cnt.unsure++;
-        const int c2 = c == kTapUnsure ? classify_tap_fp64(A, leaf, patch, safe, xt, a, sgn) : c;
-        uint32_t from = 0;
-        if (c2 == kTapSame) {
-            // the tap lies where the sample's own patch is the finest: its cell, in FP64
-            const PatchView pv = patch_view<LAY>(A, P);
-            val = brick_cell<LAY>(A, pv, cell_index(xt[0], P.lo[0], P.h[0], P.n[0]),
-                                  cell_index(xt[1], P.lo[1], P.h[1], P.n[1]), cell_index(xt[2], P.lo[2], P.h[2], P.n[2]));
-            done = true;
-        } else if (c2 == kTapFace) {
-            const DFaceXf X = A.face_xf[6 * leaf + 2 * a + (sgn ? 0 : 1)];
-            if (X.n[0] > 0) {
-                const float qo[3] = {qt[0] * X.r + X.t[0], qt[1] * X.r + X.t[1], qt[2] * X.r + X.t[2]};
-                int co[3];
-                bool clear = true;
-                #pragma unroll
-                for (int b = 0; b < 3; b++) {
-                    const float u = qo[b] + 0.5f, fl = floorf(u), fr = u - fl;
-                    clear = clear && fr >= kTapMargin && fr <= 1.f - kTapMargin;
-                    co[b] = min(max((int)fl, 0), X.n[b] - 1);
-                }
-                if (clear) {
-                    const PatchView pv = patch_view<LAY>(A, X);
-                    val = brick_cell<LAY>(A, pv, co[0], co[1], co[2]);
-                    if (REC) cnt.face++;
-                    done = true;
-                }
-            } else if (X.rope > 0) {
-                from = (uint32_t)X.rope;
+    const int a = t >> 1, sgn = t & 1;
+    double xt[3];
+    tap_point(A, patch, xs, a, sgn, xt);
+    int c = !out ? kTapSame : (face ? kTapFace : kTapUnsure);
+    if (c == kTapUnsure) {
+        if (REC) cnt.unsure++;
+        c = classify_tap_fp64(A, leaf, patch, safe, xt, a, sgn);
+    }
+    uint32_t from = 0;
+    if (c == kTapSame) {
+        // the tap lies where the sample's own patch is the finest: its cell, in FP64
+        const PatchView pv = patch_view<LAY>(A, P);
+        val = brick_cell<LAY>(A, pv, cell_index(xt[0], P.lo[0], P.h[0], P.n[0]), cell_index(xt[1], P.lo[1], P.h[1], P.n[1]),
+                              cell_index(xt[2], P.lo[2], P.h[2], P.n[2]));
+        return true;
+    }
+    if (c == kTapFace) {
+        const DFaceXf X = A.face_xf[6 * leaf + 2 * a + (sgn ? 0 : 1)];
+        if (X.n[0] > 0) {
+            int co[3];
+            bool clear = true;
+            #pragma unroll
+            for (int b = 0; b < 3; b++) {
+                const float qt = q[b] + (b == a ? (sgn ? -1.f : 1.f) : 0.f);
+                const float u = qt * X.r + X.t[b] + 0.5f, fl = floorf(u), fr = u - fl;
+                clear = clear && fr >= kTapMargin && fr <= 1.f - kTapMargin;
+                co[b] = min(max((int)fl, 0), X.n[b] - 1);
             }
-        }
-        if (!done) ok = nearest_at<REC, LAY>(A, xt, &val, cnt, from);
-        if (!ok) okbits &= ~(1u << t);
-        #pragma unroll
-        for (int b = 0; b < 3; b++) {
-            Fp[b] = (t == 2 * b) ? val : Fp[b];
-            Fm[b] = (t == 2 * b + 1) ? val : Fm[b];
+            if (clear) {
+                val = brick_cell<LAY>(A, patch_view<LAY>(A, X), co[0], co[1], co[2]);
+                if (REC) cnt.face++;
+                return true;
+            }
+        } else if (X.rope > 0) {
+            from = (uint32_t)X.rope;
         }
     }
-    return okbits;
+    return nearest_at<REC, LAY>(A, xt, &val, cnt, from);
 }
 
 // Normalised-value gradient by central differences of the taps, one-sided where a tap holds no
@@ -1308,6 +1301,12 @@ __device__ __forceinline__ int composite_unlit_quad(const RenderArgs &A, const f
 // queue could not take the next samples that will wait (their taps are classified before their
 // stencils are read), the calling lanes resolve all queued samples together, one per lane: the
 // queue holds one wave's worth, so a resolution is one round of nearly full lanes.
+// TapQueueList: one tap per lane instead, when the queued taps fill a wave, so a resolution takes the
+// chain of one tap (face record or descent, then a brick read) and not that of the sample with the
+// most.  Nearest-cell samples have up to six pending (901x677 lit: 3.48 -> 3.01 ms), and a
+// checkpointed forward also writes each resolved sample's record (fit step of eight 384x384 views:
+// 11.5 -> 11.0 ms).  Other trilinear frames have 1.3 per queued sample and pay more for the list
+// than they gain: 517x389 1.46 -> 1.49 ms, a persistent batch of 12 views 15.5 -> 15.7 ms.
 //
 // Each lane sums the colour of its samples in two accumulators, each in its own sample order: the
 // samples shaded at once (in registers), and the deferred ones (in LDS, added per owner lane in
@@ -1323,16 +1322,26 @@ struct TapQueue {
     float ta[kTapQ], lf[kTapQ];    // T alpha; LUT fraction
     int32_t leaf[kTapQ], patch[kTapQ];
     uint32_t meta[kTapQ];          // owner lane | taps' face << 6 | out << 12 | LUT index << 18 | safe faces << 26
-    uint32_t pend[kTapQ];          // taps left to resolve (bit t)
+    uint32_t pend[kTapQ];          // taps left to resolve (bit t) | tape position << 6
     float cd[3][64];               // per lane: colour of its resolved deferred samples
-    uint32_t count, pad_;
+    uint32_t count, taps;          // queued samples; one tap per lane: their taps
     unsigned long long bstart[2];  // bit j: the samples queued by one step start at slot j
 };
 
+constexpr int kTapList = 6 * kTapQ;
+struct TapQueueList : TapQueue {   // with the list of taps that a resolution hands to the lanes
+    float val[kTapList];           // a resolved tap's value
+    uint16_t tap[kTapList];        // slot | t << 6; resolved: | 512 where it holds data
+    uint16_t first[kTapQ];         // a sample's first tap
+};
+
+template <class TQ>
+constexpr bool kTapPerLane = std::is_same_v<TQ, TapQueueList>;
+
 // The block's queues (NW waves); a kernel that never calls this allocates no LDS for them.
-template <int NW>
-__device__ __forceinline__ TapQueue *tap_queues() {
-    __shared__ TapQueue q[NW];
+template <int NW, class TQ>
+__device__ __forceinline__ TQ *tap_queues() {
+    __shared__ TQ q[NW];
     return q;
 }
 
@@ -1346,12 +1355,44 @@ __device__ __forceinline__ uint32_t tq_count(TapQueue &Q) {
     return __hip_atomic_load(&Q.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
+__device__ __forceinline__ uint32_t tq_taps(TapQueue &Q) {
+    return __hip_atomic_load(&Q.taps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
+// The sum of the active lanes' n <= 7, and the sum over the lanes below this one.
+struct LaneSum {
+    uint32_t all, below;
+};
+__device__ __forceinline__ LaneSum lane_sum(uint32_t n, int lane) {
+    LaneSum r{0u, 0u};
+    const unsigned long long low = lanes_below(lane);
+    #pragma unroll
+    for (int b = 0; b < 3; b++) {
+        const unsigned long long m = __ballot((n >> b) & 1u);
+        r.all += popc64(m) << b;
+        r.below += popc64(m & low) << b;
+    }
+    return r;
+}
+
+// Whether the queue must be resolved before the active lanes queue their next samples, each with the
+// taps `pend` pending (0: none to queue).  One tap per lane: when the taps would overfill a wave
+// (each queued sample has one at least, so the samples fit too).
+template <class TQ>
+__device__ __forceinline__ bool tq_due(TQ &Q, uint32_t pend, int lane) {
+    if (!kTapPerLane<TQ>) return tapq_full(tq_count(Q), __ballot(pend != 0u));
+    const uint32_t taps = tq_taps(Q);
+    return taps > 0u && taps + lane_sum(popc64(pend), lane).all > (uint32_t)kTapQ;
+}
+
 __device__ __forceinline__ unsigned long long tq_bstart(TapQueue &Q, int w) {
     return __hip_atomic_load(&Q.bstart[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
-__device__ __forceinline__ void tq_set(TapQueue &Q, uint32_t count, unsigned long long b0, unsigned long long b1) {
+__device__ __forceinline__ void tq_set(TapQueue &Q, uint32_t count, uint32_t taps, unsigned long long b0,
+                                       unsigned long long b1) {
     __hip_atomic_store(&Q.count, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __hip_atomic_store(&Q.taps, taps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     __hip_atomic_store(&Q.bstart[0], b0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     __hip_atomic_store(&Q.bstart[1], b1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
@@ -1361,7 +1402,50 @@ __device__ __forceinline__ void tapq_init(TapQueue &Q, int lane) {
     Q.cd[0][lane] = 0.f;
     Q.cd[1][lane] = 0.f;
     Q.cd[2][lane] = 0.f;
-    if (lane == 0) tq_set(Q, 0u, 0ull, 0ull);
+    if (lane == 0) tq_set(Q, 0u, 0u, 0ull, 0ull);
+    wave_lds_fence();
+}
+
+// The queued taps, listed sample by sample and resolved one per lane (rank of nact).
+template <bool REC, int LAY, bool NEAR>
+__device__ __forceinline__ void tapq_resolve_list(const RenderArgs &A, TapQueueList &Q, uint32_t n, uint32_t rank,
+                                                  uint32_t nact, Counters &cnt) {
+    const uint32_t ntaps = min(tq_taps(Q), (uint32_t)kTapList);
+    for (uint32_t j = rank; j < n; j += nact) {
+        uint32_t todo = Q.pend[j] & 63u, at = Q.first[j];
+        while (todo) {
+            const uint32_t t = (uint32_t)__builtin_ctz(todo);
+            todo &= todo - 1u;
+            if (at < (uint32_t)kTapList) Q.tap[at] = (uint16_t)(j | (t << 6));     // always
+            at++;
+        }
+    }
+    wave_lds_fence();
+    for (uint32_t i = rank; i < ntaps; i += nact) {
+        const uint32_t e = Q.tap[i], j = e & 63u;
+        const int t = (int)(e >> 6) & 7;
+        const double xs[3] = {Q.xs[0][j], Q.xs[1][j], Q.xs[2][j]};
+        const float q[3] = {Q.q[0][j], Q.q[1][j], Q.q[2][j]};
+        const uint32_t m = Q.meta[j], safe = m >> 26;
+        const bool face = (m >> (6 + t)) & 1u, out = (m >> (12 + t)) & 1u;
+        const int leaf = Q.leaf[j], patch = Q.patch[j];
+        float val = 0.f;
+        bool ok = false;
+        if ((uint32_t)leaf < (uint32_t)A.nrec && (uint32_t)patch < (uint32_t)A.npatches) {   // always
+            if (NEAR) {
+                ok = resolve_tap_nearest<REC, LAY>(A, leaf, patch, safe, xs, q, t, out, face, val, cnt);
+            } else {
+                PatchView pv;
+                float q0, q1, q2;
+                ok = tap_brick<REC, LAY>(A, leaf, patch, safe, nullptr, xs, q[0], q[1], q[2], t, face, pv, q0, q1, q2, cnt);
+                if (ok) val = trilinear<REC, LAY>(A, pv, q0, q1, q2);
+            }
+        } else if (REC) {
+            cnt.guard++;
+        }
+        Q.val[i] = val;
+        Q.tap[i] = (uint16_t)(e | (ok ? 512u : 0u));
+    }
     wave_lds_fence();
 }
 
@@ -1371,13 +1455,15 @@ __device__ __forceinline__ void tapq_init(TapQueue &Q, int lane) {
 // also written to the owner ray's tape at the sample's position, so the adjoint need not evaluate
 // it again.  tape_base: the tape row (ray) of lane 0; lane o's ray is o / 4 of the wave's 4x4
 // pixels, row tape_base + (o / 16) * width + (o / 4) % 4.
-template <bool REC, int LAY = -1, bool NEAR = false, bool TAPE = false>
-__device__ __forceinline__ void tapq_flush(const RenderArgs &A, const float4 *s_lut, TapQueue &Q, int lane,
+template <bool REC, int LAY = -1, bool NEAR = false, bool TAPE = false, class TQ>
+__device__ __forceinline__ void tapq_flush(const RenderArgs &A, const float4 *s_lut, TQ &Q, int lane,
                                            Counters &cnt, int64_t tape_base = -1) {
     const unsigned long long act = __ballot(1);
     const uint32_t nact = popc64(act), rank = popc64(act & lanes_below(lane));
     wave_lds_fence();
     const uint32_t n = tq_count(Q);
+    static_assert(!NEAR || kTapPerLane<TQ>);
+    if constexpr (kTapPerLane<TQ>) tapq_resolve_list<REC, LAY, NEAR>(A, Q, n, rank, nact, cnt);
     for (uint32_t j = rank; j < n; j += nact) {
         const double xs[3] = {Q.xs[0][j], Q.xs[1][j], Q.xs[2][j]};
         const float F = Q.g[0][j];
@@ -1391,15 +1477,22 @@ __device__ __forceinline__ void tapq_flush(const RenderArgs &A, const float4 *s_
             Fm[a] = v;
         }
         const int leaf = Q.leaf[j], patch = Q.patch[j];
-        uint32_t ok = 0u;
-        if ((uint32_t)leaf < (uint32_t)A.nrec && (uint32_t)patch < (uint32_t)A.npatches) {   // always
-            if (NEAR) {
-                const float q[3] = {Q.q[0][j], Q.q[1][j], Q.q[2][j]};
-                ok = resolve_taps_nearest<REC, LAY>(A, leaf, patch, safe, xs, q, out, face, pend, Fp, Fm, cnt);
-            } else {
-                ok = resolve_taps<REC, LAY>(A, leaf, patch, safe, nullptr, xs, Q.q[0][j], Q.q[1][j], Q.q[2][j], out,
-                                            face, Fp, Fm, cnt);
+        uint32_t ok = kTapPerLane<TQ> ? 0x3fu : 0u;
+        if constexpr (kTapPerLane<TQ>) {
+            uint32_t at = Q.first[j];
+            #pragma unroll
+            for (int t = 0; t < 6; t++) {
+                if (pend & (1u << t)) {
+                    const uint32_t i = min(at, (uint32_t)kTapList - 1u);
+                    if (t & 1) Fm[t >> 1] = Q.val[i];
+                    else Fp[t >> 1] = Q.val[i];
+                    if (!(Q.tap[i] & 512u)) ok &= ~(1u << t);
+                    at++;
+                }
             }
+        } else if ((uint32_t)leaf < (uint32_t)A.nrec && (uint32_t)patch < (uint32_t)A.npatches) {   // always
+            ok = resolve_taps<REC, LAY>(A, leaf, patch, safe, nullptr, xs, Q.q[0][j], Q.q[1][j], Q.q[2][j], out, face,
+                                        Fp, Fm, cnt);
         } else if (REC) {
             cnt.guard++;
         }
@@ -1444,7 +1537,7 @@ __device__ __forceinline__ void tapq_flush(const RenderArgs &A, const float4 *s_
             wave_lds_fence();
         }
     }
-    if (rank == 0) tq_set(Q, 0u, 0ull, 0ull);
+    if (rank == 0) tq_set(Q, 0u, 0u, 0ull, 0ull);
     wave_lds_fence();
 }
 
@@ -1454,8 +1547,8 @@ __device__ __forceinline__ void tapq_flush(const RenderArgs &A, const float4 *s_
 // finished central difference, else as the in-brick side's value.
 // ord: the sample's tape position (below 2^26; tape_cap, which is never written, when beyond it;
 // 0 without a tape).
-template <bool REC>
-__device__ __forceinline__ void tapq_push(const RenderArgs &A, TapQueue &Q, int lane, bool want, const Ray &R,
+template <bool REC, class TQ>
+__device__ __forceinline__ void tapq_push(const RenderArgs &A, TQ &Q, int lane, bool want, const Ray &R,
                                           const Segment &S, int k, const double *xs_known, float qx, float qy,
                                           float qz, float F, const float Fp[3], const float Fm[3], TapMask tm,
                                           uint32_t pend, float Ta, const SampleVals &v, Counters &cnt,
@@ -1464,6 +1557,12 @@ __device__ __forceinline__ void tapq_push(const RenderArgs &A, TapQueue &Q, int 
     if (!need) return;
     const unsigned long long act = __ballot(1);
     const uint32_t c0 = tq_count(Q);
+    uint32_t t0 = 0u;
+    LaneSum ts{0u, 0u};
+    if (kTapPerLane<TQ>) {
+        t0 = tq_taps(Q);
+        ts = lane_sum(want ? popc64(pend) : 0u, lane);
+    }
     if (want) {
         if (REC) cnt.split++;
         const uint32_t j = tapq_slot(c0, need, lane);
@@ -1494,6 +1593,7 @@ __device__ __forceinline__ void tapq_push(const RenderArgs &A, TapQueue &Q, int 
             Q.patch[j] = S.patch;
             Q.meta[j] = (uint32_t)lane | (tm.face << 6) | (tm.out << 12) | ((uint32_t)v.i0 << 18) | (S.safe << 26);
             Q.pend[j] = pend | (ord << 6);
+            if constexpr (kTapPerLane<TQ>) Q.first[j] = (uint16_t)(t0 + ts.below);
         } else if (REC) {
             cnt.guard++;
         }
@@ -1501,7 +1601,7 @@ __device__ __forceinline__ void tapq_push(const RenderArgs &A, TapQueue &Q, int 
     wave_lds_fence();
     if (lane == (int)ctz64(act) && c0 < (uint32_t)kTapQ) {
         const TapqStarts b = tapq_mark(tq_bstart(Q, 0), tq_bstart(Q, 1), c0);
-        tq_set(Q, tapq_count_after(c0, need), b.w0, b.w1);
+        tq_set(Q, tapq_count_after(c0, need), t0 + ts.all, b.w0, b.w1);
     }
     wave_lds_fence();
 }
@@ -1555,8 +1655,8 @@ __device__ __forceinline__ LitPoint lit_point(const RenderArgs &A, const Ray &R,
 // trow, tpos (checkpointed forward with a tape): the ray's tape row and the position of the quad's
 // first sample in it, advanced here; a sample shaded at once writes its record now, a queued one
 // when resolved.
-template <bool REC, int LAY, bool NEAR>
-__device__ __forceinline__ QuadStep lit_step(const RenderArgs &A, const float4 *s_lut, TapQueue &Q, int lane,
+template <bool REC, int LAY, bool NEAR, class TQ>
+__device__ __forceinline__ QuadStep lit_step(const RenderArgs &A, const float4 *s_lut, TQ &Q, int lane,
                                              const Ray &R, const Segment &S, int k, const LitPoint &p, float &T,
                                              float &C0, float &C1, float &C2, Counters &cnt, float4 *trow,
                                              uint32_t &tpos) {
@@ -1602,8 +1702,8 @@ __device__ __forceinline__ QuadStep lit_step(const RenderArgs &A, const float4 *
 
 // After the march, by all lanes of the wave: resolve what is queued; returns the lane's
 // deferred colour.
-template <bool REC, int LAY = -1, bool NEAR = false, bool TAPE = false>
-__device__ __forceinline__ void tapq_finish(const RenderArgs &A, const float4 *s_lut, TapQueue &Q, int lane,
+template <bool REC, int LAY = -1, bool NEAR = false, bool TAPE = false, class TQ>
+__device__ __forceinline__ void tapq_finish(const RenderArgs &A, const float4 *s_lut, TQ &Q, int lane,
                                             Counters &cnt, float &D0, float &D1, float &D2, int64_t tape_base = -1) {
     if (tq_count(Q)) tapq_flush<REC, LAY, NEAR, TAPE>(A, s_lut, Q, lane, cnt, tape_base);
     wave_lds_fence();
