@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
         uint32_t start = 0;
         while (alive && tcur < R.t1) {
             double tb = R.t1;
-            int leaf = descend(A, R, tcur, tb, start);
+            int leaf = descend<true>(A, R, tcur, tb, start);
             if (leaf < 0) break;
             if (REC && sub == 0) cnt.segments++;
             const DLeaf &L = A.leaves[leaf];

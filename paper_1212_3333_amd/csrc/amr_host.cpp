@@ -849,6 +849,15 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
     std::vector<int32_t> anodes;
     for (int32_t i : T->preorder)
         if (T->kind[i] == 0) { aidx[i] = (int32_t)anodes.size(); anodes.push_back(i); }
+    // per node, the finest kind-(a) node above it
+    std::vector<int32_t> above(T->nodes.size(), -1);
+    for (int32_t i : T->preorder) {
+        const Node &n = T->nodes[i];
+        if (n.axis < 0) continue;
+        int32_t v = above[i];
+        if (aidx[i] >= 0 && (v < 0 || T->plevel[n.cover] >= T->plevel[T->nodes[v].cover])) v = i;
+        above[n.low] = above[n.high] = v;
+    }
     const int64_t na = (int64_t)anodes.size(), nl = nl0 + na;
     const int64_t o_nodes = 0;
     const int64_t o_leaves = align_up(o_nodes + nn * (int64_t)sizeof(DNode), 256);
@@ -1011,7 +1020,10 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
                 for (int f = 0; f < 6; f++) own[f] = -2;
                 L.level_flags = (uint32_t)T->plevel[np_k];
             } else {
-                L.level_flags = (uint32_t)n.level | (face_owners(T, n, bfs_index, own) << 8);
+                const int32_t v = above[T->leaves[k]];
+                const uint32_t up = v < 0 ? 1u : (uint32_t)aidx[v] + 2u;
+                L.level_flags = (uint32_t)n.level | (face_owners(T, n, bfs_index, own) << 8) |
+                                ((up >> (32 - kLeafLodShift) ? 0u : up) << kLeafLodShift);
             }
             L.vmin = 0.0f;
             L.vmax = 0.0f;

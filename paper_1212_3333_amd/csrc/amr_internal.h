@@ -26,9 +26,12 @@ static_assert(sizeof(DNode) == 16, "DNode layout");
 struct DLeaf {
     double lo[3], hi[3];
     int32_t patch;
-    uint32_t level_flags;
+    uint32_t level_flags;    // level | safe faces << 8 | finest kind-(a) node above << kLeafLodShift
     float vmin, vmax;
 };
+// Leaves: 2 + k for level-of-detail record k, 1 where no node above is one, 0 where it is not known
+// (more records than the field holds, leaves drawn from a coarser patch than their own).
+constexpr int kLeafLodShift = 14;
 static_assert(sizeof(DLeaf) == 64, "DLeaf layout");
 
 // Patch header, 128 bytes.

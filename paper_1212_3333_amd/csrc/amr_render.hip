@@ -188,10 +188,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
                     while (true) {            // next segment with samples, or the end of the ray
                         if (!(tcur < R.t1)) { alive = false; break; }
                         double tb = R.t1;
-                        const int leaf = descend(A, R, tcur, tb, start);
+                        const int leaf = descend<true>(A, R, tcur, tb, start);
                         if (leaf < 0) { alive = false; break; }
                         if (REC && lead) cnt.segments++;
-                        if (REC && A.touch_meta) touch_segment_meta(A, R, tcur, leaf);
+                        if (REC && A.touch_meta && lead) touch_segment_meta(A, R, tcur, leaf);
                         const DLeaf &L = A.leaves[leaf];
                         const int p = L.patch;
                         int n = 0;
@@ -244,10 +244,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
         uint32_t start = 0;
         while (alive && tcur < R.t1) {
             double tb = R.t1;
-            int leaf = descend(A, R, tcur, tb, start);
+            int leaf = descend<true>(A, R, tcur, tb, start);
             if (leaf < 0) break;
             if (REC && lead) cnt.segments++;
-            if (REC && A.touch_meta) touch_segment_meta(A, R, tcur, leaf);
+            if (REC && A.touch_meta && lead) touch_segment_meta(A, R, tcur, leaf);
             const DLeaf &L = A.leaves[leaf];
             const int p = L.patch;
             int nsm = 0;
