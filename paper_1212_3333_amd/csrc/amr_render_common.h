@@ -394,19 +394,18 @@ __device__ __forceinline__ bool lod_clear(const RenderArgs &A, int leaf, double 
 // learned and in-place adjoint kernels keep the walk: the second form cost the learned kernel 20 %.
 template <bool LODROPE = false>
 __device__ __forceinline__ int descend(const RenderArgs &A, const Ray &R, double tmin, double &tmax, uint32_t &start) {
-    if (!A.lod_on) return descend_rope(A, R, tmin, tmax, start);
-    if (!LODROPE) return descend_walk<true>(A, R, tmin, tmax);
-    double tb = tmax;
-    if (start) {
+    if (!LODROPE && A.lod_on) return descend_walk<true>(A, R, tmin, tmax);
+    if (!A.lod_on || start) {
+        double tb = tmax;
         const int leaf = descend_rope(A, R, tmin, tb, start);
-        if (leaf >= 0 && lod_clear(A, leaf, tmin)) {
+        if (!A.lod_on || (leaf >= 0 && lod_clear(A, leaf, tmin))) {
             tmax = tb;
             return leaf;
         }
-        tb = tmax;
-        start = 0;
     }
+    double tb = tmax;
     const int leaf = descend_walk<true>(A, R, tmin, tmax);
+    start = 0;
     if (leaf >= 0 && leaf < A.nleaves) leaf_exit(A, R, leaf, tmin, tb, start);
     return leaf;
 }
