@@ -594,7 +594,10 @@ def main():
             return dict(bound="hbm", achieved=round(achieved, 2), peak=HBM_PEAK_GBS, unit="GB/s",
                         frac=round(achieved / HBM_PEAK_GBS, 5), traffic=c["traffic"] if c else None,
                         kernel="render_fwd<%s, REC=false, NEAR=false, LAY=%d>" % ("LIT" if lit else "UNLIT",
-                                                                                  args.brick_layout),
+                                                                                  # 3: halo rows below 4 GB
+                                                                                  3 if args.brick_layout == 2 and
+                                                                                  scene.scene.pool_bytes < 1 << 32
+                                                                                  else args.brick_layout),
                         ms=round(t_ms, 4), algorithmic_bytes=int(b_alg), distinct_cells=int(cells),
                         metadata_bytes_read=int(meta), distinct_line_bytes=128 * lines,
                         gather_request_bytes=int(gather), algorithmic_flops=int(flops),
