@@ -703,6 +703,50 @@ void run_threads(int n, F &work) {
     for (auto &x : th) x.join();
 }
 
+// The GPU whose memory p lies in; -1 for host and managed memory.
+int device_of(const void *p) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return -1;
+    }
+    return at.type == hipMemoryTypeDevice ? at.device : -1;
+}
+
+// Makes GPU `want` the calling thread's current device, until `back` or the end of the scope.
+struct CurrentDevice {
+    int saved = -1;
+    bool enter(int want) {
+        int cur = -1;
+        if (hipGetDevice(&cur) != hipSuccess) return false;
+        if (cur == want) return true;
+        if (hipSetDevice(want) != hipSuccess) return false;
+        saved = cur;
+        return true;
+    }
+    void back() {
+        if (saved >= 0) (void)hipSetDevice(saved);
+        saved = -1;
+    }
+    ~CurrentDevice() { back(); }
+};
+
+// The GPU that can pack into d_pool and d_meta by kernels on `stream`: both lie in its memory and the
+// stream is its own (the null stream is every GPU's); -1 where there is none.
+int packing_device(const void *d_pool, const void *d_meta, void *stream) {
+    const int dev = device_of(d_pool);
+    if (dev < 0 || device_of(d_meta) != dev) return -1;
+    if (stream) {
+        hipDevice_t own = -1;
+        if (hipStreamGetDevice((hipStream_t)stream, &own) != hipSuccess) {
+            (void)hipGetLastError();
+            return -1;
+        }
+        if (own != dev) return -1;
+    }
+    return dev;
+}
+
 // What the packing kernels need to know of the patches: where cells, shells and bricks lie, the boxes
 // and the neighbours (pk.nbr) that the ghost layers draw from.
 void plan_device(const amr_tree *T, const amr_patch *patches, int np, int layout, const std::vector<int64_t> &off,
@@ -884,11 +928,15 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
     bool host_dst = opts && opts->host_dst;
 
     // Cell-centred patches bound for the GPU are packed there (amr_pack.hip) from the cells as they
-    // are; the host packs for host memory, vertex-centred data, an unaligned pool, and where the GPU
-    // has no room to stage the cells.  Both form the same bytes.
+    // are; the host packs for host memory, vertex-centred data, an unaligned pool, buffers or a stream
+    // of different GPUs (copies reach any of them, kernels do not), and where the GPU has no room to
+    // stage the cells.  Both form the same bytes.
     PackPlan plan;
+    CurrentDevice current;             // restored after the stage is freed
     PackStage stage;
     bool device = !host_dst && !vertex && ((uintptr_t)d_pool & 15u) == 0;
+    const int dev = device ? packing_device(d_pool, d_meta, stream) : -1;
+    device = dev >= 0 && current.enter(dev);
     struct StageGuard {
         PackStage *st;
         ~StageGuard() { pack_stage_free(st); }
@@ -910,12 +958,11 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
             pk.neighbours(nthreads);
             plan_device(T, patches, np, layout, off, nfl, pk, plan);
             device = pack_stage_alloc(plan, nl, &stage);
+            if (!device) current.back();       // the copies are enqueued as the caller's device has it
         }
         if (device) {
             // the cells travel while the tree and the records below are written
-            int dev = 0;
-            (void)hipGetDevice(&dev);
-            uploader = std::thread([&, dev]() {
+            uploader = std::thread([&]() {
                 try {
                     upload_rc = pack_upload_cells(plan, stage, dev);
                     if (upload_rc) upload_err = g_err;

@@ -1,0 +1,103 @@
+// A stand-in for the HIP runtime in host tests: memory of two GPUs is host memory tagged with a device,
+// copies are memcpy, kernels are not run, and every call that touches a GPU is logged with the thread's
+// current device.  Loaded before libamr.so, whose references it then satisfies.
+#include <hip/hip_runtime_api.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <mutex>
+#include <string>
+
+namespace {
+std::mutex g_mutex;
+std::string g_log;
+std::map<const char *, std::pair<size_t, int>> g_mem;      // address -> bytes, device
+std::map<void *, int> g_streams;
+thread_local int g_device = 0;
+int g_fail_malloc = 0;
+thread_local dim3 t_grid, t_block;
+thread_local size_t t_shared;
+thread_local hipStream_t t_stream;
+
+void say(const char *what) {
+    std::lock_guard<std::mutex> l(g_mutex);
+    char b[96];
+    snprintf(b, sizeof(b), "%s %d\n", what, g_device);
+    g_log += b;
+}
+
+int owner(const void *p) {
+    std::lock_guard<std::mutex> l(g_mutex);
+    auto it = g_mem.upper_bound((const char *)p);
+    if (it == g_mem.begin()) return -1;
+    --it;
+    return (const char *)p < it->first + it->second.first ? it->second.second : -1;
+}
+
+void *give(size_t n, int dev) {
+    char *p = (char *)aligned_alloc(256, (n + 255) / 256 * 256);
+    std::lock_guard<std::mutex> l(g_mutex);
+    g_mem[p] = {n, dev};
+    return p;
+}
+
+void take(void *p) {
+    std::lock_guard<std::mutex> l(g_mutex);
+    g_mem.erase((const char *)p);
+    free(p);
+}
+}  // namespace
+
+extern "C" {
+
+void *fake_alloc(size_t n, int dev) { return give(n, dev); }
+void fake_release(void *p) { take(p); }
+void fake_stream(void *s, int dev) { g_streams[s] = dev; }
+void fake_fail_malloc(int on) { g_fail_malloc = on; }
+long fake_held() { return (long)g_mem.size(); }
+const char *fake_log() { return g_log.c_str(); }
+void fake_clear() { g_log.clear(); }
+
+hipError_t hipGetDevice(int *d) { *d = g_device; return hipSuccess; }
+hipError_t hipSetDevice(int d) { g_device = d; return hipSuccess; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p) {
+    memset(a, 0, sizeof(*a));
+    const int d = owner(p);
+    if (d < 0) return hipErrorInvalidValue;
+    a->type = hipMemoryTypeDevice;
+    a->device = d;
+    a->devicePointer = (void *)p;
+    return hipSuccess;
+}
+hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t *d) {
+    auto it = g_streams.find((void *)s);
+    if (it == g_streams.end()) return hipErrorInvalidHandle;
+    *d = it->second;
+    return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t n) {
+    say("malloc");
+    if (g_fail_malloc) return hipErrorOutOfMemory;
+    *p = give(n, g_device);
+    return hipSuccess;
+}
+hipError_t hipFree(void *p) { say("free"); take(p); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t) {
+    say("copy");
+    memcpy(dst, src, n);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t m, hipStream_t s) {
+    t_grid = g, t_block = b, t_shared = m, t_stream = s;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *m, hipStream_t *s) {
+    *g = t_grid, *b = t_block, *m = t_shared, *s = t_stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { say("launch"); return hipSuccess; }
+}

@@ -1,0 +1,53 @@
+"""Which GPU amr_pack_pool allocates, copies and launches on, with two GPUs played on the host
+(fake_hip.cpp): kernels run only where the pool, the metadata and the stream belong to one GPU, and on
+that GPU; the caller's current device is what it was afterwards, and nothing stays allocated.  Any other
+combination is packed on the host and copied."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("g++ not available")
+    lib = str(tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so")
+    r = subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
+                        os.path.join(HERE, "fake_hip.cpp"), "-o", lib], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return lib
+
+
+def run(fake, pool, meta, stream, current, fail_malloc=0):
+    r = subprocess.run([sys.executable, os.path.join(HERE, "_fake_hip_run.py"), fake] +
+                       [str(v) for v in (pool, meta, stream, current, fail_malloc)], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+    lines = r.stdout.strip().splitlines()
+    assert lines[-1] == "end rc=0 current=%d leaked=0" % current, r.stdout
+    return [(w, int(d)) for w, d in (ln.split() for ln in lines[:-1])]
+
+
+@pytest.mark.parametrize("current", [0, 1])
+@pytest.mark.parametrize("stream", [-1, 1])
+def test_packs_on_the_gpu_of_the_pool(fake, stream, current):
+    calls = run(fake, 1, 1, stream, current)
+    assert sum(w == "launch" for w, _ in calls) >= 3 and any(w == "copy" for w, _ in calls)
+    assert {d for _, d in calls} == {1}
+
+
+@pytest.mark.parametrize("pool,meta,stream", [(1, 1, 0), (0, 0, 1), (0, 1, 0), (1, 0, -1), (1, -1, -1)])
+def test_packs_on_the_host_across_gpus(fake, pool, meta, stream):
+    calls = run(fake, pool, meta, stream, 0)
+    assert {w for w, _ in calls} == {"copy"}
+
+
+def test_packs_on_the_host_without_room(fake):
+    calls = run(fake, 1, 1, -1, 0, fail_malloc=1)
+    assert not any(w == "launch" for w, _ in calls)
+    assert {d for w, d in calls if w == "copy"} == {0}          # as the caller's device has it
