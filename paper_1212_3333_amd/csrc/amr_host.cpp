@@ -21,6 +21,7 @@
 
 #include "amr_internal.h"
 #include "amr_pack.h"
+#include "amr_threads.h"
 
 namespace amr {
 
@@ -476,9 +477,10 @@ struct Packer {
                 for (int y = cell_of(1, b.lo[1]); y <= cell_of(1, b.hi[1]); y++)
                     for (int x = cell_of(0, b.lo[0]); x <= cell_of(0, b.hi[0]); x++) bins[(size_t)x + G * (y + G * z)].push_back(q);
         }
-        auto work = [&](int t) {
+        std::atomic<int> next{0};
+        auto work = [&]() {
             std::vector<char> seen(np, 0);
-            for (int p = t; p < np; p += nthreads) {
+            for (int p; (p = next.fetch_add(1)) < np;) {
                 int64_t S = T->scale[T->plevel[p]];
                 int64_t lo[3], hi[3];
                 for (int a = 0; a < 3; a++) { lo[a] = T->pbox[p].lo[a] - S; hi[a] = T->pbox[p].hi[a] + S; }
@@ -496,9 +498,7 @@ struct Packer {
                 for (int q : out) seen[q] = 0;
             }
         };
-        std::vector<std::thread> th;
-        for (int t = 0; t < nthreads; t++) th.emplace_back(work, t);
-        for (auto &x : th) x.join();
+        run_threads(nthreads, work);
     }
 
     // Vertex-centred data (Section 5).  Patch owning the finest-level cell c: the kD leaf
@@ -595,9 +595,7 @@ struct Packer {
                     else fill_patch(ids[k]);
                 }
             };
-            std::vector<std::thread> th;
-            for (int t = 0; t < nthreads; t++) th.emplace_back(work);
-            for (auto &x : th) x.join();
+            run_threads(nthreads, work);
         }
     }
 };
@@ -693,15 +691,6 @@ double world_plane(const amr_tree *T, int a, int64_t G) {
 }
 
 int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
-
-// `work` on n threads, the calling one among them.
-template <typename F>
-void run_threads(int n, F &work) {
-    std::vector<std::thread> th;
-    for (int t = 1; t < n; t++) th.emplace_back([&]() { work(); });
-    work();
-    for (auto &x : th) x.join();
-}
 
 // The GPU whose memory p lies in; -1 for host and managed memory.
 int device_of(const void *p) {
@@ -865,7 +854,7 @@ void amr_tree_free(amr_tree *T) { delete T; }
 
 int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches, const amr_pack_opts *opts,
                   void *d_pool, int64_t *pool_bytes, void *d_meta, int64_t *meta_bytes, amr_scene *out,
-                  void *stream) {
+                  void *stream) try {
     if (!T || !patches || !pool_bytes || !meta_bytes) { set_error("null argument"); return AMR_EINVAL; }
     if (npatches != (int32_t)T->pbox.size()) { set_error("npatches differs from the tree's"); return AMR_EINVAL; }
     const int np = npatches;
@@ -946,7 +935,7 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
     std::vector<uint8_t> meta;
     int upload_rc = AMR_OK;
     std::string upload_err;
-    try {
+    {
         meta.assign((size_t)mbytes, 0);
         Packer pk{T, patches, np, vertex, {}, {}};
         std::thread uploader;
@@ -962,15 +951,19 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
         }
         if (device) {
             // the cells travel while the tree and the records below are written
-            uploader = std::thread([&]() {
+            auto upload = [&]() {
                 try {
                     upload_rc = pack_upload_cells(plan, stage, dev);
                     if (upload_rc) upload_err = g_err;
-                } catch (const std::exception &e) {      // no thread or memory to copy with
+                } catch (const std::exception &) {
                     upload_rc = AMR_ENOMEM;
-                    upload_err = e.what();
                 }
-            });
+            };
+            try {
+                uploader = std::thread(upload);
+            } catch (const std::system_error &) {        // no thread to be had
+                upload();
+            }
         } else {
             pool.assign((size_t)nfl, 0.0f);
             pk.run(nthreads);
@@ -1180,9 +1173,9 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
             out->hfine[a] = T->dom.h0[a] / (double)T->scale[0];
         }
         if (device) {
-            uploader.join();
+            if (uploader.joinable()) uploader.join();
             if (upload_rc) {
-                set_error("%s", upload_err.c_str());
+                set_error("%s", upload_err.empty() ? "out of host memory" : upload_err.c_str());
                 return upload_rc;
             }
             const int rc = pack_run(plan, stage, d_pool, d_meta, meta.data(), mbytes, o_leaves, o_patch, &vmin, &vmax, stream);
@@ -1190,9 +1183,6 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
         }
         out->v_min = vmin;
         out->v_max = vmax;
-    } catch (const std::bad_alloc &) {
-        set_error("out of host memory");
-        return AMR_ENOMEM;
     }
     if (device) return AMR_OK;
     if (host_dst) {
@@ -1206,6 +1196,9 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) { set_error("HIP copy failed: %s", hipGetErrorString(e)); return AMR_EHIP; }
     return AMR_OK;
+} catch (const std::exception &) {       // of memory; threads that cannot be had are done without
+    set_error("out of host memory");
+    return AMR_ENOMEM;
 }
 
 }  // extern "C"

@@ -10,9 +10,9 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
-#include <thread>
 
 #include "amr_pack.h"
+#include "amr_threads.h"
 
 namespace amr {
 
@@ -310,16 +310,7 @@ int pack_upload_cells(const PackPlan &plan, const PackStage &st, int device) {
         if (e == hipSuccess) e = w;
         if (e != hipSuccess) failed = (int)e;
     };
-    struct Pool {
-        std::vector<std::thread> th;
-        ~Pool() {
-            for (auto &x : th) x.join();
-        }
-    };
-    {
-        Pool pool;
-        for (int t = 0; t < nt; t++) pool.th.emplace_back(work);
-    }
+    run_threads(nt, work);
     return hip_failed((hipError_t)failed.load(), "copy of the cells");
 }
 

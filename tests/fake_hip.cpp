@@ -1,31 +1,42 @@
 // A stand-in for the HIP runtime in host tests: memory of two GPUs is host memory tagged with a device,
 // copies are memcpy, kernels are not run, and every call that touches a GPU is logged with the thread's
-// current device.  Loaded before libamr.so, whose references it then satisfies.
+// current device.  Loaded before libamr.so, whose references it then satisfies.  Also host memory
+// that runs out (on threads other than the one that asks for it) and threads that cannot be started.
 #include <hip/hip_runtime_api.h>
 
+#include <dlfcn.h>
+
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
-#include <string>
+#include <new>
+#include <system_error>
+#include <thread>
 
 namespace {
 std::mutex g_mutex;
-std::string g_log;
+char g_log[1 << 16];
+int g_log_end = 0;
 std::map<const char *, std::pair<size_t, int>> g_mem;      // address -> bytes, device
 std::map<void *, int> g_streams;
 thread_local int g_device = 0;
 int g_fail_malloc = 0;
+std::atomic<long> g_new_left{-1};          // allocations that worker threads still get; -1: no limit
+std::atomic<int> g_threads_left{-1};       // threads that can still be started; -1: no limit
+thread_local bool t_main = false;
 thread_local dim3 t_grid, t_block;
 thread_local size_t t_shared;
 thread_local hipStream_t t_stream;
 
 void say(const char *what) {
     std::lock_guard<std::mutex> l(g_mutex);
-    char b[96];
-    snprintf(b, sizeof(b), "%s %d\n", what, g_device);
-    g_log += b;
+    const int left = (int)sizeof(g_log) - g_log_end;
+    const int n = snprintf(g_log + g_log_end, (size_t)left, "%s %d\n", what, g_device);
+    if (n < left) g_log_end += n;
 }
 
 int owner(const void *p) {
@@ -56,9 +67,10 @@ void *fake_alloc(size_t n, int dev) { return give(n, dev); }
 void fake_release(void *p) { take(p); }
 void fake_stream(void *s, int dev) { g_streams[s] = dev; }
 void fake_fail_malloc(int on) { g_fail_malloc = on; }
+void fake_limits(long news, int threads) { t_main = true; g_new_left = news; g_threads_left = threads; }
 long fake_held() { return (long)g_mem.size(); }
-const char *fake_log() { return g_log.c_str(); }
-void fake_clear() { g_log.clear(); }
+const char *fake_log() { return g_log; }
+void fake_clear() { g_log[g_log_end = 0] = 0; }
 
 hipError_t hipGetDevice(int *d) { *d = g_device; return hipSuccess; }
 hipError_t hipSetDevice(int d) { g_device = d; return hipSuccess; }
@@ -100,4 +112,26 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *m, hipStream_t *s
     return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { say("launch"); return hipSuccess; }
+}
+
+void *operator new(size_t n) {
+    if (!t_main && g_new_left >= 0 && --g_new_left < 0) {
+        g_new_left = 0;
+        throw std::bad_alloc();
+    }
+    void *p = malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
+
+void std::thread::_M_start_thread(_State_ptr state, void (*depend)()) {
+    if (g_threads_left >= 0 && --g_threads_left < 0) {
+        g_threads_left = 0;
+        throw std::system_error(std::make_error_code(std::errc::resource_unavailable_try_again));
+    }
+    using Start = void (*)(std::thread *, _State_ptr, void (*)());
+    static const Start start = (Start)dlsym(RTLD_NEXT, "_ZNSt6thread15_M_start_threadESt10unique_ptrINS_6_StateESt14default_deleteIS1_EEPFvvE");
+    start(this, std::move(state), depend);
 }

@@ -1,7 +1,8 @@
 """Which GPU amr_pack_pool allocates, copies and launches on, with two GPUs played on the host
 (fake_hip.cpp): kernels run only where the pool, the metadata and the stream belong to one GPU, and on
 that GPU; the caller's current device is what it was afterwards, and nothing stays allocated.  Any other
-combination is packed on the host and copied."""
+combination is packed on the host and copied.  Host memory that runs out in a worker thread is an error
+returned, and threads that cannot be started are done without."""
 import os
 import shutil
 import subprocess
@@ -19,17 +20,19 @@ def fake(tmp_path_factory):
         pytest.skip("g++ not available")
     lib = str(tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so")
     r = subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include",
-                        os.path.join(HERE, "fake_hip.cpp"), "-o", lib], capture_output=True, text=True)
+                        os.path.join(HERE, "fake_hip.cpp"), "-o", lib, "-ldl"], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     return lib
 
 
-def run(fake, pool, meta, stream, current, fail_malloc=0):
+def run(fake, pool, meta, stream, current, fail_malloc=0, limit=""):
     r = subprocess.run([sys.executable, os.path.join(HERE, "_fake_hip_run.py"), fake] +
-                       [str(v) for v in (pool, meta, stream, current, fail_malloc)], capture_output=True, text=True, timeout=300)
+                       [str(v) for v in (pool, meta, stream, current, fail_malloc, limit)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
     lines = r.stdout.strip().splitlines()
     assert lines[-1] == "end rc=0 current=%d leaked=0" % current, r.stdout
+    if limit:
+        return [int(v) for v in lines[0].split()[1:]]
     return [(w, int(d)) for w, d in (ln.split() for ln in lines[:-1])]
 
 
@@ -51,3 +54,14 @@ def test_packs_on_the_host_without_room(fake):
     calls = run(fake, 1, 1, -1, 0, fail_malloc=1)
     assert not any(w == "launch" for w, _ in calls)
     assert {d for w, d in calls if w == "copy"} == {0}          # as the caller's device has it
+
+
+@pytest.mark.parametrize("pool", [1, -1])
+def test_host_memory_runs_out_in_a_worker(fake, pool):
+    rcs = run(fake, pool, pool, -1, 0, limit="memory")
+    assert rcs[-1] == 0 and len(rcs) > 100 and set(rcs[:-1]) == {4}      # AMR_ENOMEM
+
+
+@pytest.mark.parametrize("pool", [1, -1])
+def test_threads_that_cannot_be_started(fake, pool):
+    assert run(fake, pool, pool, -1, 0, limit="threads") == [0] * 7
