@@ -180,8 +180,13 @@ typedef struct {
  * dangling-node fix described at amr_pack_opts.centering.  Writes the device tree, leaf table
  * and patch headers to d_meta.  Two-call protocol: with d_pool == NULL and d_meta == NULL it
  * only writes the required sizes to *pool_bytes and *meta_bytes.  Otherwise the buffers
- * must hold at least those sizes (AMR_ECAPACITY).  The copies are enqueued on `stream` and
- * the function waits for them before returning (host staging memory is freed).
+ * must hold at least those sizes (AMR_ECAPACITY).  The copies (and kernels) are enqueued on
+ * `stream` and the function waits for them before returning (host staging memory is freed); it
+ * waits for no other stream.  Cell-centred data whose buffers and stream belong to one GPU (which
+ * need not be the current one) is packed there: for the duration of the call 4 bytes per cell, 8
+ * per ghost cell and the tables are allocated on that GPU in the order of `stream`
+ * (hipMallocAsync).  Where there is no room for them, and for all else, the host packs and the
+ * result is copied: the same bytes, but for the sign of a zero that is a value range's end.
  * `patches` must be the array passed to amr_build_kdtree, with cells != NULL. */
 int amr_pack_pool(const amr_tree *tree, const amr_patch *patches, int32_t npatches,
                   const amr_pack_opts *opts, void *d_pool, int64_t *pool_bytes,

@@ -582,9 +582,9 @@ struct Packer {
                 }
     }
 
+    // Every brick; cell-centred, after neighbours().
     void run(int nthreads) {
         brick.assign(np, {});
-        if (!vertex) neighbours(nthreads);
         for (int l = 0; l <= T->lmax; l++) {      // coarser bricks are complete before finer ones
             std::vector<int> ids;
             for (int p = 0; p < np; p++) if (T->plevel[p] == l) ids.push_back(p);
@@ -736,10 +736,10 @@ int packing_device(const void *d_pool, const void *d_meta, void *stream) {
     return dev;
 }
 
-// What the packing kernels need to know of the patches: where cells, shells and bricks lie, the boxes
-// and the neighbours (pk.nbr) that the ghost layers draw from.
+// What the packing kernels need to know of the patches: where cells, shells and bricks lie, and the
+// boxes.
 void plan_device(const amr_tree *T, const amr_patch *patches, int np, int layout, const std::vector<int64_t> &off,
-                 int64_t nfl, const Packer &pk, PackPlan &plan) {
+                 int64_t nfl, PackPlan &plan) {
     plan.layout = layout;
     plan.pool_floats = nfl + 64;
     for (int a = 0; a < 3; a++) {
@@ -767,11 +767,17 @@ void plan_device(const amr_tree *T, const amr_patch *patches, int np, int layout
         P.floats = (p + 1 < np ? off[p + 1] : nfl) - off[p];
         plan.cell_floats += (int64_t)P.n[0] * P.n[1] * P.n[2];
         plan.shell_doubles += shell_count(P.n);
-        P.nbr0 = (int32_t)plan.nbr.size();
-        plan.nbr.insert(plan.nbr.end(), pk.nbr[p].begin(), pk.nbr[p].end());
-        P.nbr1 = (int32_t)plan.nbr.size();
         plan.cells[p] = patches[p].cells;
         plan.levels[P.level].push_back(p);
+    }
+}
+
+// The neighbours (Packer::neighbours) that the ghost layers draw from.
+void plan_neighbours(const std::vector<std::vector<int>> &nbr, PackPlan &plan) {
+    for (size_t p = 0; p < nbr.size(); p++) {
+        plan.patches[p].nbr0 = (int32_t)plan.nbr.size();
+        plan.nbr.insert(plan.nbr.end(), nbr[p].begin(), nbr[p].end());
+        plan.patches[p].nbr1 = (int32_t)plan.nbr.size();
     }
 }
 
@@ -944,13 +950,11 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
             ~Join() { if (t->joinable()) t->join(); }
         } join{&uploader};
         if (device) {
-            pk.neighbours(nthreads);
-            plan_device(T, patches, np, layout, off, nfl, pk, plan);
-            device = pack_stage_alloc(plan, nl, &stage);
-            if (!device) current.back();       // the copies are enqueued as the caller's device has it
+            plan_device(T, patches, np, layout, off, nfl, plan);
+            device = pack_stage_alloc(plan, nl, stream, &stage);
         }
         if (device) {
-            // the cells travel while the tree and the records below are written
+            // the cells travel while neighbours are sought and the tree and the records are written
             auto upload = [&]() {
                 try {
                     upload_rc = pack_upload_cells(plan, stage, dev);
@@ -964,7 +968,16 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
             } catch (const std::system_error &) {        // no thread to be had
                 upload();
             }
-        } else {
+        }
+        if (!vertex) pk.neighbours(nthreads);
+        if (device) {
+            plan_neighbours(pk.nbr, plan);
+            device = pack_stage_neighbours(plan, &stage);
+        }
+        if (!device) {
+            if (uploader.joinable()) uploader.join();
+            pack_stage_free(&stage);
+            current.back();                // the copies are enqueued as the caller's device has it
             pool.assign((size_t)nfl, 0.0f);
             pk.run(nthreads);
             std::atomic<int> next{0};

@@ -8,11 +8,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 
 #include "amr_pack.h"
-#include "amr_threads.h"
 
 namespace amr {
 
@@ -251,29 +249,33 @@ __global__ __launch_bounds__(256) void leaf_range_kernel(const PackPatch *patche
 
 int64_t up256(int64_t b) { return (b + 255) / 256 * 256; }
 
-// Threads that copy, each on its own stream: the copy of pageable memory is bound by the host's pass
-// through pinned buffers (250 patches, 60 M cells, pack: 18.3 ms with one thread, 15.4 with two, 14.7 with
-// four, 16.3 with eight).
-constexpr int kUploaders = 4;
-
 int hip_failed(hipError_t e, const char *what) {
     if (e == hipSuccess) return AMR_OK;
     set_error("%s: %s", what, hipGetErrorString(e));
     return AMR_EHIP;
 }
 
+// Null where there is no room, or the stream is being captured.
+void *stage_take(int64_t bytes, void *stream) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    void *p = nullptr;
+    if (hipStreamIsCapturing((hipStream_t)stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+        hipMallocAsync(&p, (size_t)bytes, (hipStream_t)stream) == hipSuccess)
+        return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+
 }  // namespace
 
-bool pack_stage_alloc(const PackPlan &plan, int64_t nleaves, PackStage *st) {
+bool pack_stage_alloc(const PackPlan &plan, int64_t nleaves, void *stream, PackStage *st) {
     const int64_t np = (int64_t)plan.patches.size();
     const int64_t bytes = up256(4 * plan.cell_floats) + up256(8 * plan.shell_doubles) +
-                          up256(np * (int64_t)sizeof(PackPatch)) + up256(4 * (int64_t)plan.nbr.size()) + up256(4 * np) +
+                          up256(np * (int64_t)sizeof(PackPatch)) + up256(4 * np) +
                           up256(nleaves * (int64_t)sizeof(PackLeaf)) + up256(8 * np);
-    if (hipMalloc(&st->mem, (size_t)bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        st->mem = nullptr;
-        return false;
-    }
+    st->stream = stream;
+    st->mem = stage_take(bytes, stream);
+    if (!st->mem) return false;
     char *p = (char *)st->mem;
     auto take = [&](int64_t b) {
         char *q = p;
@@ -283,35 +285,35 @@ bool pack_stage_alloc(const PackPlan &plan, int64_t nleaves, PackStage *st) {
     st->cells = (float *)take(4 * plan.cell_floats);
     st->shell = (double *)take(8 * plan.shell_doubles);
     st->patches = (PackPatch *)take(np * (int64_t)sizeof(PackPatch));
-    st->nbr = (int32_t *)take(4 * (int64_t)plan.nbr.size());
     st->ids = (int32_t *)take(4 * np);
     st->leaves = (PackLeaf *)take(nleaves * (int64_t)sizeof(PackLeaf));
     st->ranges = (float *)take(8 * np);
     return true;
 }
 
+bool pack_stage_neighbours(const PackPlan &plan, PackStage *st) {
+    st->nbr = (int32_t *)stage_take(std::max<int64_t>(4 * (int64_t)plan.nbr.size(), 256), st->stream);
+    return st->nbr != nullptr;
+}
+
 void pack_stage_free(PackStage *st) {
-    if (st->mem) (void)hipFree(st->mem);
-    st->mem = nullptr;
+    if (!st->mem) return;
+    hipStream_t s = (hipStream_t)st->stream;
+    if (st->nbr) (void)hipFreeAsync(st->nbr, s);
+    (void)hipFreeAsync(st->mem, s);
+    (void)hipStreamSynchronize(s);
+    st->mem = st->nbr = nullptr;
 }
 
 int pack_upload_cells(const PackPlan &plan, const PackStage &st, int device) {
-    const int nt = (int)std::min<size_t>(kUploaders, plan.patches.size());
-    std::atomic<size_t> next{0};
-    std::atomic<int> failed{(int)hipSuccess};
-    auto work = [&]() {
-        hipError_t e = hipSetDevice(device);
-        for (size_t p; e == hipSuccess && failed == (int)hipSuccess && (p = next.fetch_add(1)) < plan.patches.size();) {
-            const PackPatch &P = plan.patches[p];
-            e = hipMemcpyAsync(st.cells + P.cells, plan.cells[p], 4 * (size_t)P.n[0] * P.n[1] * P.n[2], hipMemcpyHostToDevice,
-                               hipStreamPerThread);
-        }
-        const hipError_t w = hipStreamSynchronize(hipStreamPerThread);
-        if (e == hipSuccess) e = w;
-        if (e != hipSuccess) failed = (int)e;
-    };
-    run_threads(nt, work);
-    return hip_failed((hipError_t)failed.load(), "copy of the cells");
+    hipError_t e = hipSetDevice(device);
+    for (size_t p = 0; e == hipSuccess && p < plan.patches.size(); p++) {
+        const PackPatch &P = plan.patches[p];
+        e = hipMemcpyAsync(st.cells + P.cells, plan.cells[p], 4 * (size_t)P.n[0] * P.n[1] * P.n[2], hipMemcpyHostToDevice,
+                           (hipStream_t)st.stream);
+    }
+    const hipError_t w = hipStreamSynchronize((hipStream_t)st.stream);
+    return hip_failed(e != hipSuccess ? e : w, "copy of the cells");
 }
 
 int pack_run(const PackPlan &plan, const PackStage &st, void *d_pool, void *d_meta, const void *meta, int64_t meta_bytes,

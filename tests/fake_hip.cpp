@@ -24,7 +24,8 @@ int g_log_end = 0;
 std::map<const char *, std::pair<size_t, int>> g_mem;      // address -> bytes, device
 std::map<void *, int> g_streams;
 thread_local int g_device = 0;
-int g_fail_malloc = 0;
+int g_fail_malloc = 0, g_capturing = 0;
+hipStream_t g_stream = nullptr;            // the stream that the call was given
 std::atomic<long> g_new_left{-1};          // allocations that worker threads still get; -1: no limit
 std::atomic<int> g_threads_left{-1};       // threads that can still be started; -1: no limit
 thread_local bool t_main = false;
@@ -67,6 +68,8 @@ void *fake_alloc(size_t n, int dev) { return give(n, dev); }
 void fake_release(void *p) { take(p); }
 void fake_stream(void *s, int dev) { g_streams[s] = dev; }
 void fake_fail_malloc(int on) { g_fail_malloc = on; }
+void fake_capturing(int on) { g_capturing = on; }
+void fake_call_stream(void *s) { g_stream = (hipStream_t)s; }
 void fake_limits(long news, int threads) { t_main = true; g_new_left = news; g_threads_left = threads; }
 long fake_held() { return (long)g_mem.size(); }
 const char *fake_log() { return g_log; }
@@ -89,18 +92,29 @@ hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t *d) {
     *d = it->second;
     return hipSuccess;
 }
-hipError_t hipMalloc(void **p, size_t n) {
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st) {
+    *st = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+// on: the allocation that fails (counted from 1; 0: none)
+hipError_t hipMallocAsync(void **p, size_t n, hipStream_t) {
     say("malloc");
-    if (g_fail_malloc) return hipErrorOutOfMemory;
+    if (g_fail_malloc && --g_fail_malloc == 0) return hipErrorOutOfMemory;
     *p = give(n, g_device);
     return hipSuccess;
 }
-hipError_t hipFree(void *p) { say("free"); take(p); return hipSuccess; }
-hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t) {
-    say("copy");
+hipError_t hipFreeAsync(void *p, hipStream_t) { say("free"); take(p); return hipSuccess; }
+// what waits for the whole GPU
+hipError_t hipMalloc(void **p, size_t n) { say("malloc-all"); return hipMallocAsync(p, n, nullptr); }
+hipError_t hipFree(void *p) { say("free-all"); return hipFreeAsync(p, nullptr); }
+hipError_t hipDeviceSynchronize() { say("wait-all"); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s) {
+    say(s == g_stream ? "copy" : "copy-elsewhere");
     memcpy(dst, src, n);
     return hipSuccess;
 }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { say("stream"); *s = (hipStream_t)0x2000; return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t m, hipStream_t s) {

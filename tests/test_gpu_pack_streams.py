@@ -1,0 +1,69 @@
+"""Packing beside other work on the GPU: a call on one stream does not wait for work on another, and what
+it allocates on the GPU is given back."""
+import time
+
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+def _busy(torch, stream):
+    """An event behind some 0.4 s of work on the stream."""
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(int(1e9))
+        e = torch.cuda.Event()
+        e.record()
+    return e
+
+
+@pytest.mark.parametrize("other", ["null", "side"])
+def test_pack_waits_for_its_own_stream_only(gpu, other):
+    import torch
+    amr = gpu
+    h = workloads.cosmology_like(1, root=32, nlevels=4, target_patches=40)
+    tree = amr.build_tree(h)
+    keep = [amr.pack(tree, h)]
+    src = torch.ones(1 << 24, dtype=torch.uint8)
+    dst = torch.empty_like(src, device="cuda")
+    busy = torch.cuda.default_stream() if other == "null" else torch.cuda.Stream()
+    # two streams can share a hardware queue, where a copy on one waits for the other's work: take one on
+    # which a plain copy does not
+    for _ in range(16):
+        s = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        e = _busy(torch, busy)
+        with torch.cuda.stream(s):
+            dst.copy_(src)
+            s.synchronize()
+        free = not e.query()
+        torch.cuda.synchronize()
+        if free:
+            break
+    assert free, "every stream shares the busy one's queue"
+    with torch.cuda.stream(s):
+        keep.append(amr.pack(tree, h))          # torch's blocks for this stream
+        torch.cuda.synchronize()
+        e = _busy(torch, busy)
+        t = time.perf_counter()
+        keep.append(amr.pack(tree, h))
+        t = time.perf_counter() - t
+        assert not e.query(), "packing took %.3f s and ended after the other stream's work" % t
+    torch.cuda.synchronize()
+    assert torch.equal(keep[0].pool[:-256], keep[2].pool[:-256]) and torch.equal(keep[0].meta, keep[2].meta)
+
+
+def test_pack_gives_its_memory_back(gpu):
+    import torch
+    amr = gpu
+    h = workloads.single_level((256, 256, 192))          # 50 MB of cells
+    tree = amr.build_tree(h)
+    scene = amr.pack(tree, h)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    for _ in range(3):
+        del scene
+        scene = amr.pack(tree, h)
+    torch.cuda.synchronize()
+    assert before - torch.cuda.mem_get_info()[0] < 16 << 20

@@ -25,9 +25,9 @@ def fake(tmp_path_factory):
     return lib
 
 
-def run(fake, pool, meta, stream, current, fail_malloc=0, limit=""):
+def run(fake, pool, meta, stream, current, fail_malloc=0, limit="", capturing=0):
     r = subprocess.run([sys.executable, os.path.join(HERE, "_fake_hip_run.py"), fake] +
-                       [str(v) for v in (pool, meta, stream, current, fail_malloc, limit)], capture_output=True, text=True, timeout=300)
+                       [str(v) for v in (pool, meta, stream, current, fail_malloc, limit, capturing)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
     lines = r.stdout.strip().splitlines()
     assert lines[-1] == "end rc=0 current=%d leaked=0" % current, r.stdout
@@ -50,10 +50,23 @@ def test_packs_on_the_host_across_gpus(fake, pool, meta, stream):
     assert {w for w, _ in calls} == {"copy"}
 
 
-def test_packs_on_the_host_without_room(fake):
-    calls = run(fake, 1, 1, -1, 0, fail_malloc=1)
+@pytest.mark.parametrize("allocation", [1, 2])
+def test_packs_on_the_host_without_room(fake, allocation):
+    calls = run(fake, 1, 1, -1, 0, fail_malloc=allocation)
     assert not any(w == "launch" for w, _ in calls)
-    assert {d for w, d in calls if w == "copy"} == {0}          # as the caller's device has it
+    assert [d for w, d in calls if w == "copy"][-2:] == [0, 0]          # as the caller's device has it
+
+
+@pytest.mark.parametrize("stream", [-1, 1])
+def test_waits_for_no_other_stream(fake, stream):
+    """No call that waits for the whole GPU, no stream of its own (the runtime puts those on hardware
+    queues that others use), every copy on the caller's."""
+    calls = run(fake, 1, 1, stream, 1)
+    assert {w for w, _ in calls} == {"malloc", "copy", "launch", "free"}
+
+
+def test_a_stream_being_captured_sees_copies_only(fake):
+    assert {w for w, _ in run(fake, 1, 1, 1, 1, capturing=1)} == {"copy"}
 
 
 @pytest.mark.parametrize("pool", [1, -1])
