@@ -321,6 +321,11 @@ int pack_run(const PackPlan &plan, const PackStage &st, void *d_pool, void *d_me
     hipStream_t s = (hipStream_t)stream;
     const int np = (int)plan.patches.size();
     std::vector<int32_t> ids;
+    std::vector<float> r(2 * (size_t)np);
+    struct Wait {                      // on every way out: copies read and write the host memory above
+        hipStream_t s;
+        ~Wait() { (void)hipStreamSynchronize(s); }
+    } wait{s};
     for (const auto &l : plan.levels) ids.insert(ids.end(), l.begin(), l.end());
     auto send = [&](void *dst, const void *src, size_t bytes) {
         return bytes ? hip_failed(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s), "copy of the packing tables") : AMR_OK;
@@ -357,7 +362,6 @@ int pack_run(const PackPlan &plan, const PackStage &st, void *d_pool, void *d_me
                            st.cells, st.shell, (DLeaf *)((char *)d_meta + o_leaves));
     rc = hip_failed(hipGetLastError(), "packing kernels");
     if (rc) return rc;
-    std::vector<float> r(2 * (size_t)np);
     rc = hip_failed(hipMemcpyAsync(r.data(), st.ranges, r.size() * 4, hipMemcpyDeviceToHost, s), "value ranges");
     if (!rc) rc = hip_failed(hipStreamSynchronize(s), "packing kernels");
     if (rc) return rc;

@@ -1,5 +1,5 @@
 """Packs a small hierarchy for a chosen GPU against the stand-in runtime of fake_hip.cpp and prints
-what was called: python _fake_hip_run.py FAKE_LIB POOL_DEVICE META_DEVICE STREAM_DEVICE CURRENT FAIL_MALLOC [LIMIT [CAPTURING]]
+what was called: python _fake_hip_run.py FAKE_LIB POOL_DEVICE META_DEVICE STREAM_DEVICE CURRENT FAIL_MALLOC [LIMIT [CAPTURING [FAIL_LAUNCH]]]
 (STREAM_DEVICE -1: the null stream; LIMIT memory: again and again, with one more allocation left to
 the worker threads each time, until it succeeds; LIMIT threads: with 0 .. 6 threads to be had; the line
 "rcs" then holds every return code).  A process of its own, since the stand-in has to be loaded before
@@ -60,6 +60,7 @@ def main():
         fake.fake_stream(stream, stream_dev)
     fake.fake_call_stream(stream)
     fake.fake_capturing(int(sys.argv[8]) if len(sys.argv) > 8 else 0)
+    fake.fake_fail_launch(int(sys.argv[9]) if len(sys.argv) > 9 else 0)
     fake.fake_fail_malloc(fail)
     fake.hipSetDevice(current)
     fake.fake_clear()

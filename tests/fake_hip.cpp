@@ -5,6 +5,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <dlfcn.h>
+#include <malloc.h>
 
 #include <atomic>
 #include <cstdio>
@@ -24,7 +25,7 @@ int g_log_end = 0;
 std::map<const char *, std::pair<size_t, int>> g_mem;      // address -> bytes, device
 std::map<void *, int> g_streams;
 thread_local int g_device = 0;
-int g_fail_malloc = 0, g_capturing = 0;
+int g_fail_malloc = 0, g_fail_launch = 0, g_capturing = 0, g_launched = 0;
 hipStream_t g_stream = nullptr;            // the stream that the call was given
 std::atomic<long> g_new_left{-1};          // allocations that worker threads still get; -1: no limit
 std::atomic<int> g_threads_left{-1};       // threads that can still be started; -1: no limit
@@ -60,6 +61,41 @@ void take(void *p) {
     g_mem.erase((const char *)p);
     free(p);
 }
+// A copy is done when its stream is waited for, as the runtime may; memory that has been freed by then
+// has been scribbled over (operator delete below), which its sum shows.
+struct Copy {
+    void *dst;
+    const void *src;
+    size_t n;
+    uint64_t sum;
+    Copy *next;                            // the one enqueued before
+} *g_copies = nullptr;
+
+uint64_t sum_of(const void *p, size_t n) {
+    uint64_t h = 1469598103934665603ull;
+    for (size_t i = 0; i < n; i++) h = (h ^ ((const unsigned char *)p)[i]) * 1099511628211ull;
+    return h;
+}
+
+void run_copies() {
+    Copy *first = nullptr;
+    {
+        std::lock_guard<std::mutex> l(g_mutex);
+        while (g_copies) {                 // in the order in which they were enqueued
+            Copy *c = g_copies;
+            g_copies = c->next;
+            c->next = first;
+            first = c;
+        }
+    }
+    while (first) {
+        Copy *c = first;
+        first = c->next;
+        if (sum_of(c->src, c->n) != c->sum) say("source-changed");
+        else memcpy(c->dst, c->src, c->n);
+        free(c);
+    }
+}
 }  // namespace
 
 extern "C" {
@@ -67,6 +103,7 @@ extern "C" {
 void *fake_alloc(size_t n, int dev) { return give(n, dev); }
 void fake_release(void *p) { take(p); }
 void fake_stream(void *s, int dev) { g_streams[s] = dev; }
+void fake_fail_launch(int on) { g_fail_launch = on; }
 void fake_fail_malloc(int on) { g_fail_malloc = on; }
 void fake_capturing(int on) { g_capturing = on; }
 void fake_call_stream(void *s) { g_stream = (hipStream_t)s; }
@@ -110,13 +147,19 @@ hipError_t hipFree(void *p) { say("free-all"); return hipFreeAsync(p, nullptr); 
 hipError_t hipDeviceSynchronize() { say("wait-all"); return hipSuccess; }
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s) {
     say(s == g_stream ? "copy" : "copy-elsewhere");
-    memcpy(dst, src, n);
+    std::lock_guard<std::mutex> l(g_mutex);
+    Copy *c = (Copy *)malloc(sizeof(Copy));
+    *c = Copy{dst, src, n, sum_of(src, n), g_copies};
+    g_copies = c;
     return hipSuccess;
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { say("stream"); *s = (hipStream_t)0x2000; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) {
+    run_copies();
+    return hipSuccess;
+}
+hipError_t hipGetLastError() { return g_launched && g_fail_launch ? hipErrorLaunchFailure : hipSuccess; }
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t m, hipStream_t s) {
     t_grid = g, t_block = b, t_shared = m, t_stream = s;
     return hipSuccess;
@@ -125,7 +168,11 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *m, hipStream_t *s
     *g = t_grid, *b = t_block, *m = t_shared, *s = t_stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { say("launch"); return hipSuccess; }
+hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) {
+    say("launch");
+    g_launched = 1;
+    return hipSuccess;
+}
 }
 
 void *operator new(size_t n) {
@@ -137,8 +184,11 @@ void *operator new(size_t n) {
     if (!p) throw std::bad_alloc();
     return p;
 }
-void operator delete(void *p) noexcept { free(p); }
-void operator delete(void *p, size_t) noexcept { free(p); }
+void operator delete(void *p) noexcept {
+    if (p) memset(p, 0xdd, malloc_usable_size(p));
+    free(p);
+}
+void operator delete(void *p, size_t) noexcept { operator delete(p); }
 
 void std::thread::_M_start_thread(_State_ptr state, void (*depend)()) {
     if (g_threads_left >= 0 && --g_threads_left < 0) {

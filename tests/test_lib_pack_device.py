@@ -25,12 +25,12 @@ def fake(tmp_path_factory):
     return lib
 
 
-def run(fake, pool, meta, stream, current, fail_malloc=0, limit="", capturing=0):
+def run(fake, pool, meta, stream, current, fail_malloc=0, limit="", capturing=0, fail_launch=0):
     r = subprocess.run([sys.executable, os.path.join(HERE, "_fake_hip_run.py"), fake] +
-                       [str(v) for v in (pool, meta, stream, current, fail_malloc, limit, capturing)], capture_output=True, text=True, timeout=300)
+                       [str(v) for v in (pool, meta, stream, current, fail_malloc, limit, capturing, fail_launch)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
     lines = r.stdout.strip().splitlines()
-    assert lines[-1] == "end rc=0 current=%d leaked=0" % current, r.stdout
+    assert lines[-1] == "end rc=%d current=%d leaked=0" % (5 if fail_launch else 0, current), r.stdout
     if limit:
         return [int(v) for v in lines[0].split()[1:]]
     return [(w, int(d)) for w, d in (ln.split() for ln in lines[:-1])]
@@ -67,6 +67,12 @@ def test_waits_for_no_other_stream(fake, stream):
 
 def test_a_stream_being_captured_sees_copies_only(fake):
     assert {w for w, _ in run(fake, 1, 1, 1, 1, capturing=1)} == {"copy"}
+
+
+def test_an_error_leaves_no_copy_behind(fake):
+    """A launch that fails (AMR_EHIP): the copies enqueued before it read host memory that is freed."""
+    calls = run(fake, 1, 1, 1, 1, fail_launch=1)
+    assert not any(w == "source-changed" for w, _ in calls) and any(w == "free" for w, _ in calls)
 
 
 @pytest.mark.parametrize("pool", [1, -1])
