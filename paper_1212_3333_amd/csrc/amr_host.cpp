@@ -951,7 +951,7 @@ int amr_pack_pool(const amr_tree *T, const amr_patch *patches, int32_t npatches,
         } join{&uploader};
         if (device) {
             plan_device(T, patches, np, layout, off, nfl, plan);
-            device = pack_stage_alloc(plan, nl, stream, &stage);
+            device = pack_stage_alloc(plan, nl, dev, stream, &stage);
         }
         if (device) {
             // the cells travel while neighbours are sought and the tree and the records are written

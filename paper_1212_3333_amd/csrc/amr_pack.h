@@ -59,9 +59,9 @@ AMR_HD inline int64_t shell_index(const int32_t *n, int64_t i, int64_t j, int64_
 // for whatever stream the runtime has put on the same hardware queue (there are four): with 2.5 s of
 // other work on the GPU a pack of 10 ms took 2.5 s either way.  Four threads that copied, each on its
 // own stream, saved 2.6 of 18.7 ms (250 patches, 60 M cells, tree build and pack); on one stream they
-// save nothing.
+// save nothing.  The memory pool is the call's own: the GPU's default pool keeps what is freed into it.
 struct PackStage {
-    void *mem = nullptr, *stream = nullptr;
+    void *mem = nullptr, *stream = nullptr, *pool = nullptr;
     float *cells = nullptr;
     double *shell = nullptr;
     PackPatch *patches = nullptr;
@@ -71,7 +71,7 @@ struct PackStage {
 };
 
 // False when the device has no room.  nleaves: an upper bound of plan.leaves.
-bool pack_stage_alloc(const PackPlan &plan, int64_t nleaves, void *stream, PackStage *st);
+bool pack_stage_alloc(const PackPlan &plan, int64_t nleaves, int device, void *stream, PackStage *st);
 // The same for the neighbour list, once plan.nbr is known.
 bool pack_stage_neighbours(const PackPlan &plan, PackStage *st);
 // After the work on the stream; nothing to do where nothing was allocated.

@@ -255,26 +255,35 @@ int hip_failed(hipError_t e, const char *what) {
     return AMR_EHIP;
 }
 
-// Null where there is no room, or the stream is being captured.
-void *stage_take(int64_t bytes, void *stream) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+// Null where there is no room.
+void *stage_take(const PackStage &st, int64_t bytes) {
     void *p = nullptr;
-    if (hipStreamIsCapturing((hipStream_t)stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-        hipMallocAsync(&p, (size_t)bytes, (hipStream_t)stream) == hipSuccess)
-        return p;
+    if (hipMallocFromPoolAsync(&p, (size_t)bytes, (hipMemPool_t)st.pool, (hipStream_t)st.stream) == hipSuccess) return p;
     (void)hipGetLastError();
     return nullptr;
 }
 
 }  // namespace
 
-bool pack_stage_alloc(const PackPlan &plan, int64_t nleaves, void *stream, PackStage *st) {
+bool pack_stage_alloc(const PackPlan &plan, int64_t nleaves, int device, void *stream, PackStage *st) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipMemPoolProps props{};
+    props.allocType = hipMemAllocationTypePinned;
+    props.location.type = hipMemLocationTypeDevice;
+    props.location.id = device;
+    hipMemPool_t pool = nullptr;
+    if (hipStreamIsCapturing((hipStream_t)stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
+        hipMemPoolCreate(&pool, &props) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    st->pool = pool;
     const int64_t np = (int64_t)plan.patches.size();
     const int64_t bytes = up256(4 * plan.cell_floats) + up256(8 * plan.shell_doubles) +
                           up256(np * (int64_t)sizeof(PackPatch)) + up256(4 * np) +
                           up256(nleaves * (int64_t)sizeof(PackLeaf)) + up256(8 * np);
     st->stream = stream;
-    st->mem = stage_take(bytes, stream);
+    st->mem = stage_take(*st, bytes);
     if (!st->mem) return false;
     char *p = (char *)st->mem;
     auto take = [&](int64_t b) {
@@ -292,17 +301,19 @@ bool pack_stage_alloc(const PackPlan &plan, int64_t nleaves, void *stream, PackS
 }
 
 bool pack_stage_neighbours(const PackPlan &plan, PackStage *st) {
-    st->nbr = (int32_t *)stage_take(std::max<int64_t>(4 * (int64_t)plan.nbr.size(), 256), st->stream);
+    st->nbr = (int32_t *)stage_take(*st, std::max<int64_t>(4 * (int64_t)plan.nbr.size(), 256));
     return st->nbr != nullptr;
 }
 
 void pack_stage_free(PackStage *st) {
-    if (!st->mem) return;
+    if (!st->pool) return;
     hipStream_t s = (hipStream_t)st->stream;
     if (st->nbr) (void)hipFreeAsync(st->nbr, s);
-    (void)hipFreeAsync(st->mem, s);
+    if (st->mem) (void)hipFreeAsync(st->mem, s);
     (void)hipStreamSynchronize(s);
-    st->mem = st->nbr = nullptr;
+    (void)hipMemPoolDestroy((hipMemPool_t)st->pool);
+    st->mem = st->pool = nullptr;
+    st->nbr = nullptr;
 }
 
 int pack_upload_cells(const PackPlan &plan, const PackStage &st, int device) {

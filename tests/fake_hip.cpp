@@ -9,6 +9,7 @@
 
 #include <atomic>
 #include <cstdio>
+#include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -25,7 +26,7 @@ int g_log_end = 0;
 std::map<const char *, std::pair<size_t, int>> g_mem;      // address -> bytes, device
 std::map<void *, int> g_streams;
 thread_local int g_device = 0;
-int g_fail_malloc = 0, g_fail_launch = 0, g_capturing = 0, g_launched = 0;
+int g_fail_malloc = 0, g_fail_launch = 0, g_capturing = 0, g_launched = 0, g_pool_device = -1;
 hipStream_t g_stream = nullptr;            // the stream that the call was given
 std::atomic<long> g_new_left{-1};          // allocations that worker threads still get; -1: no limit
 std::atomic<int> g_threads_left{-1};       // threads that can still be started; -1: no limit
@@ -133,7 +134,17 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st) {
     *st = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
-// on: the allocation that fails (counted from 1; 0: none)
+hipError_t hipMemPoolCreate(hipMemPool_t *m, const hipMemPoolProps *q) {
+    g_pool_device = q->location.id;
+    *m = (hipMemPool_t)give(1, q->location.id);
+    return hipSuccess;
+}
+hipError_t hipMemPoolDestroy(hipMemPool_t m) { take((void *)m); return hipSuccess; }
+hipError_t hipMallocFromPoolAsync(void **p, size_t n, hipMemPool_t, hipStream_t s) {
+    if (g_pool_device != g_device) say("pool-elsewhere");
+    return hipMallocAsync(p, n, s);
+}
+// the allocation that fails is counted from 1 (0: none)
 hipError_t hipMallocAsync(void **p, size_t n, hipStream_t) {
     say("malloc");
     if (g_fail_malloc && --g_fail_malloc == 0) return hipErrorOutOfMemory;

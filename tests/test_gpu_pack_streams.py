@@ -65,5 +65,10 @@ def test_pack_gives_its_memory_back(gpu):
     for _ in range(3):
         del scene
         scene = amr.pack(tree, h)
-    torch.cuda.synchronize()
-    assert before - torch.cuda.mem_get_info()[0] < 16 << 20
+    for _ in range(100):            # the runtime frees a little after the stream has been waited for
+        torch.cuda.synchronize()
+        held = before - torch.cuda.mem_get_info()[0]
+        if held < 16 << 20:
+            break
+        time.sleep(0.02)
+    assert held < 16 << 20
