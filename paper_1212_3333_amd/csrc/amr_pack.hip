@@ -247,6 +247,15 @@ __global__ __launch_bounds__(256) void leaf_range_kernel(const PackPatch *patche
     }
 }
 
+// f(first, count) over 0 .. n in parts of as many blocks of 256 threads as a launch takes (fewer than 2^32
+// threads along a grid's x axis).
+constexpr int64_t kPart = 1 << 22;
+static_assert(kPart * 256 < (int64_t)1 << 32, "threads of one launch");
+template <typename F>
+void in_parts(int64_t n, F f) {
+    for (int64_t k = 0; k < n; k += kPart) f(k, (uint32_t)std::min(kPart, n - k));
+}
+
 int64_t up256(int64_t b) { return (b + 255) / 256 * 256; }
 
 int hip_failed(hipError_t e, const char *what) {
@@ -358,19 +367,26 @@ int pack_run(const PackPlan &plan, const PackStage &st, void *d_pool, void *d_me
         if (l.empty()) continue;
         int64_t most = 1;
         for (int32_t p : l) most = std::max(most, shell_count(plan.patches[p].n));
-        hipLaunchKernelGGL(ghost_kernel, dim3((uint32_t)l.size(), chunks(most)), dim3(256), 0, s, st.patches, st.ids + first,
-                           st.nbr, st.cells, st.shell, B);
+        in_parts((int64_t)l.size(), [&](int64_t k, uint32_t n) {
+            hipLaunchKernelGGL(ghost_kernel, dim3(n, chunks(most)), dim3(256), 0, s, st.patches, st.ids + first + k, st.nbr,
+                               st.cells, st.shell, B);
+        });
         first += l.size();
     }
     int64_t most = 1;
     for (const PackPatch &P : plan.patches) most = std::max(most, P.floats / 4);
-    hipLaunchKernelGGL(brick_kernel, dim3(np, chunks(most)), dim3(256), 0, s, st.patches, np, plan.layout, st.cells, st.shell,
-                       (float *)d_pool, plan.pool_floats);
-    hipLaunchKernelGGL(patch_range_kernel, dim3(np), dim3(256), 0, s, st.patches, st.cells, st.shell,
-                       (DPatch *)((char *)d_meta + o_patch), st.ranges);
-    if (!plan.leaves.empty())
-        hipLaunchKernelGGL(leaf_range_kernel, dim3((uint32_t)plan.leaves.size()), dim3(256), 0, s, st.patches, st.leaves,
-                           st.cells, st.shell, (DLeaf *)((char *)d_meta + o_leaves));
+    DPatch *headers = (DPatch *)((char *)d_meta + o_patch);
+    DLeaf *records = (DLeaf *)((char *)d_meta + o_leaves);
+    in_parts(np, [&](int64_t k, uint32_t n) {
+        hipLaunchKernelGGL(brick_kernel, dim3(n, chunks(most)), dim3(256), 0, s, st.patches + k, np - (int)k, plan.layout,
+                           st.cells, st.shell, (float *)d_pool, plan.pool_floats);
+        hipLaunchKernelGGL(patch_range_kernel, dim3(n), dim3(256), 0, s, st.patches + k, st.cells, st.shell, headers + k,
+                           st.ranges + 2 * k);
+    });
+    in_parts((int64_t)plan.leaves.size(), [&](int64_t k, uint32_t n) {
+        hipLaunchKernelGGL(leaf_range_kernel, dim3(n), dim3(256), 0, s, st.patches, st.leaves + k, st.cells, st.shell,
+                           records + k);
+    });
     rc = hip_failed(hipGetLastError(), "packing kernels");
     if (rc) return rc;
     rc = hip_failed(hipMemcpyAsync(r.data(), st.ranges, r.size() * 4, hipMemcpyDeviceToHost, s), "value ranges");
