@@ -37,9 +37,9 @@ __device__ inline void stage_weights(const float *W, MlpLds &s) {
 
 __device__ inline float sigmoidf_(float z) { return 1.f / (1.f + __expf(-z)); }
 
-// The training kernels: 512 threads, eight waves, each taking tiles of 32 rows.  At 65536 rows that
-// is one tile per wave on 256 blocks, one block per CU: both kernels are chains (weights, inputs,
-// layers, results), so a tile is small and a CU holds eight of them to overlap.
+// The training kernels: 512 threads, eight waves, each taking tiles of 32 rows: 65536 rows are 256
+// blocks' worth of one tile per wave.  Both kernels are chains (weights, inputs, layers, results), so
+// a tile is small and a CU holds eight of them to overlap.
 constexpr int kTile = 32;
 constexpr int kWaves = 8;
 // LDS rows are padded to a multiple of 16 bytes that is not one of 128: the matrix-core operand
@@ -208,11 +208,20 @@ struct BwdLds {
 // Of a tile: the rows' output derivatives, one per lane; then, lane = hidden unit, dZ2 of the rows,
 // H read as whole rows, all of them in flight together; the products on the matrix cores from
 // operands laid out so that each is read as 16 bytes per lane (dZ2 by row and by unit, H1 by unit).
-// dW1 and db1 are one product too: the inputs, which are fp32, enter as two fp16 terms (their sum
-// holds 22 bits), a row of ones gives db1.  65536 rows: 20 us, of which a tile takes 3.5 and the blocks'
-// 5058 atomic sums 0.06 each, hence the grid of 128 (256 blocks 25 us, 64 blocks 25 us); with
-// serial row loops, operands gathered by halves and sums in LDS by atomics it took 94 us.
-constexpr int kBwdBlocks = 128;
+// dW1 and db1 are one product too, on the fp32 matrix instruction, as the inputs are fp32 of any
+// magnitude (two fp16 terms in their place held 22 bits between 1/8 and 65504, and none of a value
+// below 3e-8); a row of ones gives db1.  A call (mlp_zero and the binding's allocations included, 20 us of
+// it at any size) takes 35.2 us at 65536 rows and 132 us at 1048576; with the two fp16 terms 33.7 and
+// 166 us on 128 blocks; with serial row loops, operands gathered by halves and sums in LDS by atomics
+// 107 and 1323 us.
+// Blocks: one fits a CU (130 KB of LDS), a tile takes some 5 us and a block's 5058 atomic sums 0.06, so
+// few blocks while a wave has few tiles, every CU when it has many.  65536 rows: 128 blocks 36.4, 160
+// 35.2, 192 35.5, 256 39.7 us; 100003: 41.8, 39.4, 41.6, 39.5; 262144: 67.2, 60.5, 57.2, 56.4; 1048576:
+// 204, 173, 154, 132.
+constexpr int64_t bwd_blocks(int64_t tiles) {
+    const int64_t full = (tiles + kWaves - 1) / kWaves;          // a tile per wave
+    return std::min<int64_t>(full, full < 1024 ? 160 : 256);
+}
 
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void mlp_backward_kernel(const float *X, const float *W, const float *H,
                                                                   const float *Y, const float *Tg, int64_t n,
@@ -335,20 +344,13 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
             }
         }
         __builtin_amdgcn_wave_barrier();
-        // dW1 += X^T dZ1 (M = input, K = row, N = unit u), the inputs as two fp16 terms
-        {
-            half8 hi, lo;
+        // dW1 += X^T dZ1 (M = input, K = row, N = unit u), both operands fp32; of step j's four rows a lane
+        // holds 8 lq + j, which is the order that x and dzt are in
+        #pragma unroll
+        for (int nt = 0; nt < 4; nt++) {
+            const half8 d = *reinterpret_cast<const half8 *>(b.dzt + (nt * 16 + lr) * kCol + 8 * lq);
             #pragma unroll
-            for (int j = 0; j < 8; j++) {
-                hi[j] = (_Float16)x[j];
-                lo[j] = (_Float16)(x[j] - (float)hi[j]);
-            }
-            #pragma unroll
-            for (int nt = 0; nt < 4; nt++) {
-                const half8 d = *reinterpret_cast<const half8 *>(b.dzt + (nt * 16 + lr) * kCol + 8 * lq);
-                dw1[nt] = mfma_k32(hi, d, dw1[nt]);
-                dw1[nt] = mfma_k32(lo, d, dw1[nt]);
-            }
+            for (int j = 0; j < 8; j++) dw1[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j], (float)d[j], dw1[nt], 0, 0, 0);
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -474,7 +476,7 @@ int amr_mlp_backward(const float *X, const float *W, const float *H, const float
     hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(mlp_zero, dim3((kParams + 256) / 256), dim3(256), 0, s, dW, loss);
     const int64_t tiles = (n + kTile - 1) / kTile;
-    const int grid = (int)std::min<int64_t>((tiles + kWaves - 1) / kWaves, kBwdBlocks);
+    const int grid = (int)bwd_blocks(tiles);
     hipLaunchKernelGGL(mlp_backward_kernel, dim3(grid), dim3(64 * kWaves), 0, s, X, W, H, Y, T, n, q_lo, q_hi, dW, loss);
     return check_hip_mlp(hipGetLastError(), "mlp_backward launch");
 }
