@@ -222,6 +222,9 @@ constexpr int64_t bwd_blocks(int64_t tiles) {
     const int64_t full = (tiles + kWaves - 1) / kWaves;          // a tile per wave
     return std::min<int64_t>(full, full < 1024 ? 160 : 256);
 }
+// The rows that fill up the last tile: an infinity of some row's in their place, times their zero, would
+// count.
+__device__ const float kNoRow[128] = {};
 
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void mlp_backward_kernel(const float *X, const float *W, const float *H,
                                                                   const float *Y, const float *Tg, int64_t n,
@@ -258,9 +261,9 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
         float h1[kTile], h2[kTile], x[8];
         #pragma unroll
         for (int r = 0; r < kTile; r++) {
-            const int64_t g = row0 + r < n ? row0 + r : n - 1;
-            h1[r] = H[g * 128 + lane];
-            h2[r] = H[g * 128 + 64 + lane];
+            const float *h = row0 + r < n ? H + (row0 + r) * 128 : kNoRow;
+            h1[r] = h[lane];
+            h2[r] = h[64 + lane];
         }
         // dW1's operand rows: input lr (row 12: ones) of tile rows 8 lq .. 8 lq + 7
         #pragma unroll
