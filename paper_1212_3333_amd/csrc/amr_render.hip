@@ -38,11 +38,12 @@ template <bool LIT, bool REC, bool NEAR, int LAY, bool CK = false>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC || NEAR ? 3 : 5))) void render_fwd(RenderArgs A, CamGroup G) {
     // scheduled launches: this block's camera and super-tile from the order (or, before a call
     // has recorded it, camera by camera, super-tiles row by row)
+    const uint32_t block = block_number();
     int gc = (int)blockIdx.y;
     uint32_t sst = 0xffffffffu;
     constexpr uint32_t kSide = sched_side(LIT);
     if (G.sched) {
-        const uint32_t rank = (blockIdx.x / (32u * kSide * kSide)) * 8u + blockIdx.x % 8u;
+        const uint32_t rank = (block / (32u * kSide * kSide)) * 8u + block % 8u;
         if (rank >= G.nst) return;
         uint32_t e;
         if (A.sched_hdr[4 * G.cam0 + 1] == G.sig) {
@@ -74,15 +75,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
     // share bricks in that XCD's L2.  With a tile schedule, the super-tiles of all the launch's
     // cameras (kSide x kSide tiles) are dealt the same way in the schedule's order (longest tile
     // of the last call first) instead.
-    const uint32_t quarter = (blockIdx.x / 8u) & 3u;
+    const uint32_t quarter = (block / 8u) & 3u;
     int col, row;
     if (G.sched) {
         const uint32_t sgw = ((uint32_t)A.t8x + kSide - 1u) / kSide;
-        const uint32_t li = blockIdx.x / 32u;
+        const uint32_t li = block / 32u;
         col = (int)((sst % sgw) * kSide + (li % (kSide * kSide)) / kSide);
         row = (int)((sst / sgw) * kSide + li % kSide);
     } else {
-        const int xcd = (int)(blockIdx.x % 8), li = (int)(blockIdx.x / 32);
+        const int xcd = (int)(block % 8), li = (int)(block / 32);
         const int sidx = (li >> 4) * 8 + xcd;          // Morton index of the super-tile
         int sx = 0, sy = 0;
         #pragma unroll
@@ -963,6 +964,7 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
         for (int c = 0; c < ncams; c++) {
             RenderArgs A;
             int rc = fill_args(S, &cams[c], P, &A);
+            if (!rc && !learned) rc = check_sides(cams[c]);
             if (rc) return rc;
             A.rgba = d_rgba + 4 * pix_off;
             A.trace = P->d_trace ? P->d_trace + pix_off * P->trace_cap : nullptr;
@@ -1009,7 +1011,7 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
         memset(&G, 0, sizeof(G));
         SchedGroup SG;
         memset(&SG, 0, sizeof(SG));
-        int gx = 0;
+        int64_t blocks = 0;
         int64_t rel = 0;
         const int64_t order0 = tile_off;
         uint32_t nst = 0;
@@ -1021,7 +1023,8 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
             Ai.cam = c0 + i;
             if (i == 0) A = Ai;
             G.cam[i] = cam_args_of(Ai, rel);
-            gx = std::max(gx, 32 * ((Ai.sgrid * Ai.sgrid + 7) / 8) * 16);
+            if (!sched && (rc = check_sides(cams[c0 + i])) != AMR_OK) return rc;
+            blocks = std::max(blocks, 32 * (((int64_t)Ai.sgrid * Ai.sgrid + 7) / 8) * 16);
             SG.tile0[i] = tile_off;
             SG.t8x[i] = Ai.t8x;
             SG.t8y[i] = Ai.t8y;
@@ -1061,7 +1064,14 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
         A.ckpt_ray0 = pix_off;
         const bool rec = A.trace || A.trace_n || A.nsamp || A.stats || A.touch || A.touch_meta || A.ckpt;
         // scheduled: one-dimensional, four blocks per tile, ranks dealt to the 8 XCDs in turn
-        const dim3 g(sched ? 32 * side * side * ((nst + 7) / 8) : gx, sched ? 1 : n), b(64);
+        if (sched) {
+            blocks = 32 * (int64_t)(side * side) * (((int64_t)nst + 7) / 8);
+            if (blocks / 4 >= kMaxSchedTiles) {
+                set_error("the tile schedule takes fewer than 2^26 tiles of 8x8 pixels in a group of %d cameras", kCamGroup);
+                return AMR_EINVAL;
+            }
+        }
+        const dim3 g = tile_grid(blocks, sched ? 1 : n), b(64);
         if (rec && !(A.ckpt && !A.nearest && !A.trace && !A.trace_n && !A.nsamp && !A.stats && !A.touch && !A.touch_meta)) {
             if (A.nearest && A.lighting) hipLaunchKernelGGL((render_fwd<true, true, true, -1>), g, b, 0, s, A, G);
             else if (A.nearest) hipLaunchKernelGGL((render_fwd<false, true, true, -1>), g, b, 0, s, A, G);

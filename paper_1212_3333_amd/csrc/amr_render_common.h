@@ -9,6 +9,7 @@
 
 #include "amr_internal.h"
 #include "amr_tapq_index.h"
+#include "amr_tiles.h"
 
 namespace amr {
 
@@ -141,6 +142,9 @@ inline CamArgs cam_args_of(const RenderArgs &A, int64_t ray0) {
     C.ray0 = ray0;
     return C;
 }
+
+// This block's number in its camera's launch (tile_grid).
+__device__ __forceinline__ uint32_t block_number() { return blockIdx.z * gridDim.x + blockIdx.x; }
 
 // A block of a group launch takes its camera (c, for unscheduled launches blockIdx.y) into A.
 __device__ __forceinline__ void take_camera(RenderArgs &A, const CamGroup &G, int c) {
@@ -1790,6 +1794,19 @@ inline void with_layout(const RenderArgs &A, F f) {
     else if (A.compiled == 1) f(std::integral_constant<int, 1>{});
     else if (A.compiled == 2) f(std::integral_constant<int, 2>{});
     else f(std::integral_constant<int, kHalo32>{});
+}
+
+// The grid of a launch of `blocks` blocks for each of `cams` cameras (blockIdx.y).
+inline dim3 tile_grid(int64_t blocks, int cams) {
+    const Slices l = slices_of(blocks);
+    return dim3(l.x, (uint32_t)cams, l.z);
+}
+
+// Images that unscheduled launches take.
+inline int check_sides(const amr_camera &C) {
+    if (C.width <= kMaxSide && C.height <= kMaxSide) return AMR_OK;
+    set_error("images of more than %d pixels on a side are not rendered in one call", (int)kMaxSide);
+    return AMR_EINVAL;
 }
 
 inline int check_hip(hipError_t e, const char *what) {

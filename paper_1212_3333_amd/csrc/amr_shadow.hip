@@ -162,8 +162,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void sh
     __shared__ float4 s_lut[256];
     for (int i = threadIdx.x; i < 256; i += 64) s_lut[i] = A.lut[i];
     __syncthreads();
-    const uint32_t quarter = (blockIdx.x / 8u) & 3u;
-    const int xcd = (int)(blockIdx.x % 8), li = (int)(blockIdx.x / 32);
+    const uint32_t block = block_number();
+    const uint32_t quarter = (block / 8u) & 3u;
+    const int xcd = (int)(block % 8), li = (int)(block / 32);
     const int sidx = (li >> 4) * 8 + xcd;
     int sx = 0, sy = 0;
     #pragma unroll
@@ -349,11 +350,11 @@ __global__ __launch_bounds__(1024) void add_block_offsets(int64_t *off, int64_t 
 }
 
 template <int LAY>
-static void launch_march(int pass, bool rec, int grid, hipStream_t s, const RenderArgs &A, const ShadowWork &W) {
-    if (pass == kPassCount) hipLaunchKernelGGL((shadow_march<kPassCount, false, LAY>), dim3(grid), dim3(64), 0, s, A, W);
-    else if (pass == kPassRecord) hipLaunchKernelGGL((shadow_march<kPassRecord, false, LAY>), dim3(grid), dim3(64), 0, s, A, W);
-    else if (rec) hipLaunchKernelGGL((shadow_march<kPassShade, true, -1>), dim3(grid), dim3(64), 0, s, A, W);
-    else hipLaunchKernelGGL((shadow_march<kPassShade, false, LAY>), dim3(grid), dim3(64), 0, s, A, W);
+static void launch_march(int pass, bool rec, const dim3 &grid, hipStream_t s, const RenderArgs &A, const ShadowWork &W) {
+    if (pass == kPassCount) hipLaunchKernelGGL((shadow_march<kPassCount, false, LAY>), grid, dim3(64), 0, s, A, W);
+    else if (pass == kPassRecord) hipLaunchKernelGGL((shadow_march<kPassRecord, false, LAY>), grid, dim3(64), 0, s, A, W);
+    else if (rec) hipLaunchKernelGGL((shadow_march<kPassShade, true, -1>), grid, dim3(64), 0, s, A, W);
+    else hipLaunchKernelGGL((shadow_march<kPassShade, false, LAY>), grid, dim3(64), 0, s, A, W);
 }
 
 // Workspace of the point-light passes for npix rays and `jobs` job slots: counts, offsets,
@@ -368,7 +369,7 @@ int64_t shadow_work_bytes(int64_t npix, int64_t jobs) {
 
 int launch_shadow(const RenderArgs &A, bool rec, void *stream, void *work, int64_t work_bytes, int64_t jobs) {
     hipStream_t s = (hipStream_t)stream;
-    const int grid = 32 * ((A.sgrid * A.sgrid + 7) / 8) * 16;
+    const dim3 grid = tile_grid(32 * (((int64_t)A.sgrid * A.sgrid + 7) / 8) * 16, 1);
     const int64_t npix = (int64_t)A.width * A.height;
     const int64_t nb = (npix + 1023) / 1024;
     if (!work || jobs < 0 || work_bytes < shadow_work_bytes(npix, jobs)) {

@@ -7,6 +7,7 @@
 #include <dlfcn.h>
 #include <malloc.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdio>
 #include <cstdint>
@@ -27,6 +28,8 @@ std::map<const char *, std::pair<size_t, int>> g_mem;      // address -> bytes, 
 std::map<void *, int> g_streams;
 thread_local int g_device = 0;
 int g_fail_malloc = 0, g_fail_launch = 0, g_capturing = 0, g_launched = 0, g_pool_device = -1;
+uint64_t g_most_blocks = 0;                // of one launch
+hipError_t g_error = hipSuccess;
 hipStream_t g_stream = nullptr;            // the stream that the call was given
 std::atomic<long> g_new_left{-1};          // allocations that worker threads still get; -1: no limit
 std::atomic<int> g_threads_left{-1};       // threads that can still be started; -1: no limit
@@ -111,7 +114,8 @@ void fake_call_stream(void *s) { g_stream = (hipStream_t)s; }
 void fake_limits(long news, int threads) { t_main = true; g_new_left = news; g_threads_left = threads; }
 long fake_held() { return (long)g_mem.size(); }
 const char *fake_log() { return g_log; }
-void fake_clear() { g_log[g_log_end = 0] = 0; }
+void fake_clear() { g_log[g_log_end = 0] = 0, g_most_blocks = 0; }
+uint64_t fake_most_blocks() { return g_most_blocks; }
 
 hipError_t hipGetDevice(int *d) { *d = g_device; return hipSuccess; }
 hipError_t hipSetDevice(int d) { g_device = d; return hipSuccess; }
@@ -170,7 +174,11 @@ hipError_t hipStreamSynchronize(hipStream_t) {
     run_copies();
     return hipSuccess;
 }
-hipError_t hipGetLastError() { return g_launched && g_fail_launch ? hipErrorLaunchFailure : hipSuccess; }
+hipError_t hipGetLastError() {
+    const hipError_t e = g_launched && g_fail_launch ? hipErrorLaunchFailure : g_error;
+    g_error = hipSuccess;
+    return e;
+}
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t m, hipStream_t s) {
     t_grid = g, t_block = b, t_shared = m, t_stream = s;
     return hipSuccess;
@@ -179,10 +187,14 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *m, hipStream_t *s
     *g = t_grid, *b = t_block, *m = t_shared, *s = t_stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) {
-    say("launch");
+hipError_t hipLaunchKernel(const void *, dim3 g, dim3 b, void **, size_t, hipStream_t) {
+    const bool fits = (uint64_t)g.x * b.x < (1ull << 32) && (uint64_t)g.y * b.y < (1ull << 32) &&
+                      (uint64_t)g.z * b.z < (1ull << 32) && g.x && g.y && g.z;
+    say(fits ? "launch" : "launch-refused");
+    g_most_blocks = std::max(g_most_blocks, (uint64_t)g.x * g.y * g.z);
     g_launched = 1;
-    return hipSuccess;
+    g_error = fits ? hipSuccess : hipErrorInvalidConfiguration;
+    return g_error;
 }
 }
 
