@@ -28,7 +28,7 @@ struct QueueView {
     long long *tile0;            // [kQueues][ncams + 1] first unit of the k-th camera in `order`
     long long *pix0;             // [ncams] first pixel of camera c in the rgba output
     int *tiles_x, *tiles_y;      // [ncams]
-    int *sgrid;                  // [ncams] side of the power-of-two super-tile grid
+    int *cover;                  // [ncams] numbering of the super-tiles (Cover): sq | nx << 4
 };
 
 __host__ __device__ __forceinline__ int64_t q_align(int64_t b) { return (b + 255) / 256 * 256; }
@@ -52,7 +52,7 @@ __host__ __device__ __forceinline__ QueueView queue_view(void *base, int ncams) 
     p += q_align(4 * (int64_t)ncams);
     q.tiles_y = (int *)p;
     p += q_align(4 * (int64_t)ncams);
-    q.sgrid = (int *)p;
+    q.cover = (int *)p;
     return q;
 }
 
@@ -76,10 +76,9 @@ __global__ void queue_setup(const amr_camera *cams, int ncams, void *qbase, int 
         pix += (long long)cams[c].width * cams[c].height;
         q.tiles_x[c] = (cams[c].width + tw - 1) / tw;
         q.tiles_y[c] = (cams[c].height + th - 1) / th;
-        int sg = 1;
-        while (sg * 4 < q.tiles_x[c] || sg * 4 < q.tiles_y[c]) sg *= 2;
-        q.sgrid[c] = sg;
-        q.ntiles[c] = 4u * (xcd_tiles ? (unsigned int)(16 * sg * sg) : (unsigned int)(q.tiles_x[c] * q.tiles_y[c]));
+        const Cover cov = cover_of(q.tiles_x[c], q.tiles_y[c], kQueueSlack);
+        q.cover[c] = cov.sq | cov.nx << 4;
+        q.ntiles[c] = 4u * (xcd_tiles ? (unsigned int)(16 * cov.n) : (unsigned int)(q.tiles_x[c] * q.tiles_y[c]));
         if (stamps) stamps[c] = 0ull;
     }
     if (stamps) stamps[ncams] = 0ull;
@@ -101,7 +100,7 @@ __global__ void queue_setup(const amr_camera *cams, int ncams, void *qbase, int 
             q.tile0[x * (ncams + 1) + k] = t;
             const int c = q.order[k];
             if (xcd_tiles) {
-                const long long S = (long long)q.sgrid[c] * q.sgrid[c];      // super-tiles x, x + 8, ...
+                const long long S = q.ntiles[c] / 64u;                       // super-tiles x, x + 8, ...
                 t += x < S ? 64 * ((S - x + kQueues - 1) / kQueues) : 0;
             } else if (x == 0) {
                 t += q.ntiles[c];
@@ -173,17 +172,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
         const long long local = ((long long)tile - tile0[k]) >> 2;
         int tx, ty;
         if (B.xcd_tiles) {
-            // super-tile qx + 8 (local / 16) along the Morton curve, tile local % 16 in it
-            const long long st = qx + (long long)kQueues * (local / 16);
-            const int sub = (int)(local % 16);
-            int sx = 0, sy = 0;
-            #pragma unroll
-            for (int bit = 0; bit < 15; bit++) {
-                sx |= (int)((st >> (2 * bit)) & 1) << bit;
-                sy |= (int)((st >> (2 * bit + 1)) & 1) << bit;
-            }
-            tx = sx * 4 + (sub >> 2);
-            ty = sy * 4 + (sub & 3);
+            // super-tile qx + 8 (local / 16) in their order, tile local % 16 in it
+            const int sub = (int)(local % 16), cov = q.cover[c];
+            const SuperTile st = super_tile(cov & 15, cov >> 4, (uint32_t)(qx + (long long)kQueues * (local / 16)));
+            tx = st.x * 4 + (sub >> 2);
+            ty = st.y * 4 + (sub & 3);
         } else {
             const int txs = q.tiles_x[c];
             tx = (int)(local % txs);

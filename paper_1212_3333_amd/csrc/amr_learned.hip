@@ -158,15 +158,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT ? 2 : (L
     // One wave per block and one 8x8 pixel tile per wave, tiles grouped in 4x4 super-tiles along
     // a Morton curve and dealt round-robin to the 8 XCDs, as in the plain forward kernel (a
     // wave's slot frees as soon as its rays end).
-    const int xcd = (int)(blockIdx.x % 8), li = (int)(blockIdx.x / 8);
-    const int sidx = (li >> 4) * 8 + xcd;
-    int sx = 0, sy = 0;
-    #pragma unroll
-    for (int bit = 0; bit < 12; bit++) {
-        sx |= ((sidx >> (2 * bit)) & 1) << bit;
-        sy |= ((sidx >> (2 * bit + 1)) & 1) << bit;
-    }
-    const int col = sx * 4 + ((li & 15) >> 2), row = sy * 4 + (li & 3);
+    const uint32_t li = blockIdx.x / 8u;
+    const SuperTile st = super_tile(A.cov_sq, A.cov_nx, (li >> 4) * 8u + blockIdx.x % 8u);
+    const int col = st.x * 4 + (int)((li & 15u) >> 2), row = st.y * 4 + (int)(li & 3u);
     if (col >= A.t8x || row >= A.t8y) return;
     const int lane = threadIdx.x & 63;
     const int pi = col * 8 + (lane & 7);
@@ -384,7 +378,7 @@ int launch_learned(const RenderArgs &A, const amr_render_params *P, int lmax, vo
     G.lmax = lmax;
     hipStream_t s = (hipStream_t)stream;
     if (G.seglog && first_camera) hipLaunchKernelGGL(seglog_reset, dim3(1), dim3(64), 0, s, G.seglog);
-    const int grid = 8 * ((A.sgrid * A.sgrid + 7) / 8) * 16;
+    const uint32_t grid = (uint32_t)cover_blocks(cover_of(A.t8x, A.t8y, kLaunchSlack).n, 1);
     const bool log = G.seglog != nullptr;
     const int dec = P->bound_only ? 1 : (G.mlp ? 2 : 0);
     const dim3 g(grid), b(64);

@@ -64,9 +64,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
     using TQ = std::conditional_t<NEAR || kCk, TapQueueList, TapQueue>;
     TQ *tq = nullptr;
     if constexpr (kDefer) tq = tap_queues<1, TQ>();
-    for (int i = threadIdx.x; i < 256; i += 64) s_lut[i] = A.lut[i];
-    __syncthreads();
-
     // One wave per block, 4x4 pixels per wave, four waves per 8x8 tile.  Tiles are grouped in 4x4
     // super-tiles (32x32 pixels) numbered along a Morton curve; blocks are dealt round-robin to the
     // 8 XCDs and XCD x renders super-tiles x, x + 8, x + 16, ...  Every XCD thus gets a share of
@@ -83,16 +80,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
         col = (int)((sst % sgw) * kSide + (li % (kSide * kSide)) / kSide);
         row = (int)((sst / sgw) * kSide + li % kSide);
     } else {
-        const int xcd = (int)(block % 8), li = (int)(block / 32);
-        const int sidx = (li >> 4) * 8 + xcd;          // Morton index of the super-tile
-        int sx = 0, sy = 0;
-        #pragma unroll
-        for (int bit = 0; bit < 12; bit++) {
-            sx |= ((sidx >> (2 * bit)) & 1) << bit;
-            sy |= ((sidx >> (2 * bit + 1)) & 1) << bit;
-        }
-        col = sx * 4 + ((li & 15) >> 2);
-        row = sy * 4 + (li & 3);
+        const uint32_t li = block / 32u;
+        const SuperTile st = super_tile(A.cov_sq, A.cov_nx, (li >> 4) * 8u + block % 8u);
+        col = st.x * 4 + (int)((li & 15u) >> 2);
+        row = st.y * 4 + (int)(li & 3u);
     }
     const int lane = threadIdx.x & 63, sub = lane & 3;
     const int pi0 = col * 8 + (int)(quarter & 1u) * 4, pj0 = row * 8 + (int)(quarter >> 1) * 4;
@@ -111,6 +102,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
     int nseg = 0, nsamp_total = 0;
     Ray R;
     bool alive = valid && setup_ray(A, pi, pj, R);
+    if (__ballot(alive)) {                  // a block whose rays all miss reads nothing
+        for (int i = threadIdx.x; i < 256; i += 64) s_lut[i] = A.lut[i];
+        __syncthreads();
+    }
     if (REC) cnt.hit = alive && lead ? 1 : 0;
     // checkpoints for the adjoint: (t, T, C) at the start of every `every`-th data segment
     CkptHeader *ckh = nullptr;
@@ -964,7 +959,7 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
         for (int c = 0; c < ncams; c++) {
             RenderArgs A;
             int rc = fill_args(S, &cams[c], P, &A);
-            if (!rc && !learned) rc = check_sides(cams[c]);
+            if (!rc) rc = check_sides(cams[c]);
             if (rc) return rc;
             A.rgba = d_rgba + 4 * pix_off;
             A.trace = P->d_trace ? P->d_trace + pix_off * P->trace_cap : nullptr;
@@ -1024,7 +1019,7 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
             if (i == 0) A = Ai;
             G.cam[i] = cam_args_of(Ai, rel);
             if (!sched && (rc = check_sides(cams[c0 + i])) != AMR_OK) return rc;
-            blocks = std::max(blocks, 32 * (((int64_t)Ai.sgrid * Ai.sgrid + 7) / 8) * 16);
+            blocks = std::max(blocks, cover_blocks(cover_of(Ai.t8x, Ai.t8y, kLaunchSlack).n, 4));
             SG.tile0[i] = tile_off;
             SG.t8x[i] = Ai.t8x;
             SG.t8y[i] = Ai.t8y;
@@ -1071,7 +1066,7 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
                 return AMR_EINVAL;
             }
         }
-        const dim3 g = tile_grid(blocks, sched ? 1 : n), b(64);
+        const dim3 g = block_grid(blocks, sched ? 1 : n), b(64);
         if (rec && !(A.ckpt && !A.nearest && !A.trace && !A.trace_n && !A.nsamp && !A.stats && !A.touch && !A.touch_meta)) {
             if (A.nearest && A.lighting) hipLaunchKernelGGL((render_fwd<true, true, true, -1>), g, b, 0, s, A, G);
             else if (A.nearest) hipLaunchKernelGGL((render_fwd<false, true, true, -1>), g, b, 0, s, A, G);

@@ -82,8 +82,7 @@ struct RenderArgs {
     int64_t tile0;                   // this camera's first tile in the schedule
     int32_t cam;                     // this camera's index in the call
     int32_t tiles_x, tiles_y, nblocks;     // 16x16 tiles of four waves (learned kernel)
-    int32_t t8x, t8y, sgrid;               // 8x8 one-wave tiles; side of the power-of-two
-                                           // grid of 4x4-tile super-tiles covering them
+    int32_t t8x, t8y, cov_sq, cov_nx;      // 8x8-pixel tiles, and how they are numbered (Cover)
 };
 
 // The per-camera fields of RenderArgs, for launches that render a group of cameras (one camera
@@ -91,7 +90,7 @@ struct RenderArgs {
 struct CamArgs {
     double eye[3], u[3], v[3], w[3];
     double tanf, win0, win1, lod_pix;
-    int32_t ortho, width, height, t8x, t8y, sgrid;
+    int32_t ortho, width, height, t8x, t8y, cov_sq, cov_nx;
     int64_t ray0;                    // the camera's first pixel, relative to the group's first
     int64_t tile0;                   // the camera's first tile in the schedule
     int32_t cam, pad_;               // the camera's index in the call
@@ -138,12 +137,13 @@ inline CamArgs cam_args_of(const RenderArgs &A, int64_t ray0) {
     C.height = A.height;
     C.t8x = A.t8x;
     C.t8y = A.t8y;
-    C.sgrid = A.sgrid;
+    C.cov_sq = A.cov_sq;
+    C.cov_nx = A.cov_nx;
     C.ray0 = ray0;
     return C;
 }
 
-// This block's number in its camera's launch (tile_grid).
+// This block's number in its camera's launch (block_grid).
 __device__ __forceinline__ uint32_t block_number() { return blockIdx.z * gridDim.x + blockIdx.x; }
 
 // A block of a group launch takes its camera (c, for unscheduled launches blockIdx.y) into A.
@@ -166,7 +166,8 @@ __device__ __forceinline__ void take_camera(RenderArgs &A, const CamGroup &G, in
     A.height = C.height;
     A.t8x = C.t8x;
     A.t8y = C.t8y;
-    A.sgrid = C.sgrid;
+    A.cov_sq = C.cov_sq;
+    A.cov_nx = C.cov_nx;
     A.tile0 = C.tile0;
     A.cam = C.cam;
     A.rgba += 4 * C.ray0;
@@ -1797,7 +1798,7 @@ inline void with_layout(const RenderArgs &A, F f) {
 }
 
 // The grid of a launch of `blocks` blocks for each of `cams` cameras (blockIdx.y).
-inline dim3 tile_grid(int64_t blocks, int cams) {
+inline dim3 block_grid(int64_t blocks, int cams) {
     const Slices l = slices_of(blocks);
     return dim3(l.x, (uint32_t)cams, l.z);
 }
@@ -1886,8 +1887,9 @@ inline int fill_args(const amr_scene *S, const amr_camera *C, const amr_render_p
     A->nblocks = A->tiles_x * A->tiles_y;
     A->t8x = (C->width + 7) / 8;
     A->t8y = (C->height + 7) / 8;
-    A->sgrid = 1;
-    while (A->sgrid * 4 < A->t8x || A->sgrid * 4 < A->t8y) A->sgrid *= 2;
+    const Cover cov = cover_of(A->t8x, A->t8y, kLaunchSlack);
+    A->cov_sq = cov.sq;
+    A->cov_nx = cov.nx;
     A->ckpt = (uint8_t *)P->d_ckpt;
     A->ckpt_stride = (int64_t)sizeof(Ckpt) * (1 + (int64_t)P->ckpt_max);
     A->ckpt_every = P->ckpt_every > 0 ? P->ckpt_every : 1;

@@ -160,21 +160,13 @@ enum { kPassCount = 0, kPassRecord = 1, kPassShade = 2 };
 template <int PASS, bool REC, int LAY>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void shadow_march(RenderArgs A, ShadowWork W) {
     __shared__ float4 s_lut[256];
-    for (int i = threadIdx.x; i < 256; i += 64) s_lut[i] = A.lut[i];
-    __syncthreads();
     const uint32_t block = block_number();
     const uint32_t quarter = (block / 8u) & 3u;
-    const int xcd = (int)(block % 8), li = (int)(block / 32);
-    const int sidx = (li >> 4) * 8 + xcd;
-    int sx = 0, sy = 0;
-    #pragma unroll
-    for (int bit = 0; bit < 12; bit++) {
-        sx |= ((sidx >> (2 * bit)) & 1) << bit;
-        sy |= ((sidx >> (2 * bit + 1)) & 1) << bit;
-    }
+    const uint32_t li = block / 32u;
+    const SuperTile st = super_tile(A.cov_sq, A.cov_nx, (li >> 4) * 8u + block % 8u);
     const int lane = threadIdx.x & 63, sub = lane & 3;
-    const int pi0 = (sx * 4 + ((li & 15) >> 2)) * 8 + (int)(quarter & 1u) * 4;
-    const int pj0 = (sy * 4 + (li & 3)) * 8 + (int)(quarter >> 1) * 4;
+    const int pi0 = (st.x * 4 + (int)((li & 15u) >> 2)) * 8 + (int)(quarter & 1u) * 4;
+    const int pj0 = (st.y * 4 + (int)(li & 3u)) * 8 + (int)(quarter >> 1) * 4;
     if (pi0 >= A.width || pj0 >= A.height) return;
     const int pi = pi0 + ((lane >> 2) & 3);
     const int pj = pj0 + (lane >> 4);
@@ -187,6 +179,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void sh
     int nseg = 0, nsamp_total = 0;
     Ray R;
     bool alive = valid && setup_ray(A, pi, pj, R);
+    if (__ballot(alive)) {                  // a block whose rays all miss reads nothing
+        for (int i = threadIdx.x; i < 256; i += 64) s_lut[i] = A.lut[i];
+        __syncthreads();
+    }
     if (REC) cnt.hit = alive && lead ? 1 : 0;
     const int64_t base = (PASS != kPassCount && valid) ? W.off[ray] : 0;
     // the later passes stay inside this ray's jobs even if a sample count came out differently
@@ -369,7 +365,7 @@ int64_t shadow_work_bytes(int64_t npix, int64_t jobs) {
 
 int launch_shadow(const RenderArgs &A, bool rec, void *stream, void *work, int64_t work_bytes, int64_t jobs) {
     hipStream_t s = (hipStream_t)stream;
-    const dim3 grid = tile_grid(32 * (((int64_t)A.sgrid * A.sgrid + 7) / 8) * 16, 1);
+    const dim3 grid = block_grid(cover_blocks(cover_of(A.t8x, A.t8y, kLaunchSlack).n, 4), 1);
     const int64_t npix = (int64_t)A.width * A.height;
     const int64_t nb = (npix + 1023) / 1024;
     if (!work || jobs < 0 || work_bytes < shadow_work_bytes(npix, jobs)) {

@@ -5,6 +5,52 @@
 
 namespace amr {
 
+// A frame's super-tiles (4x4 tiles) in launch order: squares of 2^sq super-tiles a side, nx to a row, row by
+// row, each along a Morton curve, so that the super-tiles in flight on an XCD, which takes every eighth,
+// stay close together.  The squares are the largest with which the order has at most slack / 2 times
+// as many places as the frame has super-tiles.  A launch (kLaunchSlack) keeps one square over the
+// frame until three places in four are empty: an empty place is 64 blocks that return at once.  A
+// 16384x16 frame has 512 super-tiles and the square over it 262144: lit 5.7 -> 0.9 ms, unlit 3.95 -> 0.54
+// (3.5 and 1.48 ms with one lane per ray and a quarter of the blocks).  Tighter launches gain on some
+// frames and lose on others, by what their order is worth on the XCDs (27 sizes from 63x70 to 1100x1000
+// in two scenes: 0.85 to 1.15 of the time at kQueueSlack, 0.99 on average; 0.96 to 1.04 at this).  A
+// queue (kQueueSlack) hands out its empty places by an atomic each: four images of 100 to 384 pixels a
+// side, unlit, 2.53 -> 1.77 ms.
+struct Cover {
+    int32_t sq, nx;
+    int64_t n;                         // places
+};
+constexpr int kLaunchSlack = 8, kQueueSlack = 3;
+constexpr Cover cover_of(int64_t tiles_x, int64_t tiles_y, int slack) {
+    const int64_t w = (tiles_x + 3) / 4, h = (tiles_y + 3) / 4;
+    int32_t sq = 0;
+    while (((int64_t)1 << sq) < w || ((int64_t)1 << sq) < h) sq++;
+    for (;; sq--) {
+        const int64_t nx = (w + ((int64_t)1 << sq) - 1) >> sq, ny = (h + ((int64_t)1 << sq) - 1) >> sq;
+        const int64_t n = (nx * ny) << (2 * sq);
+        if (sq == 0 || 2 * n <= slack * w * h) return Cover{sq, (int32_t)nx, n};
+    }
+}
+
+// Super-tile i of the order; beyond the cover, one below the frame.
+struct SuperTile {
+    int32_t x, y;
+};
+constexpr SuperTile super_tile(int32_t sq, int32_t nx, uint32_t i) {
+    const uint32_t q = i >> (2 * sq);
+    int32_t x = (int32_t)(q % (uint32_t)nx) << sq, y = (int32_t)(q / (uint32_t)nx) << sq;
+    for (int32_t bit = 0; bit < sq; bit++) {
+        x |= (int32_t)((i >> (2 * bit)) & 1u) << bit;
+        y |= (int32_t)((i >> (2 * bit + 1)) & 1u) << bit;
+    }
+    return SuperTile{x, y};
+}
+
+// Blocks of a launch over n super-tiles, dealt to the 8 XCDs in turn (block i on XCD i mod 8), with `per`
+// blocks to a tile; block i renders part (i / 8) % per of tile (i / (8 per)) % 16 of super-tile
+// (i / (128 per)) * 8 + i % 8.
+constexpr int64_t cover_blocks(int64_t n, int per) { return (n + 7) / 8 * 8 * 16 * per; }
+
 // One-wave blocks along a grid's x axis at most: HIP takes fewer than 2^32 threads there.
 constexpr int64_t kSliceBlocks = 1 << 25;
 
