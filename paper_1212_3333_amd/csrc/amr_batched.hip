@@ -64,7 +64,7 @@ inline int64_t queue_bytes(int ncams) {
 // One thread: reset the queues, order the cameras by pixel count (largest first, or smallest
 // first with `smallest`; ties by index) and build the tile and pixel prefix tables.
 __global__ void queue_setup(const amr_camera *cams, int ncams, void *qbase, int tw, int th,
-                            unsigned long long *stamps, int smallest, int xcd_tiles) {
+                            unsigned long long *stamps, int smallest, int xcd_tiles, int lpr) {
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
     QueueView q = queue_view(qbase, ncams);
     for (int x = 0; x < kQueues; x++) q.next[16 * x] = 0u;
@@ -78,7 +78,7 @@ __global__ void queue_setup(const amr_camera *cams, int ncams, void *qbase, int 
         q.tiles_y[c] = (cams[c].height + th - 1) / th;
         const Cover cov = cover_of(q.tiles_x[c], q.tiles_y[c], kQueueSlack);
         q.cover[c] = cov.sq | cov.nx << 4;
-        q.ntiles[c] = 4u * (xcd_tiles ? (unsigned int)(16 * cov.n) : (unsigned int)(q.tiles_x[c] * q.tiles_y[c]));
+        q.ntiles[c] = (unsigned int)lpr * (xcd_tiles ? (unsigned int)(16 * cov.n) : (unsigned int)(q.tiles_x[c] * q.tiles_y[c]));
         if (stamps) stamps[c] = 0ull;
     }
     if (stamps) stamps[ncams] = 0ull;
@@ -100,8 +100,8 @@ __global__ void queue_setup(const amr_camera *cams, int ncams, void *qbase, int 
             q.tile0[x * (ncams + 1) + k] = t;
             const int c = q.order[k];
             if (xcd_tiles) {
-                const long long S = q.ntiles[c] / 64u;                       // super-tiles x, x + 8, ...
-                t += x < S ? 64 * ((S - x + kQueues - 1) / kQueues) : 0;
+                const long long S = q.ntiles[c] / (16u * lpr);               // super-tiles x, x + 8, ...
+                t += x < S ? 16 * lpr * ((S - x + kQueues - 1) / kQueues) : 0;
             } else if (x == 0) {
                 t += q.ntiles[c];
             }
@@ -137,8 +137,9 @@ __device__ __forceinline__ void set_camera(RenderArgs &A, const amr_camera &C) {
 // LAY: the brick layout fixed at compile time (-1: read at run time, for the recording variants).
 // WPS: waves per SIMD the register allocation must allow (the lit kernel: 3 fits 168 VGPRs and
 // spills about 120 bytes per lane, 2 keeps everything in registers with a third fewer waves).
-template <bool LIT, bool REC, int LAY, int WPS = 3>
+template <bool LIT, bool REC, int LAY, int WPS = 3, int LPR = 4>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void render_batched(BatchArgs B) {
+    static_assert(LPR == 4 || (LPR == 1 && !LIT && !REC));
     __shared__ float4 s_lut[256];
     TapQueue *tq = nullptr;                        // lit: one deferred-tap queue per wave
     if constexpr (LIT) tq = tap_queues<4, TapQueue>() + (threadIdx.x >> 6);
@@ -186,8 +187,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
         }
         const amr_camera C = B.cams[c];
         set_camera(A, C);
-        const int quarter = (int)(((long long)tile - tile0[k]) & 3);
-        const long long local = ((long long)tile - tile0[k]) >> 2;
+        const int quarter = (int)(((long long)tile - tile0[k]) % LPR);
+        const long long local = ((long long)tile - tile0[k]) / LPR;
         int tx, ty;
         if (B.xcd_tiles) {
             // super-tile qx + 8 (local / 16) in their order, tile local % 16 in it
@@ -200,10 +201,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
             tx = (int)(local % txs);
             ty = (int)(local / txs);
         }
-        // the unit's pixels: 4x4 where the tile has them, else 16 in a row of the tile's pixels
-        const int r = lane >> 2, sub = lane & 3;
+        // the unit's pixels: with one lane per ray the tile's; else 4x4 where the tile has them, or 16 in a
+        // row of the tile's pixels
+        const int r = lane >> 2, sub = lane & (LPR - 1);
         int px, py;
-        if (B.tw == 8) {
+        if (LPR == 1) {
+            px = lane % B.tw;
+            py = lane / B.tw;
+        } else if (B.tw == 8) {
             px = (quarter & 1) * 4 + (r & 3);
             py = (quarter >> 1) * 4 + (r >> 2);
         } else {
@@ -213,7 +218,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
         const int pi = tx * B.tw + px;
         const int pj = ty * B.th + py;
         const bool valid = pi < C.width && pj < C.height;
-        float C0 = 0.f, C1 = 0.f, C2 = 0.f, T = 1.f;
+        float P[3][4 / LPR] = {}, T = 1.f;             // this lane's partial colour sums
         int nsamp_total = 0;
         Ray R;
         bool alive = valid && setup_ray(A, pi, pj, R);
@@ -239,14 +244,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
                         const LitPoint pt = lit_point<false>(A, R, S, min(k + sub, S.n - 1));
                         if (tq_due(Q, k + sub < S.n ? pt.pend : 0u, lane))
                             tapq_flush<REC, LAY>(A, s_lut, Q, lane, cnt);
-                        const QuadStep st = lit_step<REC, LAY, false>(A, s_lut, Q, lane, R, S, k, pt, T, C0, C1, C2, cnt,
+                        const QuadStep st = lit_step<REC, LAY, false>(A, s_lut, Q, lane, R, S, k, pt, T, P[0][0], P[1][0], P[2][0], cnt,
                                                                       nullptr, tpos);
                         nsamp_total += st.n;
                         if (st.stop) alive = false;
                     }
                 } else {
                     bool stop;
-                    nsamp_total += composite_unlit_quad<REC, false, LAY>(A, s_lut, R, S, sub, T, C0, C1, C2, stop, cnt);
+                    if constexpr (LPR == 4) {
+                        nsamp_total += composite_unlit_quad<REC, false, LAY>(A, s_lut, R, S, sub, T, P[0][0], P[1][0], P[2][0],
+                                                                             stop, cnt);
+                    } else {
+                        float tseg = 1.f;
+                        nsamp_total += composite_unlit<LAY>(A, s_lut, R, S, T, P, tseg, stop, cnt);
+                    }
                     if (stop) alive = false;
                 }
             }
@@ -260,13 +271,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS))) void
         if (LIT) {
             float D0, D1, D2;
             tapq_finish<REC, LAY>(A, s_lut, *tq, lane, cnt, D0, D1, D2);
-            C0 += D0;
-            C1 += D1;
-            C2 += D2;
+            P[0][0] += D0;
+            P[1][0] += D1;
+            P[2][0] += D2;
         }
-        C0 = quad_sum(C0);
-        C1 = quad_sum(C1);
-        C2 = quad_sum(C2);
+        const float C0 = ray_sum<LPR>(P[0]), C1 = ray_sum<LPR>(P[1]), C2 = ray_sum<LPR>(P[2]);
         if (REC && sub == 0) cnt.samples += nsamp_total;
         if (valid && sub == 0) reinterpret_cast<float4 *>(B.base.rgba)[q.pix0[c] + (long long)pj * C.width + pi] =
             make_float4(C0, C1, C2, 1.f - T);
@@ -328,15 +337,18 @@ int launch_persistent(const amr_scene *S, const amr_camera *cams, int32_t ncams,
     }
     const bool two = P->waves_per_simd == 2;
     B.xcd_tiles = P->xcd_tiles;
+    const bool rec = d_stats != nullptr;
+    int64_t pixels = 0;
+    for (int c = 0; c < ncams; c++) pixels += (int64_t)cams[c].width * cams[c].height;
+    const int lpr = B.base.lighting || rec ? 4 : lanes_per_ray(pixels / ncams, S->depth);
     hipStream_t s = (hipStream_t)stream;
     if (d_stats)
         hipLaunchKernelGGL(zero_stats, dim3(1), dim3(64), 0, s, (unsigned long long *)d_stats,
                            (int)(sizeof(amr_render_stats) / 8));
     hipLaunchKernelGGL(queue_setup, dim3(1), dim3(64), 0, s, P->d_cams, ncams, P->d_queue, tw, th, P->d_stamps,
-                       (int)P->queue_order, (int)P->xcd_tiles);
+                       (int)P->queue_order, (int)P->xcd_tiles, lpr);
     int bpc = P->blocks_per_cu > 0 ? P->blocks_per_cu : 4;
     dim3 grid(device_cus() * bpc);
-    const bool rec = d_stats != nullptr;
     if (rec) {
         if (B.base.lighting) hipLaunchKernelGGL((render_batched<true, true, -1>), grid, dim3(256), 0, s, B);
         else hipLaunchKernelGGL((render_batched<false, true, -1>), grid, dim3(256), 0, s, B);
@@ -345,7 +357,8 @@ int launch_persistent(const amr_scene *S, const amr_camera *cams, int32_t ncams,
             constexpr int L = decltype(lay)::value;
             if (B.base.lighting && two) hipLaunchKernelGGL((render_batched<true, false, L, 2>), grid, dim3(256), 0, s, B);
             else if (B.base.lighting) hipLaunchKernelGGL((render_batched<true, false, L>), grid, dim3(256), 0, s, B);
-            else hipLaunchKernelGGL((render_batched<false, false, L>), grid, dim3(256), 0, s, B);
+            else if (lpr == 4) hipLaunchKernelGGL((render_batched<false, false, L>), grid, dim3(256), 0, s, B);
+            else hipLaunchKernelGGL((render_batched<false, false, L, 4, 1>), grid, dim3(256), 0, s, B);
         });
     }
     return check_hip(hipGetLastError(), "render_batched launch");

@@ -34,8 +34,12 @@ namespace amr {
 // resolves are written to the ray's tape, so the adjoint reads them instead of resolving taps.
 // CK: checkpoints (and the tape) without the other recording outputs, for the adjoint's forward
 // pass at the layout's compiled addressing.
-template <bool LIT, bool REC, bool NEAR, int LAY, bool CK = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC || NEAR ? 3 : 5))) void render_fwd(RenderArgs A, CamGroup G) {
+// LPR: lanes per ray, 4, or 1 for unlit images of many pixels (lanes_per_ray).  One lane evaluates a ray's
+// samples four at a time and takes 4 waves per SIMD (128 VGPRs: 5.3 ms for a 2048^2 view; at 5 it
+// spills, 6.1 ms).
+template <bool LIT, bool REC, bool NEAR, int LAY, bool CK = false, int LPR = 4>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LPR == 1 ? 4 : (LIT || REC || NEAR ? 3 : 5)))) void render_fwd(RenderArgs A, CamGroup G) {
+    static_assert(LPR == 4 || (LPR == 1 && !LIT && !REC && !CK));
     // scheduled launches: this block's camera and super-tile from the order (or, before a call
     // has recorded it, camera by camera, super-tiles row by row)
     const uint32_t block = block_number();
@@ -43,7 +47,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
     uint32_t sst = 0xffffffffu;
     constexpr uint32_t kSide = sched_side(LIT);
     if (G.sched) {
-        const uint32_t rank = (block / (32u * kSide * kSide)) * 8u + block % 8u;
+        const uint32_t rank = (block / (8u * LPR * kSide * kSide)) * 8u + block % 8u;
         if (rank >= G.nst) return;
         uint32_t e;
         if (A.sched_hdr[4 * G.cam0 + 1] == G.sig) {
@@ -64,7 +68,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
     using TQ = std::conditional_t<NEAR || kCk, TapQueueList, TapQueue>;
     TQ *tq = nullptr;
     if constexpr (kDefer) tq = tap_queues<1, TQ>();
-    // One wave per block, 4x4 pixels per wave, four waves per 8x8 tile.  Tiles are grouped in 4x4
+    // One wave per block: 4x4 pixels, four waves per 8x8 tile, or with one lane per ray a tile.  Tiles are grouped in 4x4
     // super-tiles (32x32 pixels) numbered along a Morton curve; blocks are dealt round-robin to the
     // 8 XCDs and XCD x renders super-tiles x, x + 8, x + 16, ...  Every XCD thus gets a share of
     // every part of the image (the work per tile varies by 10x and more across the screen), while
@@ -72,33 +76,31 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
     // share bricks in that XCD's L2.  With a tile schedule, the super-tiles of all the launch's
     // cameras (kSide x kSide tiles) are dealt the same way in the schedule's order (longest tile
     // of the last call first) instead.
-    const uint32_t quarter = (block / 8u) & 3u;
+    const uint32_t quarter = (block / 8u) % LPR, li = block / (8u * LPR);
     int col, row;
     if (G.sched) {
         const uint32_t sgw = ((uint32_t)A.t8x + kSide - 1u) / kSide;
-        const uint32_t li = block / 32u;
         col = (int)((sst % sgw) * kSide + (li % (kSide * kSide)) / kSide);
         row = (int)((sst / sgw) * kSide + li % kSide);
     } else {
-        const uint32_t li = block / 32u;
         const SuperTile st = super_tile(A.cov_sq, A.cov_nx, (li >> 4) * 8u + block % 8u);
         col = st.x * 4 + (int)((li & 15u) >> 2);
         row = st.y * 4 + (int)(li & 3u);
     }
-    const int lane = threadIdx.x & 63, sub = lane & 3;
+    const int lane = threadIdx.x & 63, sub = lane & (LPR - 1);
     const int pi0 = col * 8 + (int)(quarter & 1u) * 4, pj0 = row * 8 + (int)(quarter >> 1) * 4;
     if (pi0 >= A.width || pj0 >= A.height) return;
     // a tile's time is that of its first quarter (the quarters' times lie close together)
     const bool timed = A.sched_time && quarter == 0u;
     const unsigned long long tile_t0 = timed ? wall_clock64() : 0ull;
-    const int pi = pi0 + ((lane >> 2) & 3);
-    const int pj = pj0 + (lane >> 4);
+    const int pi = pi0 + (LPR == 4 ? (lane >> 2) & 3 : lane & 7);
+    const int pj = pj0 + (LPR == 4 ? lane >> 4 : lane >> 3);
     const bool valid = pi < A.width && pj < A.height;
-    const bool lead = sub == 0;             // the quad's lane that writes the ray's outputs
+    const bool lead = sub == 0;             // the ray's lane that writes its outputs
     const int64_t ray = (int64_t)pj * A.width + pi;
 
     Counters cnt;
-    float C0 = 0.f, C1 = 0.f, C2 = 0.f, T = 1.f;
+    float C[3][4 / LPR] = {}, T = 1.f;      // this lane's partial colour sums
     int nseg = 0, nsamp_total = 0;
     Ray R;
     bool alive = valid && setup_ray(A, pi, pj, R);
@@ -135,9 +137,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
                 Ckpt c;
                 c.t = t;
                 c.T = T;
-                c.C[0] = quad_sum(C0 + D0);
-                c.C[1] = quad_sum(C1 + D1);
-                c.C[2] = quad_sum(C2 + D2);
+                c.C[0] = quad_sum(C[0][0] + D0);
+                c.C[1] = quad_sum(C[1][0] + D1);
+                c.C[2] = quad_sum(C[2][0] + D2);
                 c.rec = (int32_t)tpos;
                 c.sidx = nsamp_total;
                 if (lead) ck[nck] = c;
@@ -223,7 +225,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
             if (tq_due(Q, has && k + sub < S.n ? pt.pend : 0u, lane))
                 tapq_flush<REC, LAY, NEAR, kCk>(A, s_lut, Q, lane, cnt, tape_base);
             if (has) {
-                const QuadStep q = lit_step<REC, LAY, NEAR>(A, s_lut, Q, lane, R, S, k, pt, T, C0, C1, C2, cnt, trow, tpos);
+                const QuadStep q = lit_step<REC, LAY, NEAR>(A, s_lut, Q, lane, R, S, k, pt, T, C[0][0], C[1][0], C[2][0], cnt,
+                                                                trow, tpos);
                 nsamp_total += q.n;
                 k += 4;
                 if (q.stop) alive = false;
@@ -232,9 +235,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
         }
         float D0, D1, D2;
         tapq_finish<REC, LAY, NEAR, kCk>(A, s_lut, Q, lane, cnt, D0, D1, D2, tape_base);
-        C0 += D0;
-        C1 += D1;
-        C2 += D2;
+        C[0][0] += D0;
+        C[1][0] += D1;
+        C[2][0] += D2;
     } else {
         double tcur = R.t0;
         uint32_t start = 0;
@@ -253,7 +256,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
                 setup_segment<LIT, LAY>(A, R, L, leaf, tcur, tb, S);
                 nsm = S.n;
                 bool stop;
-                nsamp_total += composite_unlit_quad<REC, NEAR, LAY>(A, s_lut, R, S, sub, T, C0, C1, C2, stop, cnt);
+                if constexpr (LPR == 4) {
+                    nsamp_total += composite_unlit_quad<REC, NEAR, LAY>(A, s_lut, R, S, sub, T, C[0][0], C[1][0], C[2][0],
+                                                                        stop, cnt);
+                } else {
+                    float tseg = 1.f;
+                    nsamp_total += composite_unlit<LAY, NEAR>(A, s_lut, R, S, T, C, tseg, stop, cnt);
+                }
                 if (stop) alive = false;
             }
             if (REC && A.trace) trace(leaf, p, nsm, tcur, tb);
@@ -266,9 +275,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT || REC |
             tcur = tb;
         }
     }
-    C0 = quad_sum(C0);
-    C1 = quad_sum(C1);
-    C2 = quad_sum(C2);
+    const float C0 = ray_sum<LPR>(C[0]), C1 = ray_sum<LPR>(C[1]), C2 = ray_sum<LPR>(C[2]);
     if (timed && lane == 0) {
         const unsigned long long dt = wall_clock64() - tile_t0;
         A.sched_time[A.tile0 + (int64_t)row * A.t8x + col] = dt < 0xffffffffull ? (uint32_t)dt : 0xffffffffu;
@@ -1006,7 +1013,7 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
         memset(&G, 0, sizeof(G));
         SchedGroup SG;
         memset(&SG, 0, sizeof(SG));
-        int64_t blocks = 0;
+        int64_t places = 0;
         int64_t rel = 0;
         const int64_t order0 = tile_off;
         uint32_t nst = 0;
@@ -1019,7 +1026,7 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
             if (i == 0) A = Ai;
             G.cam[i] = cam_args_of(Ai, rel);
             if (!sched && (rc = check_sides(cams[c0 + i])) != AMR_OK) return rc;
-            blocks = std::max(blocks, cover_blocks(cover_of(Ai.t8x, Ai.t8y, kLaunchSlack).n, 4));
+            places = std::max(places, cover_of(Ai.t8x, Ai.t8y, kLaunchSlack).n);
             SG.tile0[i] = tile_off;
             SG.t8x[i] = Ai.t8x;
             SG.t8y[i] = Ai.t8y;
@@ -1058,16 +1065,17 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
         A.touch = P->d_touch;
         A.ckpt_ray0 = pix_off;
         const bool rec = A.trace || A.trace_n || A.nsamp || A.stats || A.touch || A.touch_meta || A.ckpt;
-        // scheduled: one-dimensional, four blocks per tile, ranks dealt to the 8 XCDs in turn
-        if (sched) {
-            blocks = 32 * (int64_t)(side * side) * (((int64_t)nst + 7) / 8);
-            if (blocks / 4 >= kMaxSchedTiles) {
-                set_error("the tile schedule takes fewer than 2^26 tiles of 8x8 pixels in a group of %d cameras", kCamGroup);
-                return AMR_EINVAL;
-            }
+        // the kernels that record everything but checkpoints read the layout at run time
+        const bool full = rec && !(A.ckpt && !A.nearest && !A.trace && !A.trace_n && !A.nsamp && !A.stats && !A.touch && !A.touch_meta);
+        const int lpr = A.lighting || rec ? 4 : lanes_per_ray(rel / n, A.depth);
+        if (sched && (int64_t)(side * side) * 8 * (((int64_t)nst + 7) / 8) >= kMaxSchedTiles) {
+            set_error("the tile schedule takes fewer than 2^26 tiles of 8x8 pixels in a group of %d cameras", kCamGroup);
+            return AMR_EINVAL;
         }
+        // scheduled: one-dimensional, ranks dealt to the 8 XCDs in turn
+        const int64_t blocks = sched ? 8 * lpr * (int64_t)(side * side) * (((int64_t)nst + 7) / 8) : cover_blocks(places, lpr);
         const dim3 g = block_grid(blocks, sched ? 1 : n), b(64);
-        if (rec && !(A.ckpt && !A.nearest && !A.trace && !A.trace_n && !A.nsamp && !A.stats && !A.touch && !A.touch_meta)) {
+        if (full) {
             if (A.nearest && A.lighting) hipLaunchKernelGGL((render_fwd<true, true, true, -1>), g, b, 0, s, A, G);
             else if (A.nearest) hipLaunchKernelGGL((render_fwd<false, true, true, -1>), g, b, 0, s, A, G);
             else if (A.lighting) hipLaunchKernelGGL((render_fwd<true, true, false, -1>), g, b, 0, s, A, G);
@@ -1075,17 +1083,18 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
         } else {   // the timed variants, one per brick layout
             with_layout(A, [&](auto lay) {
                 constexpr int L = decltype(lay)::value;
-                if (A.nearest) {
-                    if (A.lighting) hipLaunchKernelGGL((render_fwd<true, false, true, L>), g, b, 0, s, A, G);
-                    else hipLaunchKernelGGL((render_fwd<false, false, true, L>), g, b, 0, s, A, G);
-                } else if (A.ckpt) {       // checkpoints (and the tape) only: the adjoint's forward pass
-                    if (A.lighting) hipLaunchKernelGGL((render_fwd<true, false, false, L, true>), g, b, 0, s, A, G);
-                    else hipLaunchKernelGGL((render_fwd<false, false, false, L, true>), g, b, 0, s, A, G);
-                } else if (A.lighting) {
-                    hipLaunchKernelGGL((render_fwd<true, false, false, L>), g, b, 0, s, A, G);
-                } else {
-                    hipLaunchKernelGGL((render_fwd<false, false, false, L>), g, b, 0, s, A, G);
+                if (A.lighting) {
+                    if (A.nearest) hipLaunchKernelGGL((render_fwd<true, false, true, L>), g, b, 0, s, A, G);
+                    // checkpoints (and the tape) only: the adjoint's forward pass
+                    else if (A.ckpt) hipLaunchKernelGGL((render_fwd<true, false, false, L, true>), g, b, 0, s, A, G);
+                    else hipLaunchKernelGGL((render_fwd<true, false, false, L>), g, b, 0, s, A, G);
+                    return;
                 }
+                if (A.ckpt) hipLaunchKernelGGL((render_fwd<false, false, false, L, true>), g, b, 0, s, A, G);
+                else if (lpr == 1 && A.nearest) hipLaunchKernelGGL((render_fwd<false, false, true, L, false, 1>), g, b, 0, s, A, G);
+                else if (lpr == 1) hipLaunchKernelGGL((render_fwd<false, false, false, L, false, 1>), g, b, 0, s, A, G);
+                else if (A.nearest) hipLaunchKernelGGL((render_fwd<false, false, true, L>), g, b, 0, s, A, G);
+                else hipLaunchKernelGGL((render_fwd<false, false, false, L>), g, b, 0, s, A, G);
             });
         }
         int rc = check_hip(hipGetLastError(), "render_fwd launch");

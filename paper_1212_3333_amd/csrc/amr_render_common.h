@@ -1218,7 +1218,7 @@ __device__ __forceinline__ float sum4(const float p[4]) { return (p[0] + p[1]) +
 // repeats its last sample, which is not composited, and samples past early termination are not
 // composited either.  tseg: the segment's own transmittance, multiplied alike.  Returns the
 // samples composited; stop: the ray terminated in this segment.
-template <int LAY>
+template <int LAY, bool NEAR = false>
 __device__ __forceinline__ int composite_unlit(const RenderArgs &A, const float4 *s_lut, const Ray &R,
                                                const Segment &S, float &T, float (&C)[3][4], float &tseg, bool &stop,
                                                Counters &cnt) {
@@ -1228,7 +1228,7 @@ __device__ __forceinline__ int composite_unlit(const RenderArgs &A, const float4
         SampleVals v[4];
         #pragma unroll
         for (int u = 0; u < 4; u++)
-            eval_sample<false, false, false, LAY>(A, s_lut, R, S, min(k + u, S.n - 1), v[u], cnt);
+            eval_sample<false, false, NEAR, LAY>(A, s_lut, R, S, min(k + u, S.n - 1), v[u], cnt);
         #pragma unroll
         for (int u = 0; u < 4; u++) {
             if (!stop && k + u < S.n) {
@@ -1271,6 +1271,14 @@ __device__ __forceinline__ float quad_lane(float v) {
 __device__ __forceinline__ float quad_sum(float v) {
     const float w = v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xf, 0xf, true));
     return w + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(w), 0x4E, 0xf, 0xf, true));
+}
+
+// A ray's colour from what one of its lanes holds: with four lanes per ray a partial sum each, with one
+// all four.
+template <int LPR>
+__device__ __forceinline__ float ray_sum(const float (&p)[4 / LPR]) {
+    if constexpr (LPR == 4) return quad_sum(p[0]);
+    else return sum4(p);
 }
 
 // One step of a quad: its four samples' opacities (sub: this lane's place; valid: its sample lies

@@ -46,6 +46,21 @@ constexpr SuperTile super_tile(int32_t sq, int32_t nx, uint32_t i) {
     return SuperTile{x, y};
 }
 
+// Lanes that march a ray of an unlit image, of `pixels` pixels on average in its launch.  Four while a ray's
+// chain of dependent reads is what the image waits for; one when there are rays enough to cover it:
+// then the walk from leaf to leaf, which four lanes pay four times, and the part of a segment's last
+// step that is empty count, and neighbouring rays share bricks as a ray's samples do.  In a deep tree a ray's
+// segments are more, and its chain longer, so that the line lies further up.  Four lanes, one lane and
+// (before four were tried) one that restarted its walks, in ms: 300 patches, 1024^2 2.21, 1.94, 2.38;
+// 1536^2 4.41, 3.35, 4.10; 2048^2 7.34, 5.32, 6.54; 4096^2 27.0, 17.2, 21.3.  2000 patches, 1024^2 3.12,
+// 3.79, 4.41; 1280^2 4.60, 4.68, 5.70; 1536^2 5.90, 5.55, 6.74; 4096^2 32.1, 24.0, 29.7.  20 levels
+// (depth 82), 1024^2 1.02, 1.47, 2.42; 1536^2 1.49, 1.73, 2.91; 2048^2 2.54, 2.54, 4.28; 4096^2 9.5, 6.2,
+// 8.7.  Views of 512^2 and 768^2, eight to a launch, are better off with four lanes in both scenes,
+// or as well.
+constexpr int lanes_per_ray(int64_t pixels, int32_t depth) {
+    return pixels < (depth < 48 ? (int64_t)3 << 19 : (int64_t)1 << 22) ? 4 : 1;
+}
+
 // Blocks of a launch over n super-tiles, dealt to the 8 XCDs in turn (block i on XCD i mod 8), with `per`
 // blocks to a tile; block i renders part (i / 8) % per of tile (i / (8 per)) % 16 of super-tile
 // (i / (128 per)) * 8 + i % 8.
