@@ -130,8 +130,10 @@ constexpr int kNetMinSamples = 32;
 // DEC: how data segments are decided: 0 all sampled plainly (logging), 1 skipped by the
 // analytic bound alone, 2 the bound and then the network (G.mlp set).  LOG: segments are logged
 // for training (G.seglog set).  LAY: the brick layout (-1: read at run time).
+// Waves per SIMD: the most at which the timed forms do not spill.  By the bound alone 4, 124 VGPRs: 768^2
+// of a 20-level scene 1.52 ms, and at 5, with 116 to 168 bytes of scratch per lane, 1.76 ms.
 template <bool LIT, int DEC, bool LOG, int LAY>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT ? 2 : (LOG ? 4 : (DEC == 2 ? 3 : 5))))) void render_learned(RenderArgs A, LearnArgs G) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT ? 2 : (LOG || DEC == 1 ? 4 : (DEC == 2 ? 3 : 5))))) void render_learned(RenderArgs A, LearnArgs G) {
     __shared__ LearnLds s;
     NetLds *sn = nullptr;
     for (int i = threadIdx.x; i < 256; i += 64) s.lut[i] = A.lut[i];
