@@ -347,6 +347,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LIT ? 2 : (L
             if (tb <= tcur) {
                 cnt.guard++;
                 tb = nextafter(tcur, INFINITY);
+                start = 0;
             }
             tcur = tb;
         }

@@ -513,7 +513,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LIT ? 3 : 4
                     adjoint_sample<LIT, false>(A, v, dlt, a, acc, run, gs);
                 }
             }
-            if (tb <= tcur) tb = nextafter(tcur, INFINITY);
+            if (tb <= tcur) {
+                tb = nextafter(tcur, INFINITY);
+                start = 0;
+            }
             tcur = tb;
         }
     }
