@@ -1372,7 +1372,6 @@ struct TapQueue {
     unsigned long long bstart[2];  // bit j: the samples queued by one step start at slot j
 };
 
-constexpr int kTapList = 6 * kTapQ;
 struct TapQueueList : TapQueue {   // with the list of taps that a resolution hands to the lanes
     float val[kTapList];           // a resolved tap's value
     uint16_t tap[kTapList];        // slot | t << 6; resolved: | 512 where it holds data
@@ -1404,19 +1403,8 @@ __device__ __forceinline__ uint32_t tq_taps(TapQueue &Q) {
 }
 
 // The sum of the active lanes' n <= 7, and the sum over the lanes below this one.
-struct LaneSum {
-    uint32_t all, below;
-};
 __device__ __forceinline__ LaneSum lane_sum(uint32_t n, int lane) {
-    LaneSum r{0u, 0u};
-    const unsigned long long low = lanes_below(lane);
-    #pragma unroll
-    for (int b = 0; b < 3; b++) {
-        const unsigned long long m = __ballot((n >> b) & 1u);
-        r.all += popc64(m) << b;
-        r.below += popc64(m & low) << b;
-    }
-    return r;
+    return lane_sums(__ballot(n & 1u), __ballot((n >> 1) & 1u), __ballot((n >> 2) & 1u), lane);
 }
 
 // Whether the queue must be resolved before the active lanes queue their next samples, each with the
@@ -1425,8 +1413,7 @@ __device__ __forceinline__ LaneSum lane_sum(uint32_t n, int lane) {
 template <class TQ>
 __device__ __forceinline__ bool tq_due(TQ &Q, uint32_t pend, int lane) {
     if (!kTapPerLane<TQ>) return tapq_full(tq_count(Q), __ballot(pend != 0u));
-    const uint32_t taps = tq_taps(Q);
-    return taps > 0u && taps + lane_sum(popc64(pend), lane).all > (uint32_t)kTapQ;
+    return tapq_list_full(tq_taps(Q), lane_sum(popc64(pend), lane).all);
 }
 
 __device__ __forceinline__ unsigned long long tq_bstart(TapQueue &Q, int w) {

@@ -54,6 +54,23 @@ constexpr uint32_t tapq_run_end(uint64_t b0, uint64_t b1, uint32_t s, uint32_t n
     return above ? 64u + ctz64(above) : n;
 }
 
+// One tap per lane: the taps that queued samples have pending are counted too, as a resolution hands them to
+// the lanes.  The queue holding `taps` must be resolved before a step that adds `more`, unless it is
+// empty: a step's own samples always fit, with up to six taps each.
+constexpr int kTapList = 6 * kTapQ;
+constexpr bool tapq_list_full(uint32_t taps, uint32_t more) { return taps > 0u && taps + more > (uint32_t)kTapQ; }
+
+// Sums over lanes of a number below 8, given the masks of the lanes that have its bits 0, 1 and 2 set: over all
+// of them, and over those below a lane.
+struct LaneSum {
+    uint32_t all, below;
+};
+constexpr LaneSum lane_sums(uint64_t m0, uint64_t m1, uint64_t m2, int lane) {
+    const uint64_t low = lanes_below(lane);
+    return LaneSum{popc64(m0) + 2u * popc64(m1) + 4u * popc64(m2),
+                   popc64(m0 & low) + 2u * popc64(m1 & low) + 4u * popc64(m2 & low)};
+}
+
 // The stepped lit loop fetches segments (instead of sampling) in a step where at least a quarter of
 // the live lanes wait for one.  (With four lanes per ray: 1024^2 view of the cosmology-like scene
 // 12.75 ms, against 12.81 ms at a half, 13.56 ms at three quarters and 12.86 ms at an eighth; 517x389
@@ -62,6 +79,9 @@ constexpr bool stepped_fetch(uint64_t live, uint64_t waiting) {
     return waiting == live || 4u * popc64(waiting) >= popc64(live);
 }
 
+static_assert(!tapq_list_full(0, 6 * 64) && !tapq_list_full(60, 4) && tapq_list_full(60, 5), "taps of a wave");
+static_assert(lane_sums(0b1011ull, 0b1001ull, 0b0001ull, 3).all == 11 && lane_sums(0b1011ull, 0b1001ull, 0b0001ull, 3).below == 8,
+              "lanes with 7, 1, 0 and 3");
 static_assert(tapq_slot(5, 0b1011ull, 3) == 7, "slot of lane 3 after lanes 0 and 1");
 static_assert(tapq_run_end(0b101ull, 0ull, 0, 9) == 2 && tapq_run_end(0b101ull, 0ull, 2, 9) == 9, "runs");
 static_assert(tapq_run_end(1ull << 63, 1ull, 63, 70) == 64 && tapq_run_end(0ull, 0b11ull, 64, 70) == 65, "runs");
