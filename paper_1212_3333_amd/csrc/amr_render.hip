@@ -89,7 +89,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LPR == 1 ? 4
     }
     const int lane = threadIdx.x & 63, sub = lane & (LPR - 1);
     const int pi0 = col * 8 + (int)(quarter & 1u) * 4, pj0 = row * 8 + (int)(quarter >> 1) * 4;
-    if (pi0 >= A.width || pj0 >= A.height) return;
+    if (pi0 >= A.width || pj0 >= A.height) return;      // the whole block, before it has read anything
+    for (int i = threadIdx.x; i < 256; i += 64) s_lut[i] = A.lut[i];
+    __syncthreads();
     // a tile's time is that of its first quarter (the quarters' times lie close together)
     const bool timed = A.sched_time && quarter == 0u;
     const unsigned long long tile_t0 = timed ? wall_clock64() : 0ull;
@@ -104,10 +106,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LPR == 1 ? 4
     int nseg = 0, nsamp_total = 0;
     Ray R;
     bool alive = valid && setup_ray(A, pi, pj, R);
-    if (__ballot(alive)) {                  // a block whose rays all miss reads nothing
-        for (int i = threadIdx.x; i < 256; i += 64) s_lut[i] = A.lut[i];
-        __syncthreads();
-    }
     if (REC) cnt.hit = alive && lead ? 1 : 0;
     // checkpoints for the adjoint: (t, T, C) at the start of every `every`-th data segment
     CkptHeader *ckh = nullptr;

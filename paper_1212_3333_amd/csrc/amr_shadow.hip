@@ -167,7 +167,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void sh
     const int lane = threadIdx.x & 63, sub = lane & 3;
     const int pi0 = (st.x * 4 + (int)((li & 15u) >> 2)) * 8 + (int)(quarter & 1u) * 4;
     const int pj0 = (st.y * 4 + (int)(li & 3u)) * 8 + (int)(quarter >> 1) * 4;
-    if (pi0 >= A.width || pj0 >= A.height) return;
+    if (pi0 >= A.width || pj0 >= A.height) return;      // the whole block, before it has read anything
+    for (int i = threadIdx.x; i < 256; i += 64) s_lut[i] = A.lut[i];
+    __syncthreads();
     const int pi = pi0 + ((lane >> 2) & 3);
     const int pj = pj0 + (lane >> 4);
     const bool valid = pi < A.width && pj < A.height;
@@ -179,10 +181,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void sh
     int nseg = 0, nsamp_total = 0;
     Ray R;
     bool alive = valid && setup_ray(A, pi, pj, R);
-    if (__ballot(alive)) {                  // a block whose rays all miss reads nothing
-        for (int i = threadIdx.x; i < 256; i += 64) s_lut[i] = A.lut[i];
-        __syncthreads();
-    }
     if (REC) cnt.hit = alive && lead ? 1 : 0;
     const int64_t base = (PASS != kPassCount && valid) ? W.off[ray] : 0;
     // the later passes stay inside this ray's jobs even if a sample count came out differently
