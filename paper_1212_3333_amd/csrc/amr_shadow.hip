@@ -30,10 +30,12 @@ namespace amr {
 // a walk from the root finds the same leaf, and the march starts there.
 // The calling lanes step together: a step fetches the next segments once half of the live lanes wait
 // for one, else it takes kLightBatch samples (read together, summed in sample order) on every lane
-// that has a segment.  What bounds it: gathers, in the address units for a loop per segment, as
-// long as its longest lane's (26 of 64 lanes active, 1.1 G vector loads at 384x288 with 27 M rays:
-// 35.3 ms), in L1 misses for the stepped loop, whose lanes drift apart (0.8 G loads, 2.6 times the L2
-// reads at two samples a step: 34.1 ms); four samples of one lane share rows: 32.0 ms.
+// that has a segment.  What bounds it: gathers, in the address units for a loop per segment, as long as
+// its longest lane's (26 of 64 lanes active, 1.1 G vector loads at 384x288 with 27 M rays), in L1 misses
+// for the stepped loop, whose lanes drift apart (0.8 G loads, 2.6 times the L2 reads at two samples a step);
+// four samples of one lane share rows.  A frame of 384x288 (250 patches), all passes: a loop per segment
+// 34.5 ms, with four samples a step 35.1; stepped with one sample 36.0, two 34.9, four 32.1, eight (which
+// spill) 64.5.
 constexpr int kLightBatch = 4;
 constexpr bool light_fetch(uint64_t live, uint64_t waiting) { return 2u * popc64(waiting) >= popc64(live); }
 
