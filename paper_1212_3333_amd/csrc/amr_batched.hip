@@ -1,7 +1,8 @@
 // Persistent multi-camera raycasting: one launch renders many cameras of different sizes.
 //
 // Work unit: a quarter (16 pixels) of a 64-pixel tile (tile_w x tile_h), rendered by one wave with
-// four lanes per ray and the per-ray code of the single-camera kernel.  Waves take units from one global atomic
+// four lanes per ray, or the tile with one (unlit images of many pixels), and the per-ray code of the
+// single-camera kernel.  Waves take units from one global atomic
 // queue that lists the cameras largest first, so the short images of a batch fill the tail of
 // the long ones.  The wave that finishes an image's last tile writes the device clock into
 // stamps[camera]; the wave that takes tile 0 writes stamps[ncams] (launch start).  Everything
@@ -16,14 +17,14 @@ namespace amr {
 // Queue scratch layout (amr_queue_bytes): counters first, then per-camera tables.  There are
 // kQueues tile queues: with XCD-aware tiles, queue x serves the waves of blocks x, x + 8, ...
 // (the hardware deals blocks to the 8 XCDs in turn) and lists, image by image, the 4x4-tile
-// super-tiles x, x + 8, x + 16, ... of each image along a Morton curve, as the single-camera
+// super-tiles x, x + 8, x + 16, ... of each image along Morton curves, as the single-camera
 // kernel deals them; otherwise queue 0 lists every image's tiles row by row.
 constexpr int kQueues = 8;
 
 struct QueueView {
     unsigned int *next;          // [kQueues] next unit of each queue, 64 bytes apart
     unsigned int *done;          // [ncams] units finished per camera
-    unsigned int *ntiles;        // [ncams] units (quarter tiles) of each camera over all queues
+    unsigned int *ntiles;        // [ncams] units of each camera over all queues
     int *order;                  // [ncams] cameras in queue order
     long long *tile0;            // [kQueues][ncams + 1] first unit of the k-th camera in `order`
     long long *pix0;             // [ncams] first pixel of camera c in the rgba output

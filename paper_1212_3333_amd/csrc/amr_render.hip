@@ -1,7 +1,7 @@
 // Device side of libamr: the single-pass raycaster (Section 5.3), its adjoint, and launchers.
 //
-// In the forward kernel four lanes march one ray and a wave64 covers 4x4 pixels, one wave per block;
-// in the adjoint a lane owns one ray's interval, four waves per block.
+// In the forward kernel four lanes march one ray and a wave64 covers 4x4 pixels, one wave per block (unlit
+// images of many pixels: one lane, 8x8 pixels); in the adjoint a lane owns one ray's interval, four waves per block.
 // The FP64 parts (ray generation, slab clip, kD-restart planes, sample positions of gradient
 // taps) are written with contraction disabled so that every operation is correctly rounded
 // exactly once; the per-sample arithmetic (trilinear, LUT, exp, compositing) is fp32 in
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LPR == 1 ? 4
     TQ *tq = nullptr;
     if constexpr (kDefer) tq = tap_queues<1, TQ>();
     // One wave per block: 4x4 pixels, four waves per 8x8 tile, or with one lane per ray a tile.  Tiles are grouped in 4x4
-    // super-tiles (32x32 pixels) numbered along a Morton curve; blocks are dealt round-robin to the
+    // super-tiles (32x32 pixels) numbered along Morton curves (Cover); blocks are dealt round-robin to the
     // 8 XCDs and XCD x renders super-tiles x, x + 8, x + 16, ...  Every XCD thus gets a share of
     // every part of the image (the work per tile varies by 10x and more across the screen), while
     // the tiles in flight on one XCD stay grouped in a few compact 32x32 patches whose rays

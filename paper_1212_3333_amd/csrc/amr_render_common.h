@@ -1258,7 +1258,9 @@ __device__ __forceinline__ int composite_unlit(const RenderArgs &A, const float4
 // apart, fall into the same rows and cache lines, where the stencils of neighbouring pixels lie
 // several fine cells apart.  The walk is paid four times; ropes keep it short.  One lane per ray
 // against four: lit, 256^2 of a tiny scene 583 -> 175 us, 517x389 5.27 -> 1.94 ms, 1024^2 14.8 -> 12.9
-// ms; unlit, 1024^2 3.47 -> 2.54 ms, 1024^2 of a 20-level hierarchy 1.92 -> 1.29 ms.  What bounds them
+// ms; unlit, 1024^2 3.47 -> 2.54 ms, 1024^2 of a 20-level hierarchy 1.92 -> 1.29 ms.  Unlit images of many
+// more pixels are faster with one (lanes_per_ray); lit ones of 4096^2 take the same or 4 % longer with
+// four, and nearest-cell lit ones a quarter less.  What bounds them
 // now: VALU issue (73% of the cycles at 1024^2, lit and unlit, 41 and 44 of 64 lanes active).
 
 // The value of lane U of the quad (every lane of the quad active).
