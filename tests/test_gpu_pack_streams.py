@@ -72,3 +72,30 @@ def test_pack_gives_its_memory_back(gpu):
             break
         time.sleep(0.02)
     assert held < 16 << 20
+
+
+def test_packs_from_several_threads(gpu):
+    """Four threads pack their hierarchies at once, each on its own stream, again and again."""
+    import threading
+    import torch
+    amr = gpu
+    hs = [workloads.cosmology_like(i, root=32, nlevels=4, target_patches=20 + 10 * i) for i in range(4)]
+    trees = [amr.build_tree(h) for h in hs]
+    refs = [amr.pack(t, h) for t, h in zip(trees, hs)]
+    torch.cuda.synchronize()
+    bad = []
+
+    def work(i):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            for _ in range(6):
+                got = amr.pack(trees[i], hs[i])
+                s.synchronize()
+                if not (torch.equal(got.pool[:-256], refs[i].pool[:-256]) and torch.equal(got.meta, refs[i].meta)):
+                    bad.append(i)
+    th = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for x in th:
+        x.start()
+    for x in th:
+        x.join()
+    assert not bad
