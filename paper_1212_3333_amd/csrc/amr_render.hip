@@ -39,7 +39,7 @@ namespace amr {
 // spills, 6.1 ms).
 template <bool LIT, bool REC, bool NEAR, int LAY, bool CK = false, int LPR = 4>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LPR == 1 ? 4 : (LIT || REC || NEAR ? 3 : 5)))) void render_fwd(RenderArgs A, CamGroup G) {
-    static_assert(LPR == 4 || (LPR == 1 && !LIT && !REC && !CK));
+    static_assert(LPR == 4 || (LPR == 1 && !LIT && !REC));
     // scheduled launches: this block's camera and super-tile from the order (or, before a call
     // has recorded it, camera by camera, super-tiles row by row)
     const uint32_t block = block_number();
@@ -135,9 +135,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LPR == 1 ? 4
                 Ckpt c;
                 c.t = t;
                 c.T = T;
-                c.C[0] = quad_sum(C[0][0] + D0);
-                c.C[1] = quad_sum(C[1][0] + D1);
-                c.C[2] = quad_sum(C[2][0] + D2);
+                if constexpr (LPR == 4) {
+                    c.C[0] = quad_sum(C[0][0] + D0);
+                    c.C[1] = quad_sum(C[1][0] + D1);
+                    c.C[2] = quad_sum(C[2][0] + D2);
+                } else {
+                    #pragma unroll
+                    for (int a = 0; a < 3; a++) c.C[a] = sum4(C[a]);
+                }
                 c.rec = (int32_t)tpos;
                 c.sidx = nsamp_total;
                 if (lead) ck[nck] = c;
@@ -1068,7 +1073,7 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
         const bool rec = A.trace || A.trace_n || A.nsamp || A.stats || A.touch || A.touch_meta || A.ckpt;
         // the kernels that record everything but checkpoints read the layout at run time
         const bool full = rec && !(A.ckpt && !A.nearest && !A.trace && !A.trace_n && !A.nsamp && !A.stats && !A.touch && !A.touch_meta);
-        const int lpr = A.lighting || rec ? 4 : lanes_per_ray(rel / n, A.depth);
+        const int lpr = A.lighting || full ? 4 : lanes_per_ray(rel / n, A.depth, A.ckpt != nullptr);
         if (sched && (int64_t)(side * side) * 8 * (((int64_t)nst + 7) / 8) >= kMaxSchedTiles) {
             set_error("the tile schedule takes fewer than 2^26 tiles of 8x8 pixels in a group of %d cameras", kCamGroup);
             return AMR_EINVAL;
@@ -1091,7 +1096,8 @@ int amr_render(const amr_scene *S, const amr_camera *cams, int32_t ncams, const 
                     else hipLaunchKernelGGL((render_fwd<true, false, false, L>), g, b, 0, s, A, G);
                     return;
                 }
-                if (A.ckpt) hipLaunchKernelGGL((render_fwd<false, false, false, L, true>), g, b, 0, s, A, G);
+                if (A.ckpt && lpr == 1) hipLaunchKernelGGL((render_fwd<false, false, false, L, true, 1>), g, b, 0, s, A, G);
+                else if (A.ckpt) hipLaunchKernelGGL((render_fwd<false, false, false, L, true>), g, b, 0, s, A, G);
                 else if (lpr == 1 && A.nearest) hipLaunchKernelGGL((render_fwd<false, false, true, L, false, 1>), g, b, 0, s, A, G);
                 else if (lpr == 1) hipLaunchKernelGGL((render_fwd<false, false, false, L, false, 1>), g, b, 0, s, A, G);
                 else if (A.nearest) hipLaunchKernelGGL((render_fwd<false, false, true, L>), g, b, 0, s, A, G);

@@ -56,9 +56,11 @@ constexpr SuperTile super_tile(int32_t sq, int32_t nx, uint32_t i) {
 // 3.79, 4.41; 1280^2 4.60, 4.68, 5.70; 1536^2 5.90, 5.55, 6.74; 4096^2 32.1, 24.0, 29.7.  20 levels
 // (depth 82), 1024^2 1.02, 1.47, 2.42; 1536^2 1.49, 1.73, 2.91; 2048^2 2.54, 2.54, 4.28; 4096^2 9.5, 6.2,
 // 8.7.  Views of 512^2 and 768^2, eight to a launch, are better off with four lanes in both scenes,
-// or as well.
-constexpr int lanes_per_ray(int64_t pixels, int32_t depth) {
-    return pixels < (depth < 48 ? (int64_t)3 << 19 : (int64_t)1 << 22) ? 4 : 1;
+// or as well.  With checkpoints the line lies further up in shallow trees too: 300 patches, 1280^2 3.50,
+// 3.44, 3.43; 2048^2 7.78, 6.67, 6.71; 4096^2 28.4, 20.4, 21.4.  2000 patches, 1280^2 4.86, 6.52, 6.33;
+// 1536^2 6.36, 7.74, 7.53; 2048^2 10.2, 10.7, 10.3; 4096^2 34.0, 30.3, 30.3.
+constexpr int lanes_per_ray(int64_t pixels, int32_t depth, bool ckpt = false) {
+    return pixels < (depth < 48 && !ckpt ? (int64_t)3 << 19 : (int64_t)1 << 22) ? 4 : 1;
 }
 
 // Blocks of a launch over n super-tiles, dealt to the 8 XCDs in turn (block i on XCD i mod 8), with `per`

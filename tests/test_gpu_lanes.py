@@ -1,5 +1,5 @@
-"""Unlit images of many pixels are marched with one lane per ray, smaller ones and every recording render with
-four: the images agree bit for bit, in every layout, for both samplings, with a level of detail, with a tile
+"""Unlit images of many pixels are marched with one lane per ray, smaller ones and every render that records
+more than checkpoints with four: the images agree bit for bit, in every layout, for both samplings, with a level of detail, with a tile
 schedule, in groups and in persistent batches, at sizes on either side of the rule."""
 import pytest
 
@@ -78,3 +78,21 @@ def test_persistent(gpu, scene_of, sizes, kw):
             if stamped:
                 s = stamps.cpu()
                 assert int(s[-1]) > 0 and bool((s[:-1] >= s[-1]).all())
+
+
+@pytest.mark.parametrize("cap", [2, 4])
+@pytest.mark.parametrize("sizes", [[(2048, 2048)], [(2047, 2049)], [(2050, 2047), (2051, 2061)]], ids=str)
+def test_checkpoints(gpu, scene_of, sizes, cap):
+    """The images, checkpoints and headers of a checkpointed forward (one lane from 2^22 pixels on) are
+    those of the recording render, whose quads write them."""
+    import torch
+    lut, prm = _setup()
+    scene, cams = scene_of(2), [_cam(w, h, 0.3 * i) for i, (w, h) in enumerate(sizes)]
+    n = sum(w * h for w, h in sizes)
+    got = []
+    for kw in ({}, dict(stats=True)):
+        ck = gpu.Checkpoints(n, "cuda", 2, cap)
+        ck.buf.zero_()
+        got.append((gpu.render(scene, cams, lut, prm, **ck.params(), **kw)["rgba"].flatten(), ck.buf))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert int(got[0][1].view(n, -1)[:, 20:24].view(torch.int32).max()) == cap      # rays ran out of records
